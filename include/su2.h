@@ -167,14 +167,16 @@ su2_status su2_ape_smear(su2_lattice lat, double alpha, int nsteps);
  * three spatial directions.  Spatial lines use the smeared links when
  * su2_ape_smear produced them since the last update, else the raw links;
  * the temporal sides always use the raw links.  The handle keeps a device
- * buffer of 3*Rmax*V spatial-line quaternions (grown on demand and kept, so
- * that repeated measurements allocate nothing; freed with the handle).  Rmax <= min(Nx,Ny,Nz), Tmax <= min(Nt, 32), else EINVAL.
+ * buffer of the links in the temporal gauge, (1 + Tmax/Nt) V times 92 bytes
+ * (SU2_F32) or 152 bytes (SU2_F64), grown on demand and kept, so that repeated
+ * measurements allocate nothing; freed with the handle.
+ * Rmax <= min(Nx,Ny,Nz), Tmax <= min(Nt, 32), else EINVAL.
  * Synchronises. */
 su2_status su2_wilson_loops(su2_lattice lat, int Rmax, int Tmax, double *out);
 
 /* Free the measurement buffers the handle keeps between calls: the smeared
- * links (2 x 3V links), the Wilson-line buffer (3 Rmax V quaternions: 382 MB
- * for Rmax = 12 at 24^3 x 48 in binary32) and the Wilson-loop partials.  The
+ * links (2 x 3V links), the gauge-rotated links of the Wilson loops (81 MB
+ * for Tmax = 16 at 24^3 x 48 in binary32) and the Wilson-loop partials.  The
  * next su2_ape_smear / su2_wilson_loops allocates them again; the smeared
  * links are gone (su2_get_smeared: ESTATE).  Synchronises. */
 su2_status su2_release_buffers(su2_lattice lat);

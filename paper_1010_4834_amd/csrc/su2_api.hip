@@ -125,10 +125,12 @@ struct su2_ensemble_s {
     void *sm[2] = {nullptr, nullptr};
     int sm_cur = -1;  // index of the valid smeared buffer, -1 none
 
-    void *wl_s = nullptr;  // spatial lines of the Wilson loops
-    size_t wl_s_bytes = 0;
+    void *wl_p = nullptr;  // temporal prefix products of the Wilson loops
+    size_t wl_p_bytes = 0;
     double *wpart = nullptr;
     size_t wpart_bytes = 0;
+    su2::WPlan wl_plan[2];          // work split of the last Wilson-loop call, for
+    int wl_plan_r = 0, wl_plan_t = 0;  // these bounds
 
     uint32_t *trace = nullptr;
 
@@ -595,7 +597,7 @@ void destroy_common(su2_ensemble_s *E) {
     for (auto e : E->evpool) (void)hipEventDestroy(e);
     void *bufs[] = {E->ddesc, E->tiles, E->stiles, E->vtiles, E->mtiles, E->mtiles_z, E->mtiles_b, E->mtiles_b3, E->st, E->tries_part, E->part_plaq,
                     E->part_poly, E->part_hb, E->fin_cnt, E->fin_chunk, E->res, E->ser_chunk,
-                    E->sm[0], E->sm[1], E->wl_s, E->wpart, E->trace};
+                    E->sm[0], E->sm[1], E->wl_p, E->wpart, E->trace};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     if (E->own_links && E->links) (void)hipFree(E->links);
@@ -1514,44 +1516,58 @@ su2_status su2_wilson_loops(su2_lattice E, int Rmax, int Tmax, double *out) {
     const LatDesc &d = E->hdesc[0];
     const int smin = std::min(d.n[0], std::min(d.n[1], d.n[2]));
     if (!out || Rmax < 1 || Tmax < 1 || Rmax > smin || Tmax > d.n[3] || Tmax > 32) return SU2_EINVAL;
-    const size_t qb = link_size(E->f32);
-    const long long V = E->total_sites;
-    const size_t sb = qb * (size_t)3 * Rmax * V;
-    if (sb > E->wl_s_bytes) {
-        CHK(dalloc(E, &E->wl_s, sb));
-        E->wl_s_bytes = sb;
+    const int npass = Tmax > 16 ? 2 : 1;
+    if (E->wl_plan_r != Rmax || E->wl_plan_t != Tmax) {
+        E->wl_plan_r = 0;
+        int grid = 0;
+        for (int k = 0; k < npass; ++k) {
+            if (!su2::wloops_plan(E->f32, d.n, Rmax, Tmax, 16 * k, E->wl_plan[k])) return SU2_ENOMEM;
+            grid = std::max(grid, E->wl_plan[k].grid);
+        }
+        for (int k = 0; k < npass; ++k) E->wl_plan[k].grid = grid;
+        E->wl_plan_r = Rmax, E->wl_plan_t = Tmax;
     }
-    const KArgs va = kargs(E, 2);
-    const int nparts = su2::wtrace_groups(va);
-    // partials, then the Rmax * Tmax results
-    const size_t pb = sizeof(double) * (2 * (size_t)Rmax * nparts * Tmax + (size_t)Rmax * Tmax);
+    const su2::WPlan *plan = E->wl_plan;
+    const int nparts = plan[0].grid;
+    // per spatial site and time: the prefix product (32 bytes), three links
+    // in its gauge and their weights
+    const int next = d.n[3] + Tmax;
+    const size_t nst = (size_t)d.ns * next, gb = nst * (32 + 3 * (E->f32 ? 20 : 40));
+    if (gb > E->wl_p_bytes) {
+        CHK(dalloc(E, &E->wl_p, gb));
+        E->wl_p_bytes = gb;
+    }
+    const size_t pb = sizeof(double) * 2 * (size_t)Rmax * nparts * Tmax;
     if (pb > E->wpart_bytes) {
         CHK(dalloc(E, &E->wpart, pb));
         E->wpart_bytes = pb;
     }
+    CHK(ensure_series(E, Rmax * Tmax));
     hipStream_t s = E->stream();
     const bool sm = E->sm_cur >= 0;
+    const KArgs a = kargs(E);
+    char *L = (char *)E->wl_p + nst * 32, *w = L + nst * 3 * link_size(E->f32);
     Timed t(E, SU2_K_WILSON, s);
-    su2::launch_wlines(va, E->f32, sm ? E->sm[E->sm_cur] : E->links, sm ? 0 : 1, Rmax, E->wl_s, E->block, s);
-    su2::launch_wtrace(va, E->f32, Rmax, Tmax, V, d.n[3], E->wl_s, E->wpart, E->block, s);
-    double *dout = E->wpart + 2 * (size_t)Rmax * nparts * Tmax;
-    su2::launch_wfinal(E->ddesc, nparts, Rmax, Tmax, E->wpart, dout, s);
+    su2::launch_wgauge(a, E->f32, d.ns, next, E->wl_p, s);
+    su2::launch_wlinks(a, E->f32, d.n, sm ? E->sm[E->sm_cur] : E->links, sm ? 0 : 1, next, E->wl_p, L, w, s);
+    for (int k = 0; k < npass; ++k) su2::launch_wloops(a, E->f32, plan[k], Rmax, next, L, w, E->wpart, s);
+    su2::launch_wfinal(E->ddesc, nparts, Rmax, Tmax, E->wpart, E->dser, E->st, E->derr, s);
     t.done(s);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(out, dout, sizeof(double) * Rmax * Tmax, hipMemcpyDeviceToHost, s));
-    return finish(E);
+    const su2_status st = finish(E, true);
+    if (st != SU2_EDEVICE) std::memcpy(out, E->hser, sizeof(double) * Rmax * Tmax);
+    return st;
 }
 
 su2_status su2_release_buffers(su2_lattice E) {
     CHK(enter(E));
     HIPCHK(hipStreamSynchronize(E->stream()));
-    for (void **b : {&E->sm[0], &E->sm[1], &E->wl_s}) {
+    for (void **b : {&E->sm[0], &E->sm[1], &E->wl_p}) {
         if (*b) HIPCHK(hipFree(*b));
         *b = nullptr;
     }
     if (E->wpart) HIPCHK(hipFree(E->wpart));
     E->wpart = nullptr;
-    E->wl_s_bytes = E->wpart_bytes = 0;
+    E->wl_p_bytes = E->wpart_bytes = 0;
     E->sm_cur = -1;
     return SU2_OK;
 }

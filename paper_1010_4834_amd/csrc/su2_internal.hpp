@@ -75,13 +75,27 @@ void launch_clear_err(DevState *st, hipStream_t s);
 void launch_err_to_host(const DevState *st, unsigned *out, hipStream_t s);
 void launch_ape(const KArgs &a, bool f32, const void *src, int src_raw, void *dst, double alpha, int block,
                 int grid, hipStream_t s);
-void launch_wlines(const KArgs &a, bool f32, const void *sp, int sp_raw, int Rmax, void *sl, int block,
-                   hipStream_t s);
-void launch_wtrace(const KArgs &a, bool f32, int Rmax, int Tmax, long long V, int Nt, const void *sl, double *part,
-                   int block, hipStream_t s);
-// Workgroups per R of the Wilson-loop trace launch (its partials per R).
-int wtrace_groups(const KArgs &a);
+// Wilson loops: prefix products of the temporal links (times 0 .. next - 1),
+// the spatial links and weights in that gauge, line by line, the loop traces of one pass of times (several passes beyond T = 16) and
+// their final sums, written to mapped host memory with the error word.
+constexpr int wl_ke(bool f32) { return f32 ? 8 : 6; }  // line elements per lane at most
+struct WDir {             // split of one direction, see k_wloops
+    int N, lines, XC, XE, G, TC, NB, ngrp, nxc, ntc, unit0;
+};
+struct WPlan {
+    WDir d[3];
+    int nunits, nel;            // units; LDS elements of the largest unit
+    int block, grid, nc, lds;   // threads, workgroups, rows per lane, LDS bytes
+    int toff, Tp, Tall;         // times toff < T <= toff + Tp of Tall
+};
+// false if no split fits the LDS
+bool wloops_plan(bool f32, const int *n, int Rmax, int Tmax, int toff, WPlan &out);
+void launch_wgauge(const KArgs &a, bool f32, int ns, int next, void *P, hipStream_t s);
+void launch_wlinks(const KArgs &a, bool f32, const int *n, const void *sp, int sp_raw, int next, const void *P, void *L,
+                   void *w, hipStream_t s);
+void launch_wloops(const KArgs &a, bool f32, const WPlan &p, int Rmax, int next, const void *L, const void *w,
+                   double *part, hipStream_t s);
 void launch_wfinal(const LatDesc *desc, int nparts, int Rmax, int Tmax, const double *part, double *out,
-                   hipStream_t s);
+                   const DevState *st, unsigned *err, hipStream_t s);
 
 }  // namespace su2

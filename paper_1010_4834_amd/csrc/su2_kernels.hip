@@ -10,6 +10,8 @@
 // coalesced float4 / float64x2 loads of the parity-split layout.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+
 #include "su2_internal.hpp"
 
 namespace su2 {
@@ -878,165 +880,432 @@ __global__ __launch_bounds__(256) void k_ape(KArgs a, const void *src, int src_r
 }
 
 // ---------------------------------------------------------------------------
-// Wilson loops (paper Sec. 2, W(R,T)).  Spatial lines first: S_mu(x;R) =
-// U_mu(x) .. U_mu(x+(R-1)mu), stored per site as Q<T> arrays
-// sl[(mu*Rmax + R-1)*V + s].  `sp` / `sp_raw`: the spatial links (smeared
-// buffer or raw links).  Temporal lines are not stored: the trace kernel
-// builds them by transport from the raw temporal links.
-template <class T>
-__global__ __launch_bounds__(256) void k_wlines(KArgs a, const void *sp, int sp_raw, int Rmax, Q<T> *sl) {
-    for_each_tile(a.ntiles, a.xcd_remap, [&](int tile) {
-        const Tile tv = load_tile(a.tiles, tile);
-        const LatDesc d = load_desc(a.desc + tv.x);
-        const Blocks<T, 3> Bs = blocks<T, 3>(sp, sp_raw ? d.off : d.soff, d.vh);
-        const int s = tv.y + (int)threadIdx.x;
-        const long long V = 2LL * d.vh;
-        if (s >= V) return;
-        int c[4], r = s;
-        udiv(r, d.n[0], d.inv_nx, r, c[0]);
-        udiv(r, d.n[1], d.inv_ny, r, c[1]);
-        udiv(r, d.n[2], d.inv_nz, c[3], c[2]);
-#pragma unroll
-        for (int mu = 0; mu < 3; ++mu) {
-            const int st = mu == 0 ? 1 : mu == 1 ? d.n[0] : d.n[0] * d.n[1];
-            Q<T> P = qone<T>();
-            int cm = c[mu];
-            for (int R = 1; R <= Rmax; ++R) {
-                const int y = s + (cm - c[mu]) * st;
-                const int par = (c[0] + c[1] + c[2] + c[3] - c[mu] + cm) & 1;
-                P = qmul(P, lds_(Bs, mu, par, (uint32_t)y >> 1));
-                sl[((long long)mu * Rmax + R - 1) * V + s] = P;
-                cm = (cm + 1 == d.n[mu]) ? 0 : cm + 1;
-            }
-        }
-    });
+// Wilson loops (paper Sec. 2, W(R,T)) in the temporal gauge.  With the
+// prefix products P(x,t) = U_4(x,0) .. U_4(x,t-1) of a spatial site's temporal
+// links the loop is, for any links (unitary or not),
+//   1/2 Tr[S(x,t;R) T(x+R) S(x,t+T;R)^dag T(x)^dag]
+//     = w(x,t) w(x+R,t) Z(x,t;R) . Z(x,t+T;R),
+//   Z(x,t;R) = P(x,t) S(x,t;R) P(x+R,t)^dag,  w = 1/|P|^2,
+// the dot product running over the four quaternion components: a trace costs
+// four multiply-adds, where transporting the temporal sides around each loop
+// took two quaternion products more.  Times t >= Nt continue the prefix
+// products over the periodic links, so a loop that wraps needs nothing of its
+// own.  Products of P, the dot products and their sums are binary64; the
+// lines Z are held in link precision.
+//
+template <class T> __device__ __forceinline__ Q<double> qwide(const Q<T> &q) {
+    return Q<double>{(double)q.a, (double)q.b, (double)q.c, (double)q.d};
 }
 
-// W(R,T) partials: blockIdx.y = R-1; per site x and spatial mu the loop
-// 1/2 Tr[S(x;R) T(x+R mu;T) S(x+T t;R)^dag T(x;T)^dag] = 1/2 Tr[A_T S(x+T t;R)^dag]
-// with A_T = T(x;T)^dag S(x;R) T(x+R mu;T), built by transport up the two
-// temporal sides: A_0 = S(x;R), A_T = U_t(x+(T-1)t)^dag A_{T-1} U_t(x+R mu+(T-1)t).
-// Temporal links come from the raw link buffer, the spatial lines from sl.
-//
-// A lane owns a column of NC sites x_j = x_0 + j t (j < NC; NC divides Nt)
-// of lattice 0 and takes the three directions mu one after another: at
-// temporal offset m from x_0 every column site with step k = m - j < Tmax
-// applies the same two temporal links and meets the same spatial line at
-// x_0 + (m+1) t, so each is loaded once per column instead of once per site
-// (NC + Tmax - 1 offsets of three loads per mu).  Column q = (spatial site
-// q % Ns, t block q / Ns); column tile i is columns [i B, (i+1) B) for block
-// size B.  A workgroup walks its share of the column tiles (a fixed
-// assignment), each lane summing in binary64, then one compensated block sum
-// per (R, workgroup, T).
-template <class T, int TMAX, int NC>
-__device__ __forceinline__ void wtrace_body(const KArgs &a, int Rmax, int Tmax, int ncols, int nctiles,
-                                            const Q<T> *sl, double *part) {
-    __shared__ DD lds[TMAX * 4];
-    const int R = blockIdx.y + 1;
-    double sum[TMAX];
-#pragma unroll
-    for (int k = 0; k < TMAX; ++k) sum[k] = 0.0;
+// k_wgauge: P of 64 spatial sites (lanes), times 0 .. next - 1.  The
+// ordered product is bound by its own latency (one lane per site fills a
+// fifth of the chip's wavefront slots at 24^3 sites), so the eight wavefronts
+// of a workgroup take eight times each of 64: they multiply their links,
+// exchange the products through LDS and start from the product of the
+// wavefronts before them: 9.2 us at 24^3 x 48, T <= 16, 25 us as one ordered
+// product per lane.  P: planes (a0,a1) and (a2,a3) per time, [t][plane][spatial
+// site].
+template <class T>
+__global__ __launch_bounds__(512) void k_wgauge(KArgs a, int next, double2 *__restrict__ P) {
+    __shared__ double2 seg[8][2][64];
     const LatDesc d = load_desc(a.desc);
     const Blocks<T, 4> B = blocks<T, 4>(a.links, d.off, d.vh);
-    const long long V = 2LL * d.vh;
-    const Q<T> *slR = sl + (long long)(R - 1) * V;
-    const long long mstride = (long long)Rmax * V;
-    for (TileWalk w(nctiles, a.xcd_remap); w.ok(); w.next()) {
-        const int q = w.tile() * (int)blockDim.x + (int)threadIdx.x;
-        if (q >= ncols) continue;
-        // q = sp + Ns tb: spatial site sp = x + Nx (y + Ny z), t0 = NC tb
-        int c[3], r, tb, sp;
-        udiv(q, d.n[0], d.inv_nx, r, c[0]);
-        udiv(r, d.n[1], d.inv_ny, r, c[1]);
-        udiv(r, d.n[2], d.inv_nz, tb, c[2]);
-        sp = q - tb * d.ns;
-        const int t0 = NC * tb;
-        const int s0 = sp + t0 * d.ns;  // site of x_0
+    const int lane = (int)threadIdx.x & 63, wave = uni((int)threadIdx.x >> 6);
+    const int xs = min((int)blockIdx.x * 64 + lane, d.ns - 1);  // lanes beyond the lattice repeat its last site
+    int r, x, y, z;
+    udiv(xs, d.n[0], d.inv_nx, r, x);
+    udiv(r, d.n[1], d.inv_ny, z, y);
+    const int p0 = (x + y + z) & 1, Nt = d.n[3];
+    Q<double> carry = qone<double>();
+    for (int t0 = 0; t0 < next; t0 += 64) {
+        Q<T> U[8];
+        int tl = (t0 + 8 * wave) % Nt;
 #pragma unroll
-        for (int mu = 0; mu < 3; ++mu) {
-            const int st = mu == 0 ? 1 : mu == 1 ? d.n[0] : d.n[0] * d.n[1];
-            int cm = c[mu] + R;
-            if (cm >= d.n[mu]) cm -= d.n[mu];
-            const int sR = s0 + (cm - c[mu]) * st;  // x_0 + R mu
-            Q<T> A[NC];
+        for (int k = 0; k < 8; ++k) {
+            U[k] = lds_(B, 3, (p0 + tl) & 1, (uint32_t)(xs + d.ns * tl) >> 1);
+            tl = tl + 1 == Nt ? 0 : tl + 1;
+        }
+        Q<double> p{(double)U[0].a, (double)U[0].b, (double)U[0].c, (double)U[0].d};
 #pragma unroll
-            for (int j = 0; j < NC; ++j) A[j] = slR[mu * mstride + s0 + j * d.ns];
-            // parity of x_0 + m t and of x_0 + R mu + m t (R flips it when odd)
-            const int p0 = (c[0] + c[1] + c[2] + t0) & 1, pR = p0 ^ (R & 1);
-            int tm = t0;  // t of x_0 + m t
+        for (int k = 1; k < 8; ++k)
+            p = qmul(p, Q<double>{(double)U[k].a, (double)U[k].b, (double)U[k].c, (double)U[k].d});
+        seg[wave][0][lane] = make_double2(p.a, p.b);
+        seg[wave][1][lane] = make_double2(p.c, p.d);
+        __syncthreads();
+        p = carry;
 #pragma unroll
-            for (int m = 0; m < NC + TMAX - 1; ++m) {
-                if (m < NC + Tmax - 1) {
-                    const int dt = (tm - t0) * d.ns;  // x_0 + m t = s0 + dt
-                    const int pm = (p0 + m) & 1, pRm = (pR + m) & 1;
-                    const Q<T> ua = qdag(lds_(B, 3, pm, (uint32_t)(s0 + dt) >> 1));
-                    const Q<T> ub = lds_(B, 3, pRm, (uint32_t)(sR + dt) >> 1);
-                    tm = (tm + 1 == d.n[3]) ? 0 : tm + 1;
-                    const Q<T> top = slR[mu * mstride + s0 + (tm - t0) * d.ns];  // S(x_0 + (m+1) t; R)
+        for (int v = 0; v < 8; ++v) {
+            const double2 l = seg[v][0][lane], h = seg[v][1][lane];
+            carry = qmul(carry, Q<double>{l.x, l.y, h.x, h.y});
+            if (v + 1 == wave) p = carry;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int t = t0 + 8 * wave + k;
+            if (t < next) {
+                double2 *q = P + 2 * (long long)t * d.ns + xs;
+                q[0] = make_double2(p.a, p.b);
+                q[d.ns] = make_double2(p.c, p.d);
+                p = qmul(p, Q<double>{(double)U[k].a, (double)U[k].b, (double)U[k].c, (double)U[k].d});
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// s (1 + f), the small f given: weights within rounding of 1 are kept as their
+// distance from it (rounded to binary32 themselves they average 1.3e-8 too
+// small, 1e-7 in a loop of R = 8)
+template <class T> __device__ __forceinline__ Q<T> qscale1p(const Q<T> &q, T f) {
+    return Q<T>{fma(q.a, f, q.a), fma(q.b, f, q.b), fma(q.c, f, q.c), fma(q.d, f, q.d)};
+}
+
+// k_wlinks: the spatial links in that gauge, P(x,t) U_mu(x,t) P(x+mu,t)^dag =
+// Z(x,t;1), and the weights as w - 1, line by line along mu:
+// [mu][line][t][position along mu], so that k_wloops reads its lines as
+// contiguous blocks.  (Gathered by k_wloops itself from the parity-split links
+// and P, 16 bytes from each cache line where mu is not x, the same loads took
+// 75 of its 158 us at 24^3 x 48.)  A workgroup takes a 32 x 32 tile of one
+// time: x and, for mu = 2, z, else y; where mu is not x the tile is
+// transposed through LDS.
+__device__ __forceinline__ double rcp_newton(double x) {  // 1/x, relative error below 2^-52
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(y, fma(-x, y, 1.0), y);
+    return fma(y, fma(-x, y, 1.0), y);
+}
+
+template <class T>
+__global__ __launch_bounds__(512) void k_wlinks(KArgs a, const void *sp, int sp_raw, int next,
+                                                const double2 *__restrict__ P, Q<T> *__restrict__ L,
+                                                T *__restrict__ w) {
+    __shared__ Q<T> tq[32 * 33];
+    __shared__ T tw[32 * 33];
+    const LatDesc d = load_desc(a.desc);
+    const Blocks<T, 3> B = blocks<T, 3>(sp, sp_raw ? d.off : d.soff, d.vh);
+    // times round-robin over the XCDs (workgroup b runs on XCD b % 8), the
+    // three directions of a time one after another: its P and links are
+    // fetched into that XCD's L2 once (with the directions as separate passes
+    // over all times 28 us at 24^3 x 48)
+    const int per = gridDim.x >> 3, q8 = (int)blockIdx.x >> 3, t = ((int)blockIdx.x & 7) + 8 * (int)blockIdx.y;
+    if (t >= next) return;
+    const int mu = q8 / (per / 3);
+    const int ntx = (d.n[0] + 31) >> 5;
+    const int nj = mu == 2 ? d.n[2] : d.n[1], no = mu == 2 ? d.n[1] : d.n[2], ntj = (nj + 31) >> 5;
+    for (int tile = q8 - mu * (per / 3); tile < ntx * ntj * no; tile += per / 3) {
+        const int x0 = (tile % ntx) << 5, r = tile / ntx;
+        const int j0 = (r % ntj) << 5, o = r / ntj;
+        const int TX = min(32, d.n[0] - x0), TJ = min(32, nj - j0), nel = TX * TJ;
+        const int tm = t % d.n[3], st = mu == 0 ? 1 : mu == 1 ? d.n[0] : d.n[0] * d.n[1];
+        const long long first = (long long)mu * d.ns * next;
+        const double2 *Pt = P + 2 * (long long)t * d.ns;
+        const float iX = 1.0f / (float)TX, iJ = 1.0f / (float)TJ;
+        // two elements per thread, their loads together (at most 1024 elements,
+        // threads for at least half of them); threads beyond the tile repeat its
+        // last element
+        Q<T> U[2];
+        double2 al[2], ah[2], bl[2], bh[2];
+        int is[2], js[2];
+        long long ks[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int e = min((int)threadIdx.x + h * (int)blockDim.x, nel - 1);
+            const int j = (int)(((float)e + 0.5f) * iX), i = e - j * TX;
+            const int x = x0 + i, c = j0 + j, y = mu == 2 ? o : c, z = mu == 2 ? c : o;
+            const int sa = x + d.n[0] * (y + d.n[1] * z);
+            const int pos = mu == 0 ? x : c, N = mu == 0 ? d.n[0] : nj;
+            const int sb = sa + (pos + 1 == N ? -(N - 1) * st : st);
+            is[h] = i, js[h] = j;
+            ks[h] = first + ((long long)(y + d.n[1] * z) * next + t) * d.n[0] + x;
+            U[h] = lds_(B, mu, (x + y + z + tm) & 1, (uint32_t)(sa + tm * d.ns) >> 1);
+            al[h] = Pt[sa], ah[h] = Pt[sa + d.ns], bl[h] = Pt[sb], bh[h] = Pt[sb + d.ns];
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const Q<double> m = qmul(qmul(Q<double>{al[h].x, al[h].y, ah[h].x, ah[h].y}, qwide(U[h])),
+                                     Q<double>{bl[h].x, -bl[h].y, -bh[h].x, -bh[h].y});
+            const double n2 = al[h].x * al[h].x + al[h].y * al[h].y + ah[h].x * ah[h].x + ah[h].y * ah[h].y;
+            const T wv = (T)((1.0 - n2) * rcp_newton(n2));
+            const Q<T> q{(T)m.a, (T)m.b, (T)m.c, (T)m.d};
+            if (mu == 0) {
+                L[ks[h]] = q;
+                w[ks[h]] = wv;
+            } else {
+                tq[is[h] * 33 + js[h]] = q;
+                tw[is[h] * 33 + js[h]] = wv;
+            }
+        }
+        if (mu == 0) continue;
+        __syncthreads();
+        for (int e = (int)threadIdx.x; e < nel; e += (int)blockDim.x) {
+            const int i = (int)(((float)e + 0.5f) * iJ), j = e - i * TJ;
+            const long long k = first + ((long long)(x0 + i + d.n[0] * o) * next + t) * nj + j0 + j;
+            L[k] = tq[i * 33 + j];
+            w[k] = tw[i * 33 + j];
+        }
+        __syncthreads();
+    }
+}
+
+// Quaternions in LDS: float4, or two double2 planes n apart, so that
+// consecutive lanes read consecutive 16-byte words.
+template <class T> struct LdsQ;
+template <> struct LdsQ<float> {
+    float4 *z;
+    __device__ __forceinline__ LdsQ(void *p, int) : z((float4 *)p) {}
+    __device__ __forceinline__ Q<float> ld(int i) const {
+        const float4 v = z[i];
+        return Q<float>{v.x, v.y, v.z, v.w};
+    }
+    __device__ __forceinline__ void st(int i, const Q<float> &q) const { z[i] = make_float4(q.a, q.b, q.c, q.d); }
+};
+template <> struct LdsQ<double> {
+    double2 *z;
+    int n;
+    __device__ __forceinline__ LdsQ(void *p, int n_) : z((double2 *)p), n(n_) {}
+    __device__ __forceinline__ Q<double> ld(int i) const {
+        const double2 l = z[i], h = z[i + n];
+        return Q<double>{l.x, l.y, h.x, h.y};
+    }
+    __device__ __forceinline__ void st(int i, const Q<double> &q) const {
+        z[i] = make_double2(q.a, q.b);
+        z[i + n] = make_double2(q.c, q.d);
+    }
+};
+
+// s + 1/2 Tr(x y^dag), the trace in the precision of its operands, the sum in
+// binary64
+__device__ __forceinline__ double add_dot(double s, const Q<float> &x, const Q<float> &y) {
+    return s + (double)half_tr_xyd(x, y);
+}
+__device__ __forceinline__ double add_dot(double s, const Q<double> &x, const Q<double> &y) {
+    return fma(x.d, y.d, fma(x.c, y.c, fma(x.b, y.b, fma(x.a, y.a, s))));
+}
+
+// Wavefront sums of N values (a power of two) at once.  Each step adds the
+// two halves of the wavefront that differ in one lane bit and, while more
+// than one value is left, keeps half of the values in either half, so N = 16
+// takes 17 exchanges where separate butterflies take 96.  Lane bits 5 and 4
+// are exchanged by the lane-swap instructions, bits 0, 1, 3 and 2 by DPP.
+// Every lane ends with the total of value `which`.
+__device__ __forceinline__ void swap_halves32(double &a, double &b) {
+    const unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    a = __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0]));
+    b = __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+__device__ __forceinline__ void swap_halves16(double &a, double &b) {
+    const unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    a = __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0]));
+    b = __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+template <int CTRL> __device__ __forceinline__ double dpp_f64(double v) {
+    const unsigned long long b = __double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128;  // quad_perm, row_ror
+template <int CTRL, int N, int H>
+__device__ __forceinline__ void dpp_step(double (&v)[N], bool up) {
+    if constexpr (H >= 1) {  // 2 H values left: keep H of them
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const double keep = up ? v[i + H] : v[i], send = up ? v[i] : v[i + H];
+            v[i] = keep + dpp_f64<CTRL>(send);
+        }
+    } else {
+        v[0] += dpp_f64<CTRL>(v[0]);
+    }
+}
+template <int N> __device__ __forceinline__ double wave_sum_many(double (&v)[N], int lane, int &which) {
+    static_assert(N == 4 || N == 8 || N == 16, "number of values");
+    constexpr int H5 = N / 2, H4 = N / 4, H0 = N / 8, H1 = N / 16;
+#pragma unroll
+    for (int i = 0; i < H5; ++i) {
+        swap_halves32(v[i], v[i + H5]);
+        v[i] += v[i + H5];
+    }
+#pragma unroll
+    for (int i = 0; i < H4; ++i) {
+        swap_halves16(v[i], v[i + H4]);
+        v[i] += v[i + H4];
+    }
+    dpp_step<DPP_XOR1, N, H0>(v, lane & 1);
+    dpp_step<DPP_XOR2, N, H1>(v, lane & 2);
+    v[0] += dpp_f64<DPP_ROR8>(v[0]);
+    v[0] += dpp_f64<DPP_ROR4>(v[0]);
+    which = (lane & 32 ? H5 : 0) + (lane & 16 ? H4 : 0) + (lane & 1 ? H0 : 0) + (lane & 2 ? H1 : 0);
+    return v[0];
+}
+
+// Loop traces of the times toff < T <= toff + Tp (Tp <= TMAX) and every
+// R <= Rmax.  A work unit is a group of G lattice lines along direction mu (or
+// a piece of XC sites of one line), times t0 .. t0 + TC - 1: the workgroup
+// holds Z of its elements (line, x, t) for the current R in LDS, times up to
+// t0 + TC - 1 + toff + Tp, and the single transformed link P(x,t) U(x,t)
+// P(x+mu,t)^-1 of an element in the registers of the lane that owns it, so
+// that Z(x,t;R+1) = link(x,t) Z(x+mu,t;R) reads only its LDS neighbour.  A
+// line that is held whole wraps around (XE = XC = N); a piece carries
+// XE - XC = Rmax elements beyond it, whose last values are not used.
+// For the traces a lane owns NC successive times of one x and meets each
+// later Z once for all of them: NC + Tp LDS reads, as many conversions and
+// 4 NC Tp binary64 multiply-adds per R.  The lane sums of one R are added over
+// the wavefront and kept per (wavefront, R, T) in LDS until the last unit.
+// Rows beyond the lattice or the unit enter as zero times a valid Z.
+// At 24^3 x 48, R <= 12, T <= 16 in binary32: 127 us, with k_wgauge, k_wlinks
+// and k_wfinal 164 us, where storing the lines of every R (84 us) and
+// transporting the temporal sides around each loop (488 us, 37.5 vector
+// instructions per (site, mu, R, T)) took 580.  About 9.6 us per R: 6 vector
+// instructions per (site, mu, R, T) in binary32 and 4 in binary64, where a
+// binary64 instruction issues every 5.6 cycles against 3.1 in binary32
+// (measured), and 3.7 us per R for the next line, the sums and two barriers.
+// 24^3 x 32, R <= 10, T <= 12 in binary64: 190 us, was 865.
+template <class T, int TMAX, int NC, int KE>
+__global__ __attribute__((amdgpu_flat_work_group_size(64, 512), amdgpu_waves_per_eu(3))) void k_wloops(
+    KArgs a, WPlan pl, int Rmax, int next, const Q<T> *__restrict__ L, const T *__restrict__ w,
+    double *__restrict__ part) {
+    extern __shared__ double4 wl_lds[];
+    const int tid = (int)threadIdx.x, nb = (int)blockDim.x, lane = tid & 63, wave = tid >> 6;
+    const LatDesc d = load_desc(a.desc);
+    const LdsQ<T> Z(wl_lds, pl.nel);
+    T *wt = (T *)((char *)wl_lds + (size_t)pl.nel * Links<T>::BYTES);
+    double *acc = (double *)(wt + pl.nel);
+    for (int i = tid; i < (nb >> 6) * Rmax * TMAX; i += nb) acc[i] = 0.0;
+    acc += wave * Rmax * TMAX;
+    for (TileWalk u(pl.nunits, 1); u.ok(); u.next()) {
+        const int unit = u.tile();
+        const int mu = unit >= pl.d[2].unit0 ? 2 : unit >= pl.d[1].unit0 ? 1 : 0;
+        const WDir D = mu == 2 ? pl.d[2] : mu == 1 ? pl.d[1] : pl.d[0];
+        int v = unit - D.unit0;
+        const int tc = v % D.ntc;
+        v /= D.ntc;
+        const int xc = v % D.nxc, grp = v / D.nxc;
+        const int t0 = tc * D.TC, x0 = xc * D.XC, rows = min(D.TC, d.n[3] - t0), W = D.G * D.XE;
+        const int nrow = D.NB * NC, nel = W * (nrow + pl.toff + TMAX), ke = (nel + nb - 1) / nb;
+        const float iW = 1.0f / (float)W, iX = 1.0f / (float)D.XE;
+        const long long first = (long long)mu * d.ns * next;
+        const Q<T> *Lm = L + first;
+        const T *wm = w + first;
+
+        // elements tid + k nb of this lane: Z and the LDS neighbour along mu.
+        // Lanes beyond the last element repeat it into the padding.
+        Q<T> Ue[KE];
+        uint32_t nbr[KE / 2];  // two 16-bit indices each
+#pragma unroll
+        for (int k = 0; k < KE; ++k) Ue[k] = Q<T>{T(0), T(0), T(0), T(0)}, nbr[k >> 1] = 0;
+#pragma unroll
+        for (int k = 0; k < KE; ++k) {
+            if (k < ke) {
+                const int e = min(tid + k * nb, nel - 1);
+                const int te = (int)(((float)e + 0.5f) * iW), gx = e - te * W;
+                const int g = (int)(((float)gx + 0.5f) * iX), xi = gx - g * D.XE;
+                const uint32_t up = (uint32_t)(xi + 1 < D.XE ? e + 1 : D.XE == D.XC ? e - (D.XE - 1) : e);
+                nbr[k >> 1] = k & 1 ? nbr[k >> 1] | up << 16 : up;
+                const int line = min(grp * D.G + g, D.lines - 1), t = min(t0 + te, next - 1);
+                int xa = x0 + xi;
+                while (xa >= D.N) xa -= D.N;
+                const long long o = ((long long)line * next + t) * D.N + xa;
+                Ue[k] = Lm[o];
+                wt[tid + k * nb] = wm[o];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < KE; ++k)
+            if (k < ke) Z.st(tid + k * nb, Ue[k]);
+        __syncthreads();
+        // P(x) U P(x+mu)^-1
+#pragma unroll
+        for (int k = 0; k < KE; ++k) {
+            const T f = wt[k & 1 ? nbr[k >> 1] >> 16 : nbr[k >> 1] & 0xFFFFu];
+            Ue[k] = qscale1p(Ue[k], f);
+        }
+        // rows of this lane
+        const int per = D.G * D.XC, tb = (int)(((float)tid + 0.5f) * (1.0f / (float)per));
+        const int gi = tid - tb * per, g = (int)(((float)gi + 0.5f) * (1.0f / (float)D.XC)), xi = gi - g * D.XC;
+        const bool on = tb < D.NB && grp * D.G + g < D.lines && x0 + xi < D.N;
+        const int gx = g * D.XE + xi, r0 = tb * NC;
+        int gR = gx, xR = xi;  // x + R
+        for (int R = 1; R <= Rmax; ++R) {
+            double sum[TMAX];
+#pragma unroll
+            for (int k = 0; k < TMAX; ++k) sum[k] = 0.0;
+            ++gR, ++xR;
+            if (xR == D.XE) xR = 0, gR -= D.XE;
+            if (on) {
+                // opaque per R: addresses formed as they are used, not kept
+                // in registers across the loop
+                int o = r0 * W;
+                __asm__ volatile("" : "+v"(o));
+                Q<T> A[NC];
+#pragma unroll
+                for (int j = 0; j < NC; ++j) {
+                    const Q<T> q = Z.ld(o + gx);
+                    const T f = wt[o + gx], h = wt[o + gR];
+                    A[j] = r0 + j < rows ? qscale1p(q, fma(f, h, f + h)) : Q<T>{T(0), T(0), T(0), T(0)};
+                    o += W;
+                }
+                o = (r0 + pl.toff) * W + gx;
+                __asm__ volatile("" : "+v"(o));
+#pragma unroll
+                for (int m = 1; m < NC + TMAX; ++m) {
+                    o += W;
+                    const Q<T> q = Z.ld(o);
 #pragma unroll
                     for (int j = 0; j < NC; ++j) {
-                        const int k = m - j;
-                        if (k >= 0 && k < TMAX && k < Tmax) {
-                            A[j] = qmul(qmul(ua, A[j]), ub);
-                            sum[k] += (double)half_tr_xyd(A[j], top);
-                        }
+                        const int k = m - j - 1;
+                        if (k >= 0 && k < TMAX) sum[k] = add_dot(sum[k], A[j], q);
                     }
                 }
             }
+            int which;
+            const double tot = wave_sum_many<TMAX>(sum, lane, which);
+            if ((lane & 12) == 0 && (TMAX > 4 || (lane & 1) == 0) && (TMAX > 8 || (lane & 2) == 0))
+                acc[(R - 1) * TMAX + which] += tot;
+            if (R < Rmax) {
+                Q<T> n[KE];
+#pragma unroll
+                for (int k = 0; k < KE; ++k)
+                    n[k] = Z.ld((int)(k & 1 ? nbr[k >> 1] >> 16 : nbr[k >> 1] & 0xFFFFu));
+                __syncthreads();
+                int e = tid;
+                __asm__ volatile("" : "+v"(e));
+#pragma unroll
+                for (int k = 0; k < KE; ++k)
+                    if (k < ke) Z.st(e + k * nb, qmul(Ue[k], n[k]));
+            }
+            __syncthreads();
         }
     }
-    // Wavefront sums by binary64 butterflies in a fixed order (each lane holds
-    // a plain binary64 sum; a compensated butterfly cost as much as a tenth of
-    // the kernel's instructions), then the workgroup's wavefronts combined by
-    // compensated sums in thread 0.
-    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
-#pragma unroll
-    for (int k = 0; k < TMAX; ++k) {
-        const double ws = wave_sum_f64(sum[k]);
-        if (lane == 0) lds[wave * TMAX + k] = DD{ws, 0.0};
-    }
     __syncthreads();
-    if (threadIdx.x == 0)
-#pragma unroll
-        for (int k = 0; k < TMAX; ++k)
-            if (k < Tmax) {
-                DD acc = lds[k];
-                for (int w = 1; w < nw; ++w) acc = dd_add(acc, lds[w * TMAX + k]);
-                double *p = part + 2 * (((long long)(R - 1) * gridDim.x + blockIdx.x) * Tmax + k);
-                p[0] = acc.hi;
-                p[1] = acc.lo;
-            }
-}
-
-// Binary32 traces are held to 128 registers (4 waves per SIMD): under that
-// bound the compiler also schedules the unrolled offsets without copying the
-// binary64 sums around their run-time bounds, 10% faster at 24^3 x 48 than
-// the same code unbounded (122 registers, also 4 waves).  Binary64 traces
-// need more registers and run unbounded (the bound would spill).
-template <int TMAX, int NC>
-__global__ __launch_bounds__(256, 4) void k_wtrace(KArgs a, int Rmax, int Tmax, int ncols, int nctiles,
-                                                   const Q<float> *sl, double *part) {
-    wtrace_body<float, TMAX, NC>(a, Rmax, Tmax, ncols, nctiles, sl, part);
-}
-template <int TMAX, int NC>
-__global__ __launch_bounds__(256) void k_wtrace64(KArgs a, int Rmax, int Tmax, int ncols, int nctiles,
-                                                  const Q<double> *sl, double *part) {
-    wtrace_body<double, TMAX, NC>(a, Rmax, Tmax, ncols, nctiles, sl, part);
-}
-
-// One block per (R, T): fixed-order sum over the k_wtrace workgroups'
-// partials (nparts per R) of lattice 0.
-__global__ __launch_bounds__(256) void k_wfinal(const LatDesc *desc, int ntiles, int Tmax, const double *part,
-                                                double *out) {
-    __shared__ DD lds[4];
-    const int R = blockIdx.x / Tmax + 1, k = blockIdx.x % Tmax;
-    DD acc[1] = {{0.0, 0.0}};
-    for (int t = threadIdx.x; t < ntiles; t += blockDim.x) {
-        const double *p = part + 2 * (((long long)(R - 1) * ntiles + t) * Tmax + k);
-        acc[0] = dd_add(acc[0], DD{p[0], p[1]});
+    acc -= wave * Rmax * TMAX;
+    for (int i = tid; i < Rmax * pl.Tp; i += nb) {
+        const int r = i / pl.Tp, k = i - r * pl.Tp;
+        DD s{0.0, 0.0};
+        for (int wv = 0; wv < (nb >> 6); ++wv) s = dd_add(s, DD{acc[(wv * Rmax + r) * TMAX + k], 0.0});
+        double *o = part + 2 * (((long long)r * pl.Tall + pl.toff + k) * gridDim.x + blockIdx.x);
+        o[0] = s.hi;
+        o[1] = s.lo;
     }
+}
+
+// One block per (R, T): fixed-order sum over the k_wloops workgroups'
+// partials (nparts per (R, T)), written straight into mapped host memory, the
+// error word with them.
+__global__ __launch_bounds__(256) void k_wfinal(const LatDesc *desc, int nparts, const double *part, double *out,
+                                                const DevState *st, unsigned *err) {
+    __shared__ DD lds[4];
+    const double2 *p = reinterpret_cast<const double2 *>(part) + (long long)blockIdx.x * nparts;
+    const double vh = (double)uni(desc->vh);
+    DD acc[1] = {{0.0, 0.0}};
+    for (int t = threadIdx.x; t < nparts; t += blockDim.x) acc[0] = dd_add(acc[0], DD{p[t].x, p[t].y});
     dd_block_sum<1>(acc, lds);
-    if (threadIdx.x == 0) out[blockIdx.x] = (acc[0].hi + acc[0].lo) / (6.0 * (double)desc[0].vh);
+    if (threadIdx.x == 0) {
+        out[blockIdx.x] = (acc[0].hi + acc[0].lo) / (6.0 * vh);
+        if (blockIdx.x == 0) *err = st->err;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1204,70 +1473,155 @@ void launch_ape(const KArgs &a, bool f32, const void *src, int src_raw, void *ds
     else hipLaunchKernelGGL((k_ape<double>), g, dim3(block), 0, s, a, src, src_raw, dst, alpha);
 }
 
-void launch_wlines(const KArgs &a, bool f32, const void *sp, int sp_raw, int Rmax, void *sl, int block,
-                   hipStream_t s) {
-    if (f32)
-        hipLaunchKernelGGL((k_wlines<float>), grid_of(a, 0), dim3(block), 0, s, a, sp, sp_raw, Rmax,
-                           (Q<float> *)sl);
-    else
-        hipLaunchKernelGGL((k_wlines<double>), grid_of(a, 0), dim3(block), 0, s, a, sp, sp_raw, Rmax,
-                           (Q<double> *)sl);
+void launch_wgauge(const KArgs &a, bool f32, int ns, int next, void *P, hipStream_t s) {
+    const dim3 g((unsigned)((ns + 63) / 64)), b(512);
+    if (f32) hipLaunchKernelGGL((k_wgauge<float>), g, b, 0, s, a, next, (double2 *)P);
+    else hipLaunchKernelGGL((k_wgauge<double>), g, b, 0, s, a, next, (double2 *)P);
 }
 
-// Workgroups per R of the Wilson trace: enough to fill the chip a few times
-// over, each taking several column tiles (a multiple of 8, one share per XCD).
-int wtrace_groups(const KArgs &a) {
-    const int g = ((a.ntiles + 7) / 8) * 8;
-    return g < 1024 ? (g < 8 ? 8 : g) : 1024;
+void launch_wlinks(const KArgs &a, bool f32, const int *n, const void *sp, int sp_raw, int next, const void *P, void *L,
+                   void *w, hipStream_t s) {
+    const auto tiles = [](int k) { return (k + 31) / 32; };
+    const int gx = std::min(1 << 16, tiles(n[0]) * std::max(tiles(n[1]) * n[2], tiles(n[2]) * n[1]));
+    const int most = std::min(32, n[0]) * std::min(32, std::max(n[1], n[2]));
+    const dim3 g((unsigned)(8 * 3 * gx), (unsigned)((next + 7) / 8)), b((unsigned)((most + 127) / 128 * 64));  // two elements per thread
+    const double2 *p = (const double2 *)P;
+    if (f32) hipLaunchKernelGGL((k_wlinks<float>), g, b, 0, s, a, sp, sp_raw, next, p, (Q<float> *)L, (float *)w);
+    else hipLaunchKernelGGL((k_wlinks<double>), g, b, 0, s, a, sp, sp_raw, next, p, (Q<double> *)L, (double *)w);
 }
 
-// Column height of the Wilson trace: in binary32 with up to 16 time steps,
-// 6 or else 4 when it divides Nt (the same four waves per SIMD; 8 would
-// spill registers); otherwise 2 (extents are even).
-template <class T> static int wtrace_nc(int Nt, int Tmax) {
-    if (sizeof(T) == 4 && Tmax <= 16) return Nt % 6 == 0 ? 6 : Nt % 4 == 0 ? 4 : 2;
-    return 2;
+// Work split of the Wilson loops of times toff < T <= toff + Tp.  Among the
+// splits that fit (elements in WL_KE per lane, rows in one per lane, LDS) it
+// takes the least modelled time: wavefront instructions per R of a unit times
+// its wavefronts, over the whole chip, but at least one unit's own length.
+// The weights are the instruction counts of k_wloops.  A line is held whole
+// unless the smallest unit of it does not fit, which takes lines of several
+// hundred sites.
+namespace {
+struct WChoice {
+    WPlan p;
+    double cost;
+    size_t lds;
+};
+size_t wl_bytes(bool f32, int nel, int block, int Rmax, int TM) {
+    return (size_t)(nel + block - 1) / block * block * (f32 ? 20 : 40) + 8 * (size_t)(block / 64) * Rmax * TM;
+}
+bool wl_plan_at(bool f32, const int *n, int Rmax, int toff, int Tp, int TM, int nc, int block, size_t lds_max,
+                WChoice &best) {
+    WPlan p{};
+    p.block = block, p.nc = nc, p.toff = toff, p.Tp = Tp;
+    const int ns = n[0] * n[1] * n[2], Nt = n[3];
+    double total = 0;
+    for (int mu = 0; mu < 3; ++mu) {
+        WDir &D = p.d[mu];
+        D.N = n[mu];
+        D.lines = ns / D.N;
+        double dbest = 1e300;
+        WDir pick{};
+        int punits = 0;
+        for (int nbl = std::min(block, (Nt + nc - 1) / nc); nbl >= 1; --nbl) {
+            const int ntc = (Nt + nbl * nc - 1) / (nbl * nc), TC = (Nt + ntc - 1) / ntc;
+            const int NB = (TC + nc - 1) / nc, TE = NB * nc + toff + TM;
+            const int emax = wl_ke(f32) * block;
+            int XC = D.N, XE = D.N;
+            if ((long long)XE * TE > emax || D.N * NB > block ||
+                wl_bytes(f32, XE * TE, block, Rmax, TM) > lds_max) {
+                // a piece of a line with Rmax sites beyond it, only for lines too long for any unit
+                if ((long long)D.N * (nc + toff + TM) <= emax && D.N <= block &&
+                    wl_bytes(f32, D.N * (nc + toff + TM), block, Rmax, TM) <= lds_max)
+                    continue;
+                XC = std::min(block / NB, emax / TE - Rmax);
+                while (XC > 0 && wl_bytes(f32, (XC + Rmax) * TE, block, Rmax, TM) > lds_max) --XC;
+                XC = std::min(XC, D.N);
+                if (XC < 1) continue;
+                XE = XC + Rmax;
+            }
+            for (int G = 1; G <= D.lines && G <= 64; ++G) {
+                if (G > 1 && XE != XC) break;
+                if (G * XC * NB > block || (long long)G * XE * TE > emax ||
+                    wl_bytes(f32, G * XE * TE, block, Rmax, TM) > lds_max)
+                    break;
+                const int ngrp = (D.lines + G - 1) / G, nxc = (D.N + XC - 1) / XC, ntcs = (Nt + TC - 1) / TC;
+                const double ke = (G * XE * TE + block - 1) / block;
+                const double len = 30.0 * ke + (f32 ? 6.0 : 3.0) * (nc + TM) + 4.0 * nc * TM + 8.0 * nc + 120.0;
+                const double units = (double)ngrp * nxc * ntcs, wv = block / 64;
+                const double c = std::max(units * wv * len / 1024.0, 1.5 * len);
+                if (c < dbest) {
+                    dbest = c;
+                    pick = D;
+                    pick.XC = XC, pick.XE = XE, pick.G = G, pick.TC = TC, pick.NB = NB;
+                    pick.ngrp = ngrp, pick.nxc = nxc, pick.ntc = ntcs;
+                    punits = ngrp * nxc * ntcs;
+                    pick.unit0 = p.nunits;
+                }
+            }
+        }
+        if (dbest >= 1e300) return false;
+        D = pick;
+        p.nunits += punits;
+        const int e = D.G * D.XE * (D.NB * nc + toff + TM);
+        p.nel = std::max(p.nel, (e + block - 1) / block * block);
+        total += dbest;
+    }
+    const size_t lds = wl_bytes(f32, p.nel, block, Rmax, TM);
+    if (total < best.cost) best = WChoice{p, total, lds};
+    return true;
+}
+}  // namespace
+
+bool wloops_plan(bool f32, const int *n, int Rmax, int Tmax, int toff, WPlan &out) {
+    const int Tp = std::min(16, Tmax - toff), TM = Tp <= 4 ? 4 : Tp <= 8 ? 8 : 16;
+    WChoice best{};
+    best.cost = 1e300;
+    for (int block : {64, 128, 192, 256})
+        for (int nc : {4, 5, 6}) wl_plan_at(f32, n, Rmax, toff, Tp, TM, nc, block, 48 << 10, best);
+    if (best.cost >= 1e300) wl_plan_at(f32, n, Rmax, toff, Tp, TM, 4, 512, 160 << 10, best);
+    if (best.cost >= 1e300) return false;
+    out = best.p;
+    out.lds = (int)best.lds;
+    out.Tall = Tmax;
+    // one unit per workgroup, so that the hardware evens out the last round
+    // (24^3 x 48: 1728 units on 1024 resident workgroups), unless the partial
+    // sums would be many
+    out.grid = std::min(4096, (out.nunits + 7) / 8 * 8);
+    return true;
+}
+
+template <class T, int TM, int NC>
+static void launch_wloops_k(const KArgs &a, const WPlan &p, int Rmax, int next, const void *L, const void *w, double *part,
+                            hipStream_t s) {
+    const auto kern = k_wloops<T, TM, NC, wl_ke(sizeof(T) == 4)>;
+    if (p.lds > (64 << 10))
+        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, p.lds);
+    hipLaunchKernelGGL(kern, dim3((unsigned)p.grid), dim3((unsigned)p.block), (size_t)p.lds, s, a, p, Rmax, next,
+                       (const Q<T> *)L, (const T *)w, part);
 }
 
 template <class T, int NC>
-static void launch_wtrace_nc(const KArgs &a, int Rmax, int Tmax, long long V, const void *sl, double *part,
-                             int block, hipStream_t s) {
-    const dim3 g(wtrace_groups(a), (unsigned)Rmax), b((unsigned)block);
-    const int ncols = (int)(V / NC), nct = (ncols + block - 1) / block;
-    const Q<T> *l = (const Q<T> *)sl;
-    if constexpr (sizeof(T) == 4) {
-        if (Tmax <= 4) hipLaunchKernelGGL((k_wtrace<4, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
-        else if (Tmax <= 8) hipLaunchKernelGGL((k_wtrace<8, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
-        else if (Tmax <= 16) hipLaunchKernelGGL((k_wtrace<16, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
-        else if constexpr (NC == 2) hipLaunchKernelGGL((k_wtrace<32, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
-    } else {
-        if (Tmax <= 4) hipLaunchKernelGGL((k_wtrace64<4, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
-        else if (Tmax <= 8) hipLaunchKernelGGL((k_wtrace64<8, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
-        else if (Tmax <= 16) hipLaunchKernelGGL((k_wtrace64<16, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
-        else if constexpr (NC == 2) hipLaunchKernelGGL((k_wtrace64<32, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
-    }
+static void launch_wloops_nc(const KArgs &a, const WPlan &p, int Rmax, int next, const void *L, const void *w,
+                             double *part, hipStream_t s) {
+    if (p.Tp <= 4) launch_wloops_k<T, 4, NC>(a, p, Rmax, next, L, w, part, s);
+    else if (p.Tp <= 8) launch_wloops_k<T, 8, NC>(a, p, Rmax, next, L, w, part, s);
+    else launch_wloops_k<T, 16, NC>(a, p, Rmax, next, L, w, part, s);
 }
 
 template <class T>
-static void launch_wtrace_t(const KArgs &a, int Rmax, int Tmax, long long V, int Nt, const void *sl, double *part,
-                            int block, hipStream_t s) {
-    const int nc = wtrace_nc<T>(Nt, Tmax);
-    if constexpr (sizeof(T) == 4) {
-        if (nc == 6) return launch_wtrace_nc<T, 6>(a, Rmax, Tmax, V, sl, part, block, s);
-        if (nc == 4) return launch_wtrace_nc<T, 4>(a, Rmax, Tmax, V, sl, part, block, s);
-    }
-    launch_wtrace_nc<T, 2>(a, Rmax, Tmax, V, sl, part, block, s);
+static void launch_wloops_t(const KArgs &a, const WPlan &p, int Rmax, int next, const void *L, const void *w,
+                            double *part, hipStream_t s) {
+    if (p.nc == 6) launch_wloops_nc<T, 6>(a, p, Rmax, next, L, w, part, s);
+    else if (p.nc == 5) launch_wloops_nc<T, 5>(a, p, Rmax, next, L, w, part, s);
+    else launch_wloops_nc<T, 4>(a, p, Rmax, next, L, w, part, s);
 }
 
-void launch_wtrace(const KArgs &a, bool f32, int Rmax, int Tmax, long long V, int Nt, const void *sl, double *part,
-                   int block, hipStream_t s) {
-    if (f32) launch_wtrace_t<float>(a, Rmax, Tmax, V, Nt, sl, part, block, s);
-    else launch_wtrace_t<double>(a, Rmax, Tmax, V, Nt, sl, part, block, s);
+void launch_wloops(const KArgs &a, bool f32, const WPlan &p, int Rmax, int next, const void *L, const void *w,
+                   double *part, hipStream_t s) {
+    if (f32) launch_wloops_t<float>(a, p, Rmax, next, L, w, part, s);
+    else launch_wloops_t<double>(a, p, Rmax, next, L, w, part, s);
 }
 
 void launch_wfinal(const LatDesc *desc, int nparts, int Rmax, int Tmax, const double *part, double *out,
-                   hipStream_t s) {
-    hipLaunchKernelGGL(k_wfinal, dim3((unsigned)(Rmax * Tmax)), dim3(256), 0, s, desc, nparts, Tmax, part, out);
+                   const DevState *st, unsigned *err, hipStream_t s) {
+    hipLaunchKernelGGL(k_wfinal, dim3((unsigned)(Rmax * Tmax)), dim3(256), 0, s, desc, nparts, part, out, st, err);
 }
 
 }  // namespace su2
