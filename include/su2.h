@@ -312,7 +312,9 @@ su2_status su2_ensemble_set_sampler(su2_ensemble ens, su2_sampler sampler);
  * poly[i*M + k]; the last nsweeps % measure_every sweeps measure nothing.
  * Either pointer may be NULL to skip that measurement.  The sweeps (eight
  * substep launches each; the plaquette is summed inside the odd substeps of
- * measured sweeps) are replayed from captured HIP graphs: a run of 2 to 256
+ * measured sweeps) are replayed from captured HIP graphs -- or, where no
+ * lattice has more than 1024 sites and every lattice finds room on a compute
+ * unit, run as one launch with one workgroup per lattice: a run of 2 to 256
  * sweeps is one graph (run state, sweeps, series reduction and error word),
  * captured on the first run of that length, measure_every and measurement
  * choice; longer runs replay graphs of up to 16 sweeps (environment

@@ -72,6 +72,7 @@ struct su2_ensemble_s {
     LatDesc *ddesc = nullptr;
     long long total_links = 0;  // 4 * sum V
     long long total_sites = 0;
+    long long max_sites = 0;    // of the largest lattice
 
     int block = 256, grid = 0, remap = 1, nl = 1;
     std::vector<Tile> htiles, hstiles, hvtiles, hmtiles, hmtiles_z, hmtiles_b, hmtiles_b3;
@@ -97,8 +98,9 @@ struct su2_ensemble_s {
     unsigned *fin_cnt = nullptr;    // per-lattice arrival tickets of the final reduction
     double *fin_chunk = nullptr;    // per-workgroup chunk sums of the final reduction
     int fin_chunks = 1;             // workgroups per lattice in the final reduction
-    double *res = nullptr;   // device scratch for single results
-    double *hres = nullptr;  // pinned host mirror of res
+    // single results, written by kernels into mapped host memory (device
+    // address dres)
+    double *hres = nullptr, *dres = nullptr;
 
     int ser_C = 1;                  // chunks per (lattice, sweep) of the series reduction
     double *ser_chunk = nullptr;    // their (hi, lo) pairs
@@ -551,6 +553,7 @@ su2_status create_common(int n, const int *dims, const double *betas, su2_start 
         const long long V = (long long)d[0] * d[1] * d[2] * d[3];
         off += 4 * V;
         sites += V;
+        E->max_sites = std::max(E->max_sites, V);
     }
     E->total_links = off;
     E->total_sites = sites;
@@ -565,11 +568,7 @@ su2_status create_common(int n, const int *dims, const double *betas, su2_start 
     }
     CHK(dalloc(E, &E->ddesc, sizeof(LatDesc) * n));
     CHK(dalloc(E, &E->st, sizeof(DevState)));
-    CHK(dalloc(E, &E->res, sizeof(double) * 4 * n));
-    if (hipHostMalloc((void **)&E->hres, sizeof(double) * 4 * n, hipHostMallocDefault) != hipSuccess) {
-        E->hres = nullptr;
-        return SU2_ENOMEM;
-    }
+    if (host_mapped(E, (void **)&E->hres, (void **)&E->dres, sizeof(double) * 4 * n) != SU2_OK) return SU2_ENOMEM;
     if (host_mapped(E, (void **)&E->herr, (void **)&E->derr, sizeof(unsigned) * 16) != SU2_OK) return SU2_ENOMEM;
     E->hst.seed = seed;
     E->hst.sweep = 0;
@@ -596,7 +595,7 @@ void destroy_common(su2_ensemble_s *E) {
     }
     for (auto e : E->evpool) (void)hipEventDestroy(e);
     void *bufs[] = {E->ddesc, E->tiles, E->stiles, E->vtiles, E->mtiles, E->mtiles_z, E->mtiles_b, E->mtiles_b3, E->st, E->tries_part, E->part_plaq,
-                    E->part_poly, E->part_hb, E->fin_cnt, E->fin_chunk, E->res, E->ser_chunk,
+                    E->part_poly, E->part_hb, E->fin_cnt, E->fin_chunk, E->ser_chunk,
                     E->sm[0], E->sm[1], E->wl_p, E->wpart, E->trace};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
@@ -755,6 +754,42 @@ su2_status capture_run(su2_ensemble_s *E, int meas, int every, int nsweeps, hipG
     return SU2_OK;
 }
 
+// Whether a call's sweeps run as one workgroup per lattice (k_small_run): no
+// lattice above SMALL_SITES and every workgroup resident at once -- at most
+// eight wavefronts per CU (what two per SIMD overlap) and the lattices of a CU
+// within its LDS.  Where lattices would queue for CUs the batched substeps
+// keep the whole chip busy instead.  Not while tries are recorded per link or
+// kernels timed one by one, nor under SU2_NO_GRAPH.
+bool small_run_ok(const su2_ensemble_s *E) {
+    if (E->trace || E->timing || E->n > 8 * 256 || std::getenv("SU2_NO_GRAPH")) return false;
+    const int per_cu = (E->n + 255) / 256, waves = (E->max_sites / 2 + 63) / 64;
+    return E->max_sites <= su2::SMALL_SITES && per_cu * waves <= 8 &&
+           per_cu * (su2::small_lds_bytes(E->f32, (int)E->max_sites) + 1024) <= (size_t)160 << 10;
+}
+
+// The sweeps of run_sweeps (over = 0) or over-relaxation sweeps as one such
+// launch; false: not launched.
+bool run_small(su2_ensemble_s *E, int nsweeps, int over, int meas, int every, bool *err_enqueued) {
+    su2::SmallRun r{};
+    r.seed = E->hst.seed;
+    r.sweep0 = E->hst.sweep;
+    r.nsweeps = nsweeps;
+    r.over = over;
+    r.every = every;
+    r.nm = meas ? nsweeps / every : 0;
+    if (!su2::launch_small_run(kargs(E), E->f32, E->n, (int)E->max_sites, r, (meas & 1) ? E->run_plaq : nullptr,
+                               (meas & 2) ? E->run_poly : nullptr, E->n == 1 ? E->derr : nullptr, E->stream()))
+        return false;
+    if (err_enqueued) *err_enqueued = E->n == 1;
+    if (!over) {
+        E->hst.sweep += (unsigned)nsweeps;
+        E->hst.next = E->hst.sweep;
+        E->updates += (unsigned long long)nsweeps * (unsigned long long)E->total_links;
+    }
+    invalidate_measure_buffers(E);
+    return true;
+}
+
 // nsweeps sweeps; with meas, sweep k (0-based) of the run is measured when
 // (k + 1) % every == 0 (nsweeps / every measurements, series batches of at
 // most nslots of them) and the remaining nsweeps % every sweeps at the end
@@ -766,6 +801,10 @@ su2_status run_sweeps(su2_ensemble_s *E, int nsweeps, int meas, int every, bool 
                       bool upload = false) {
     const int nm = meas ? nsweeps / every : 0;
     if (err_enqueued) *err_enqueued = false;
+    if (small_run_ok(E) && run_small(E, nsweeps, 0, meas, every, err_enqueued)) {
+        HIPCHK(hipGetLastError());
+        return SU2_OK;
+    }
     if (err_enqueued && run_graph_ok(E, nsweeps)) {
         // every call synchronises before it returns, so no replay of a run
         // graph is pending while these words are rewritten
@@ -839,12 +878,10 @@ su2_status measure_plaquette(su2_ensemble_s *E, int l, double *avg, double *sp, 
     {
         Timed t(E, SU2_K_REDUCE, s);
         su2::launch_finalize(E->ddesc, E->n, E->fin_chunks, E->part_plaq, nullptr, E->fin_cnt, E->fin_chunk,
-                             E->res, nullptr, 4, s);
+                             E->dres, nullptr, 4, E->st, E->derr, s);
         t.done(s);
     }
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(E->hres, E->res, sizeof(double) * 4 * E->n, hipMemcpyDeviceToHost, s));
-    const su2_status st = finish(E);
+    const su2_status st = finish(E, true);
     if (st == SU2_EDEVICE) return st;
     if (avg) *avg = E->hres[4 * l + 0];
     if (sp) *sp = E->hres[4 * l + 1];
@@ -863,12 +900,10 @@ su2_status measure_polyakov(su2_ensemble_s *E, int l, double *out) {
     {
         Timed t(E, SU2_K_REDUCE, s);
         su2::launch_finalize(E->ddesc, E->n, E->fin_chunks, nullptr, E->part_poly, E->fin_cnt, E->fin_chunk,
-                             nullptr, E->res, 4, s);
+                             nullptr, E->dres, 4, E->st, E->derr, s);
         t.done(s);
     }
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(E->hres, E->res, sizeof(double) * 4 * E->n, hipMemcpyDeviceToHost, s));
-    const su2_status st = finish(E);
+    const su2_status st = finish(E, true);
     if (st == SU2_EDEVICE) return st;
     if (out) *out = E->hres[4 * l];
     return st;
@@ -1454,7 +1489,9 @@ su2_status su2_overrelax(su2_lattice E, int nsweeps) {
     if (nsweeps < 0) return SU2_EINVAL;
     hipStream_t s = E->stream();
     const KArgs a = kargs(E);
-    for (int k = 0; k < nsweeps; ++k)
+    bool err_enqueued = false;
+    const bool small = nsweeps > 0 && small_run_ok(E) && run_small(E, nsweeps, 1, 0, 1, &err_enqueued);
+    for (int k = 0; k < nsweeps && !small; ++k)
         for (int mu = 0; mu < 4; ++mu)
             for (int par = 0; par < 2; ++par) {
                 Timed t(E, SU2_K_OVERRELAX, s, true);
@@ -1464,7 +1501,7 @@ su2_status su2_overrelax(su2_lattice E, int nsweeps) {
     HIPCHK(hipGetLastError());
     if (nsweeps == 0) return SU2_OK;
     invalidate_measure_buffers(E);
-    return finish(E);
+    return finish(E, err_enqueued);
 }
 
 su2_status su2_plaquette(su2_lattice E, double *avg, double *sp, double *tp) {

@@ -24,6 +24,22 @@ struct KArgs {
     int every;                           // series: one measured sweep per `every` sweeps (>= 1)
 };
 
+// A call's sweeps of small lattices, one workgroup per lattice with its links
+// in LDS.
+constexpr int SMALL_SITES = 1024;  // largest lattice
+constexpr int SMALL_BLOCK = 512;   // threads at most: one link per lane
+struct SmallRun {
+    unsigned long long seed;
+    unsigned int sweep0;   // Philox sweep word of the first sweep
+    int nsweeps, over;     // over: over-relaxation instead of heat bath
+    int every, nm;         // measured sweeps: every `every`-th, nm of them
+};
+size_t small_lds_bytes(bool f32, int sites);
+// false: the launch shape is not available; errp (nullable): where a single
+// lattice's error word goes.
+bool launch_small_run(const KArgs &a, bool f32, int nlat, int sites, const SmallRun &r, double *outp, double *outl,
+                      unsigned *errp, hipStream_t s);
+
 // Optional timing events stamped by the launch itself (both null: none).
 struct Ev {
     hipEvent_t a = nullptr, b = nullptr;
@@ -50,9 +66,10 @@ void launch_polyakov(const KArgs &a, bool f32, double *part, int block, int grid
 // lattice, cnt[nlat] arrival tickets (zero between launches), chunk scratch
 // of 6 doubles per workgroup.  pp: k_plaquette partials (4 per tile) ->
 // outp[l * ostride + 0..2] = (avg, spatial, temporal); pl: Polyakov
-// partials -> outl[l * ostride].
+// partials -> outl[l * ostride]; the error word -> err.
 void launch_finalize(const LatDesc *desc, int nlat, int chunks, const double *pp, const double *pl,
-                     unsigned *cnt, double *chunk, double *outp, double *outl, long long ostride, hipStream_t s);
+                     unsigned *cnt, double *chunk, double *outp, double *outl, long long ostride, const DevState *st,
+                     unsigned *err, hipStream_t s);
 // Series values of nsw consecutive measured sweeps, slots slot0 .. slot0 +
 // nsw - 1 (mod nslots): plaquette from the heat-bath partials (12 doubles
 // per heat-bath tile per slot: 3 planes x 4 wavefronts, unused entries zero;

@@ -53,6 +53,22 @@ __device__ __forceinline__ int step_bwd(const LatDesc &d, const Site &S, int mu)
     return S.c[mu] == 0 ? wrap : in;
 }
 
+// The same for a run-time (uniform) direction.
+__device__ __forceinline__ int coord_of(const Site &S, int mu) {
+    return mu == 0 ? S.c[0] : mu == 1 ? S.c[1] : mu == 2 ? S.c[2] : S.c[3];
+}
+__device__ __forceinline__ int extent_of(const LatDesc &d, int mu) {
+    return mu == 0 ? d.n[0] : mu == 1 ? d.n[1] : mu == 2 ? d.n[2] : d.n[3];
+}
+__device__ __forceinline__ int step_fwd_rt(const LatDesc &d, const Site &S, int mu) {
+    const int st = uni(stride_of(d, mu)), n = uni(extent_of(d, mu));
+    return coord_of(S, mu) == n - 1 ? -(n - 1) * st : st;
+}
+__device__ __forceinline__ int step_bwd_rt(const LatDesc &d, const Site &S, int mu) {
+    const int st = uni(stride_of(d, mu)), n = uni(extent_of(d, mu));
+    return coord_of(S, mu) == 0 ? (n - 1) * st : -st;
+}
+
 // Uniform bases of the (direction, parity) blocks of one lattice in a link
 // buffer whose lattice starts at link `first` ([mu][parity][cb]).
 template <class T, int NDIR> struct Blocks {
@@ -125,17 +141,16 @@ __device__ __forceinline__ void gather(const LatDesc &d, const Blocks<T, 4> &B, 
 // fused multiply-adds.  The planes nu < MU come first, so Vlow (the fused
 // plaquette) is V as it stands after plane MU - 1: the substep updates its
 // links bit for bit the same with and without the plaquette.
-template <class T, int MU>
-__device__ __forceinline__ Q<T> combine(const Q<T> (&L)[18], Q<T> *Vlow = nullptr) {
+template <class T>
+__device__ __forceinline__ Q<T> combine(const Q<T> (&L)[18], int mu, Q<T> *Vlow = nullptr) {
     Q<T> V{T(0), T(0), T(0), T(0)};
 #pragma unroll
-    for (int nu = 0; nu < 4; ++nu) {
-        if (nu == MU) continue;
-        const int q = 6 * (nu < MU ? nu : nu - 1);
+    for (int k = 0; k < 3; ++k) {  // plane nu = k, or k + 1 from nu = mu on
+        const int q = 6 * k;
         const Q<T> &A = L[q + 0], &Bm = L[q + 1], &C = L[q + 2], &D = L[q + 3], &E = L[q + 4], &F = L[q + 5];
         qmul_acc(V, A, qdag(qmul(C, Bm)));
         qmul_acc(V, qdag(qmul(E, D)), F);
-        if (Vlow && nu == MU - 1) *Vlow = V;
+        if (Vlow && k == mu - 1) *Vlow = V;
     }
     return V;
 }
@@ -145,7 +160,7 @@ __device__ __forceinline__ Q<T> staple(const LatDesc &d, const Blocks<T, 4> &B, 
                                        Q<T> *Vlow = nullptr) {
     Q<T> L[18];
     gather<T, MU>(d, B, S, par, L);
-    return combine<T, MU>(L, Vlow);
+    return combine<T>(L, MU, Vlow);
 }
 
 template <class T, int N> __device__ __forceinline__ T pick(const T (&a)[N], int m) {
@@ -185,9 +200,148 @@ template <class T, int N> __device__ __forceinline__ void put(T (&a)[N], int m, 
 // plaquette sum (paper Sec. 2, eq. for <P>) of the configuration at the end
 // of the sweep; by linearity only the summed staple of those planes is
 // kept.  Each wavefront writes its binary64 sum to slot MU-1 of its tile.
+// One pass of up to NL links per lane, those of parity `par` at half-sites
+// first, first + blockDim.x, ... below vh: staple_at(S, Vlow) the staple of the
+// link at S, store(cb, s, U, rec) the new link.  Adds the tries of the
+// wavefront to wtries and, with PLAQ, 1/2 Tr(U' Vlow) to pq.
+template <class T, int NL, bool PLAQ, class STAPLE, class STORE>
+__device__ __forceinline__ void heatbath_links(const LatDesc &d, int par, int first, T beta, int sampler, uint32_t sweep,
+                                               uint32_t c2, uint32_t k0, uint32_t k1, unsigned *err,
+                                               uint32_t &wtries, double &pq, const STAPLE &staple_at,
+                                               const STORE &store) {
+    using M = Mth<T>;
+    int sidx[NL];
+    T alpha[NL], ial[NL];  // alpha = beta k and its reciprocal (0 when alpha = 0)
+    Q<T> Wd[NL];
+    Q<T> Vl[NL];  // summed staples of the planes nu < MU (PLAQ only)
+    uint32_t pend = 0, nonfinite = 0;
+#pragma unroll
+    for (int m = 0; m < NL; ++m) {
+        const int cb = first + m * (int)blockDim.x;
+        sidx[m] = 0;
+        alpha[m] = T(0);
+        ial[m] = T(0);
+        Wd[m] = qone<T>();
+        if (cb < d.vh) {
+            Vl[m] = Q<T>{T(0), T(0), T(0), T(0)};
+            const Site S = site_of(d, cb, par);
+            const Q<T> V = staple_at(S, PLAQ ? &Vl[m] : nullptr);
+            const T k2 = V.a * V.a + V.b * V.b + V.c * V.c + V.d * V.d;
+            // a non-finite staple (a non-finite neighbour link) is not
+            // sampled: the link becomes NaN and the error word counts it
+            if (k2 <= M::MAXV) pend |= 1u << m;
+            else nonfinite |= 1u << m;
+            T k, ik;
+            if (sizeof(T) == 4) {
+                ik = M::rsqrt_(k2);
+                k = k2 > T(0) ? k2 * ik : T(0);
+            } else {
+                k = M::sqrt_(k2);
+                ik = T(1) / k;
+            }
+            sidx[m] = S.s;
+            alpha[m] = beta * k;
+            if (alpha[m] > T(0)) ial[m] = M::rcp_(alpha[m]);
+            if (k2 > T(0)) Wd[m] = Q<T>{V.a * ik, -V.b * ik, -V.c * ik, -V.d * ik};
+        }
+    }
+
+    // Creutz factor -expm1(-2 alpha) per link, formed only when a lane of
+    // the wavefront samples with Creutz (as a loop invariant it would
+    // otherwise be hoisted and evaluated for every link).
+    T cfv[NL];
+    bool creutz_any = false;
+#pragma unroll
+    for (int m = 0; m < NL; ++m) {
+        cfv[m] = T(0);
+        creutz_any |= ((pend >> m) & 1u) && ((sampler == 1) || !(alpha[m] >= T(2)));
+    }
+    if (__ballot(creutz_any)) {
+#pragma unroll
+        for (int m = 0; m < NL; ++m)
+            if (((pend >> m) & 1u) && alpha[m] >= T(1e-20)) cfv[m] = -M::expm1_(T(-2) * alpha[m]);
+    }
+
+    // Rejection loop: a lane moves to its next link when one is accepted.
+    T delta[NL];
+    uint32_t rec[NL];
+#pragma unroll
+    for (int m = 0; m < NL; ++m) {
+        delta[m] = ((nonfinite >> m) & 1u) ? M::nan_() : T(0);
+        rec[m] = 0;
+    }
+    if (__ballot(nonfinite != 0u)) {
+        if (nonfinite) atomicAdd(err, (unsigned)__popc(nonfinite));
+    }
+    // The loop runs while any lane of the wavefront has a link pending;
+    // each pass is one try of every active lane, so the wavefront's try
+    // count is the sum of the active-lane counts (scalar work).
+    uint32_t j = 0;
+    while (true) {
+        const unsigned long long act = __ballot(pend != 0u);
+        if (act == 0ull) break;
+        wtries += (uint32_t)__popcll(act);
+        if (!pend) continue;
+        const int m = __builtin_ctz(pend);
+        const int s = pick(sidx, m);
+        const T al = pick(alpha, m), ia = pick(ial, m);
+        const bool creutz = (sampler == 1) || !(al >= T(2));
+        const uint4 wd = philox10((uint32_t)s, sweep, c2, j, k0, k1);
+        bool acc;
+        T dl;
+        if (creutz) {
+            const T u1 = M::u(wd.x), u2 = M::u(wd.y);
+            if (al >= T(1e-20)) {
+                const T cf = pick(cfv, m);
+                dl = -M::log1p_(-(T(1) - u1) * cf) * ia;
+            } else {
+                dl = T(2) * (T(1) - u1);
+            }
+            acc = u2 * u2 <= dl * (T(2) - dl);
+        } else {
+            const T r1 = M::u(wd.x), r2 = M::u(wd.y), r3 = M::u(wd.z), r4 = M::u(wd.w);
+            const T cs = M::cos2pi(r2);
+            const T lam2 = -(M::lg(r1) + cs * cs * M::lg(r3)) * (ia * (T(0.5) * M::LN_LG));
+            acc = r4 * r4 <= T(1) - lam2;
+            dl = T(2) * lam2;
+        }
+        ++j;
+        if (acc || j >= MAX_TRIES) {
+            if (!acc) {
+                atomicAdd(err, 1u);
+                dl = M::nan_();
+            }
+            put(delta, m, dl);
+            put(rec, m, j | ((uint32_t)creutz << 31));
+            pend &= pend - 1;
+            j = 0;
+        }
+    }
+
+    // Direction from its own Philox call (try word 0xFFFFFFFF), then
+    // U' = X W^dag, renormalised.
+#pragma unroll
+    for (int m = 0; m < NL; ++m) {
+        const int cb = first + m * (int)blockDim.x;
+        if (cb < d.vh) {
+            const uint4 wd = philox10((uint32_t)sidx[m], sweep, c2, 0xFFFFFFFFu, k0, k1);
+            const T u1 = M::u(wd.x), u2 = M::u(wd.y);
+            const T dl = delta[m];
+            const T cth = T(1) - T(2) * u1;
+            const T sth = T(2) * M::sqrt_(u1 * (T(1) - u1));
+            const T ra = M::sqrt_(dl * (T(2) - dl));
+            const T rs = ra * sth;
+            const Q<T> X{T(1) - dl, rs * M::cos2pi(u2), rs * M::sin2pi(u2), ra * cth};
+            const Q<T> Un = qnormalize(qmul(X, Wd[m]));
+            store(cb, sidx[m], Un, rec[m]);
+            if (PLAQ)  // 1/2 Re Tr(U' V_low)
+                pq += (double)(Un.a * Vl[m].a - Un.b * Vl[m].b - Un.c * Vl[m].c - Un.d * Vl[m].d);
+        }
+    }
+}
+
 template <class T, int MU, bool TRACE, int NL, bool PLAQ>
 __global__ __launch_bounds__(256) void k_heatbath(KArgs a, int par) {
-    using M = Mth<T>;
     // the first substep of a sweep takes the sweep word from `next`, and so
     // does a lone substep (no advance: part of the next sweep to run)
     const bool first = a.advance && MU == 0 && par == 0;
@@ -211,136 +365,15 @@ __global__ __launch_bounds__(256) void k_heatbath(KArgs a, int par) {
         const uint32_t c2 = tag(d.lat_id, PURPOSE_HEATBATH, MU, par);
         const T beta = (sizeof(T) == 4) ? (T)d.betaf : (T)d.beta;
 
-        int sidx[NL];
-        T alpha[NL], ial[NL];  // alpha = beta k and its reciprocal (0 when alpha = 0)
-        Q<T> Wd[NL];
-        Q<T> Vl[NL];  // summed staples of the planes nu < MU (PLAQ only)
-        uint32_t pend = 0, nonfinite = 0;
-#pragma unroll
-        for (int m = 0; m < NL; ++m) {
-            const int cb = tl.y + m * (int)blockDim.x + (int)threadIdx.x;
-            sidx[m] = 0;
-            alpha[m] = T(0);
-            ial[m] = T(0);
-            Wd[m] = qone<T>();
-            if (cb < d.vh) {
-                Vl[m] = Q<T>{T(0), T(0), T(0), T(0)};
-                const Site S = site_of(d, cb, par);
-                const Q<T> V = staple<T, MU>(d, B, S, par, PLAQ ? &Vl[m] : nullptr);
-                const T k2 = V.a * V.a + V.b * V.b + V.c * V.c + V.d * V.d;
-                // a non-finite staple (a non-finite neighbour link) is not
-                // sampled: the link becomes NaN and the error word counts it
-                if (k2 <= M::MAXV) pend |= 1u << m;
-                else nonfinite |= 1u << m;
-                T k, ik;
-                if (sizeof(T) == 4) {
-                    ik = M::rsqrt_(k2);
-                    k = k2 > T(0) ? k2 * ik : T(0);
-                } else {
-                    k = M::sqrt_(k2);
-                    ik = T(1) / k;
-                }
-                sidx[m] = S.s;
-                alpha[m] = beta * k;
-                if (alpha[m] > T(0)) ial[m] = M::rcp_(alpha[m]);
-                if (k2 > T(0)) Wd[m] = Q<T>{V.a * ik, -V.b * ik, -V.c * ik, -V.d * ik};
-            }
-        }
-
-        // Creutz factor -expm1(-2 alpha) per link, formed only when a lane of
-        // the wavefront samples with Creutz (as a loop invariant it would
-        // otherwise be hoisted and evaluated for every link).
-        T cfv[NL];
-        bool creutz_any = false;
-#pragma unroll
-        for (int m = 0; m < NL; ++m) {
-            cfv[m] = T(0);
-            creutz_any |= ((pend >> m) & 1u) && ((a.sampler == 1) || !(alpha[m] >= T(2)));
-        }
-        if (__ballot(creutz_any)) {
-#pragma unroll
-            for (int m = 0; m < NL; ++m)
-                if (((pend >> m) & 1u) && alpha[m] >= T(1e-20)) cfv[m] = -M::expm1_(T(-2) * alpha[m]);
-        }
-
-        // Rejection loop: a lane moves to its next link when one is accepted.
-        T delta[NL];
-        uint32_t rec[NL];
-#pragma unroll
-        for (int m = 0; m < NL; ++m) {
-            delta[m] = ((nonfinite >> m) & 1u) ? M::nan_() : T(0);
-            rec[m] = 0;
-        }
-        if (__ballot(nonfinite != 0u)) {
-            if (nonfinite) atomicAdd(a.err, (unsigned)__popc(nonfinite));
-        }
-        // The loop runs while any lane of the wavefront has a link pending;
-        // each pass is one try of every active lane, so the wavefront's try
-        // count is the sum of the active-lane counts (scalar work).
-        uint32_t j = 0, wtries = 0;
-        while (true) {
-            const unsigned long long act = __ballot(pend != 0u);
-            if (act == 0ull) break;
-            wtries += (uint32_t)__popcll(act);
-            if (!pend) continue;
-            const int m = __builtin_ctz(pend);
-            const int s = pick(sidx, m);
-            const T al = pick(alpha, m), ia = pick(ial, m);
-            const bool creutz = (a.sampler == 1) || !(al >= T(2));
-            const uint4 wd = philox10((uint32_t)s, sweep, c2, j, k0, k1);
-            bool acc;
-            T dl;
-            if (creutz) {
-                const T u1 = M::u(wd.x), u2 = M::u(wd.y);
-                if (al >= T(1e-20)) {
-                    const T cf = pick(cfv, m);
-                    dl = -M::log1p_(-(T(1) - u1) * cf) * ia;
-                } else {
-                    dl = T(2) * (T(1) - u1);
-                }
-                acc = u2 * u2 <= dl * (T(2) - dl);
-            } else {
-                const T r1 = M::u(wd.x), r2 = M::u(wd.y), r3 = M::u(wd.z), r4 = M::u(wd.w);
-                const T cs = M::cos2pi(r2);
-                const T lam2 = -(M::lg(r1) + cs * cs * M::lg(r3)) * (ia * (T(0.5) * M::LN_LG));
-                acc = r4 * r4 <= T(1) - lam2;
-                dl = T(2) * lam2;
-            }
-            ++j;
-            if (acc || j >= MAX_TRIES) {
-                if (!acc) {
-                    atomicAdd(a.err, 1u);
-                    dl = M::nan_();
-                }
-                put(delta, m, dl);
-                put(rec, m, j | ((uint32_t)creutz << 31));
-                pend &= pend - 1;
-                j = 0;
-            }
-        }
-
-        // Direction from its own Philox call (try word 0xFFFFFFFF), then
-        // U' = X W^dag, renormalised.
+        uint32_t wtries = 0;
         double pq = 0.0;
-#pragma unroll
-        for (int m = 0; m < NL; ++m) {
-            const int cb = tl.y + m * (int)blockDim.x + (int)threadIdx.x;
-            if (cb < d.vh) {
-                const uint4 wd = philox10((uint32_t)sidx[m], sweep, c2, 0xFFFFFFFFu, k0, k1);
-                const T u1 = M::u(wd.x), u2 = M::u(wd.y);
-                const T dl = delta[m];
-                const T cth = T(1) - T(2) * u1;
-                const T sth = T(2) * M::sqrt_(u1 * (T(1) - u1));
-                const T ra = M::sqrt_(dl * (T(2) - dl));
-                const T rs = ra * sth;
-                const Q<T> X{T(1) - dl, rs * M::cos2pi(u2), rs * M::sin2pi(u2), ra * cth};
-                const Q<T> Un = qnormalize(qmul(X, Wd[m]));
-                sts_(B, MU, par, (uint32_t)cb, Un);
-                if (TRACE) a.trace[d.toff + (long long)sidx[m] * 4 + MU] = rec[m];
-                if (PLAQ)  // 1/2 Re Tr(U' V_low)
-                    pq += (double)(Un.a * Vl[m].a - Un.b * Vl[m].b - Un.c * Vl[m].c - Un.d * Vl[m].d);
-            }
-        }
+        heatbath_links<T, NL, PLAQ>(
+            d, par, tl.y + (int)threadIdx.x, beta, a.sampler, sweep, c2, k0, k1, a.err, wtries, pq,
+            [&](const Site &S, Q<T> *Vlow) { return staple<T, MU>(d, B, S, par, Vlow); },
+            [&](int cb, int s, const Q<T> &U, uint32_t rec) {
+                sts_(B, MU, par, (uint32_t)cb, U);
+                if (TRACE) a.trace[d.toff + (long long)s * 4 + MU] = rec;
+            });
         if (PLAQ) {
             pq = wave_sum_f64(pq);
             if ((threadIdx.x & 63) == 0)
@@ -356,6 +389,23 @@ __global__ __launch_bounds__(256) void k_heatbath(KArgs a, int par) {
 
 // Over-relaxation substep (paper Sec. 2, over-relaxation equation, in its
 // action-preserving form U' = W^dag U^dag W^dag, W = V/k).
+// overrelax_link: U replaced by its image under the staple V; false where V
+// is zero and U stays.
+template <class T> __device__ __forceinline__ bool overrelax_link(const Q<T> &V, Q<T> &U, unsigned *err) {
+    const T k2 = V.a * V.a + V.b * V.b + V.c * V.c + V.d * V.d;
+    if (!(k2 <= Mth<T>::MAXV)) {  // non-finite staple: NaN link, counted
+        atomicAdd(err, 1u);
+        const T nan = Mth<T>::nan_();
+        U = Q<T>{nan, nan, nan, nan};
+        return true;
+    }
+    if (!(k2 > T(0))) return false;
+    const T ik = T(1) / Mth<T>::sqrt_(k2);
+    const Q<T> Wd{V.a * ik, -V.b * ik, -V.c * ik, -V.d * ik};
+    U = qnormalize(qmul(qmul(Wd, qdag(U)), Wd));
+    return true;
+}
+
 template <class T, int MU>
 __global__ __launch_bounds__(256) void k_overrelax(KArgs a, int par) {
     for_each_tile(a.ntiles, a.xcd_remap, [&](int tile) {
@@ -366,19 +416,175 @@ __global__ __launch_bounds__(256) void k_overrelax(KArgs a, int par) {
         if (cb >= d.vh) return;
         const Site S = site_of(d, cb, par);
         const Q<T> V = staple<T, MU>(d, B, S, par);
-        const T k2 = V.a * V.a + V.b * V.b + V.c * V.c + V.d * V.d;
-        if (!(k2 <= Mth<T>::MAXV)) {  // non-finite staple: NaN link, counted
-            atomicAdd(a.err, 1u);
-            const T nan = Mth<T>::nan_();
-            sts_(B, MU, par, (uint32_t)cb, Q<T>{nan, nan, nan, nan});
-            return;
-        }
-        if (!(k2 > T(0))) return;
-        const T ik = T(1) / Mth<T>::sqrt_(k2);
-        const Q<T> Wd{V.a * ik, -V.b * ik, -V.c * ik, -V.d * ik};
-        const Q<T> U = lds_(B, MU, par, (uint32_t)cb);
-        sts_(B, MU, par, (uint32_t)cb, qnormalize(qmul(qmul(Wd, qdag(U)), Wd)));
+        Q<T> U = lds_(B, MU, par, (uint32_t)cb);
+        if (overrelax_link(V, U, a.err)) sts_(B, MU, par, (uint32_t)cb, U);
     });
+}
+
+// ---------------------------------------------------------------------------
+// Whole runs of small lattices.  A substep of a lattice of up to
+// SMALL_SITES sites is a few wavefronts, and its launch lasts as long as one
+// link update after a cold start (descriptor, tile and links fetched anew by
+// every kernel: 3.3 us in binary32, 8 us in binary64).  Here one workgroup
+// keeps its lattice in LDS for all sweeps of a call, a workgroup barrier
+// between substeps, and one launch advances every lattice of the ensemble.
+// The update is heatbath_links / the formula of k_overrelax on the same
+// staples, so the links are bit for bit those of the substep kernels.
+// At 1024 sites (8 wavefronts a substep) one workgroup is still faster than
+// the launches in both precisions, by a tenth in binary64 (figures at
+// k_small_run); beyond it two wavefronts share a SIMD and lattices are faster
+// spread over the chip.
+
+// Links of one lattice in LDS, in the order of the link buffer.
+template <class T> struct LdsBlocks;
+template <> struct LdsBlocks<float> {
+    float4 *p;
+    int vh;
+    __device__ __forceinline__ Q<float> ld(int mu, int par, int cb) const {
+        const float4 v = p[(2 * mu + par) * vh + cb];
+        return Q<float>{v.x, v.y, v.z, v.w};
+    }
+    __device__ __forceinline__ void st(int mu, int par, int cb, const Q<float> &q) const {
+        p[(2 * mu + par) * vh + cb] = make_float4(q.a, q.b, q.c, q.d);
+    }
+};
+template <> struct LdsBlocks<double> {
+    double2 *p;
+    int vh;
+    __device__ __forceinline__ Q<double> ld(int mu, int par, int cb) const {
+        const double2 *b = p + 2 * (2 * mu + par) * vh + cb;
+        return Q<double>{b[0].x, b[0].y, b[vh].x, b[vh].y};
+    }
+    __device__ __forceinline__ void st(int mu, int par, int cb, const Q<double> &q) const {
+        double2 *b = p + 2 * (2 * mu + par) * vh + cb;
+        b[0] = make_double2(q.a, q.b);
+        b[vh] = make_double2(q.c, q.d);
+    }
+};
+
+// staple() with the links in LDS and the direction a run-time (uniform) value
+template <class T>
+__device__ __forceinline__ Q<T> staple_lds(const LatDesc &d, const LdsBlocks<T> &B, const Site &S, int par, int mu,
+                                           Q<T> *Vlow) {
+    Q<T> L[18];
+    const int op = par ^ 1;
+    const int s_mu = S.s + step_fwd_rt(d, S, mu);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int nu = k < mu ? k : k + 1, q = 6 * k;
+        const int fn = step_fwd_rt(d, S, nu), bn = step_bwd_rt(d, S, nu);
+        L[q + 0] = B.ld(nu, op, s_mu >> 1);
+        L[q + 1] = B.ld(mu, op, (S.s + fn) >> 1);
+        L[q + 2] = B.ld(nu, par, S.s >> 1);
+        L[q + 3] = B.ld(nu, par, (s_mu + bn) >> 1);
+        L[q + 4] = B.ld(mu, op, (S.s + bn) >> 1);
+        L[q + 5] = B.ld(nu, op, (S.s + bn) >> 1);
+    }
+    return combine<T>(L, mu, Vlow);
+}
+
+// Links of the lattice between the link buffer and LDS (16-byte words).
+template <class T>
+__device__ __forceinline__ void small_copy(const LatDesc &d, char *links, float4 *lds, bool in) {
+    float4 *g = (float4 *)(links + d.off * Links<T>::BYTES);
+    const int n = 8 * d.vh * (Links<T>::BYTES / 16);
+    for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x) {
+        if (in) lds[i] = g[i];
+        else g[i] = lds[i];
+    }
+}
+
+// Sweeps (with over = 0: heat bath, sweep words sweep0 ..; else
+// over-relaxation) of lattice blockIdx.x.  Measured sweeps write the mean
+// plaquette, summed as in k_heatbath, and the Polyakov loop to
+// outp / outl[l * nm + measurement].
+// us per substep here and as launches: heat bath 2.1 and 3.8 (4^4 binary32),
+// 4.3 and 6.0 (4^4 binary64), 2.6 and 4.3 (1024 sites, binary32), 6.6 and 7.3
+// (1024 sites, binary64); over-relaxation 1.3 and 3.4 (4^4 binary32), 2.2 and
+// 4.1 (1024 sites, binary64).  The time is the instructions of one wavefront's
+// update, issued alone on its SIMD.
+template <class T>
+__global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, double *outp, double *outl,
+                                                           unsigned *errp) {
+    extern __shared__ double4 small_lds[];
+    __shared__ double red[SMALL_BLOCK / 64][2];
+    const int l = (int)blockIdx.x, tid = (int)threadIdx.x, nb = (int)blockDim.x, lane = tid & 63, wave = tid >> 6;
+    const LatDesc d = load_desc(a.desc + l);
+    const LdsBlocks<T> B{(decltype(LdsBlocks<T>::p))small_lds, d.vh};
+    const T beta = (sizeof(T) == 4) ? (T)d.betaf : (T)d.beta;
+    const uint32_t k0 = (uint32_t)r.seed, k1 = (uint32_t)(r.seed >> 32);
+    small_copy<T>(d, (char *)a.links, (float4 *)small_lds, true);
+    __syncthreads();
+    unsigned long long tries = 0;
+    int next = r.every - 1, m = 0;  // sweep of the next measurement
+    for (int sw = 0; sw < r.nsweeps; ++sw) {
+        double pq = 0.0;
+        for (int sub = 0; sub < 8; ++sub) {
+            const int mu = sub >> 1, par = sub & 1;
+            if (!r.over) {
+                const uint32_t c2 = tag(d.lat_id, PURPOSE_HEATBATH, mu, par);
+                for (int first = tid; first - lane < d.vh; first += nb) {
+                    uint32_t wt = 0;
+                    double pw = 0.0;
+                    heatbath_links<T, 1, true>(
+                        d, par, first, beta, a.sampler, r.sweep0 + (uint32_t)sw, c2, k0, k1, a.err, wt, pw,
+                        [&](const Site &S, Q<T> *Vlow) { return staple_lds<T>(d, B, S, par, mu, Vlow); },
+                        [&](int cb, int, const Q<T> &U, uint32_t) { B.st(mu, par, cb, U); });
+                    tries += wt;
+                    if (par) pq += pw;
+                }
+            } else {
+                for (int cb = tid; cb < d.vh; cb += nb) {
+                    const Site S = site_of(d, cb, par);
+                    const Q<T> V = staple_lds<T>(d, B, S, par, mu, (Q<T> *)nullptr);
+                    Q<T> U = B.ld(mu, par, cb);
+                    if (overrelax_link(V, U, a.err)) B.st(mu, par, cb, U);
+                }
+            }
+            __syncthreads();
+        }
+        if (sw == next && m < r.nm) {
+            double pl = 0.0;
+            if (outl)
+                for (int xs = tid; xs < d.ns; xs += nb) {
+                    int row, x, z, y;
+                    udiv(xs, d.n[0], d.inv_nx, row, x);
+                    udiv(row, d.n[1], d.inv_ny, z, y);
+                    Q<T> P = qone<T>();
+                    const int p0 = (x + y + z) & 1;
+                    for (int t = 0; t < d.n[3]; ++t) P = qmul(P, B.ld(3, (p0 + t) & 1, (xs + d.ns * t) >> 1));
+                    pl += (double)P.a;
+                }
+            pq = wave_sum_f64(pq);
+            pl = wave_sum_f64(pl);
+            if (lane == 0) red[wave][0] = pq, red[wave][1] = pl;
+            __syncthreads();
+            if (tid == 0) {
+                DD s{0.0, 0.0}, q{0.0, 0.0};
+                for (int v = 0; v < (nb >> 6); ++v) {
+                    s = dd_add(s, DD{red[v][0], 0.0});
+                    q = dd_add(q, DD{red[v][1], 0.0});
+                }
+                if (outp) outp[(long long)l * r.nm + m] = (s.hi + s.lo) / (12.0 * (double)d.vh);
+                if (outl) outl[(long long)l * r.nm + m] = (q.hi + q.lo) / (double)d.ns;
+            }
+            __syncthreads();
+            next += r.every;
+            ++m;
+        }
+    }
+    small_copy<T>(d, (char *)a.links, (float4 *)small_lds, false);
+    if (lane == 0 && tries) atomicAdd(&a.tries_part[d.tile0], tries);
+    if (l == 0 && tid == 0 && !r.over) {
+        a.st->seed = r.seed;
+        a.st->sweep = a.st->next = r.sweep0 + (uint32_t)r.nsweeps;
+    }
+    // one lattice: its error word, all of whose counts are this workgroup's or
+    // earlier, goes straight to the host
+    if (errp) {
+        __syncthreads();
+        if (tid == 0) *errp = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -581,7 +787,10 @@ __global__ __launch_bounds__(256) void k_polyakov(KArgs a, double *part) {
 // b / C: it sums its share of the lattice's partials, writes a (hi, lo) pair
 // per quantity to `chunk`, and the last chunk of the lattice to arrive
 // (ticket in cnt[l]) combines the C pairs in chunk order and writes the
-// plaquette (avg, spatial, temporal) and / or the Polyakov loop.
+// plaquette (avg, spatial, temporal) and / or the Polyakov loop, and with the
+// first lattice the error word, to mapped host memory: a measurement call ends
+// with its synchronisation, without a copy or a kernel for the error word
+// (4^4 plaquette: 24 us).
 __device__ __forceinline__ void chunk_range(int n, int C, int c, int &lo, int &hi) {
     lo = (int)(((long long)n * c) / C);
     hi = (int)(((long long)n * (c + 1)) / C);
@@ -589,7 +798,7 @@ __device__ __forceinline__ void chunk_range(int n, int C, int c, int &lo, int &h
 
 __global__ __launch_bounds__(256) void k_finalize(const LatDesc *desc, const double *pp, const double *pl,
                                                   unsigned *cnt, double *chunk, int C, double *outp, double *outl,
-                                                  long long ostride) {
+                                                  long long ostride, const DevState *st, unsigned *err) {
     __shared__ DD lds[3 * 4];
     __shared__ int last;
     last = 1;
@@ -668,6 +877,7 @@ __global__ __launch_bounds__(256) void k_finalize(const LatDesc *desc, const dou
             o[2] = tp / (3.0 * V);
         }
         if (pl) outl[l * ostride] = (tot[2].hi + tot[2].lo) / (double)d.ns;
+        if (l == 0) *err = st->err;
     }
 }
 
@@ -1403,6 +1613,26 @@ void launch_overrelax(const KArgs &a, bool f32, int mu, int par, int block, int 
     else launch_or_t<double>(a, mu, par, block, grid, s, ev);
 }
 
+size_t small_lds_bytes(bool f32, int sites) { return (size_t)sites * (f32 ? 64 : 128); }
+
+// Workgroups of the largest lattice's size; every one of them is resident at
+// once (the caller's rule), so a run lasts as long as its slowest lattice.
+bool launch_small_run(const KArgs &a, bool f32, int nlat, int sites, const SmallRun &r, double *outp, double *outl,
+                      unsigned *errp, hipStream_t s) {
+    const size_t lds = small_lds_bytes(f32, sites);
+    const int block = std::min(SMALL_BLOCK, std::max(64, (sites / 2 + 63) / 64 * 64));
+    const void *k = f32 ? (const void *)k_small_run<float> : (const void *)k_small_run<double>;
+    if (lds > (48 << 10) &&
+        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const dim3 g((unsigned)nlat), b((unsigned)block);
+    if (f32) hipLaunchKernelGGL((k_small_run<float>), g, b, lds, s, a, r, outp, outl, errp);
+    else hipLaunchKernelGGL((k_small_run<double>), g, b, lds, s, a, r, outp, outl, errp);
+    return true;
+}
+
 void launch_init(const KArgs &a, bool f32, int hot, int block, int grid, hipStream_t s) {
     if (f32) hipLaunchKernelGGL((k_init<float>), grid_of(a, grid), dim3(block), 0, s, a, hot);
     else hipLaunchKernelGGL((k_init<double>), grid_of(a, grid), dim3(block), 0, s, a, hot);
@@ -1435,9 +1665,10 @@ void launch_polyakov(const KArgs &a, bool f32, double *part, int block, int grid
 }
 
 void launch_finalize(const LatDesc *desc, int nlat, int chunks, const double *pp, const double *pl,
-                     unsigned *cnt, double *chunk, double *outp, double *outl, long long ostride, hipStream_t s) {
+                     unsigned *cnt, double *chunk, double *outp, double *outl, long long ostride, const DevState *st,
+                     unsigned *err, hipStream_t s) {
     hipLaunchKernelGGL(k_finalize, dim3((unsigned)(nlat * chunks)), dim3(256), 0, s, desc, pp, pl, cnt, chunk,
-                       chunks, outp, outl, ostride);
+                       chunks, outp, outl, ostride, st, err);
 }
 
 void launch_series(const LatDesc *desc, int nlat, const double *pp, long long pp_stride, const double *pl,
