@@ -280,6 +280,7 @@ KArgs kargs(su2_ensemble_s *E, int which = 0) {
     a.advance = 0;
     a.nslots = 0;
     a.every = 1;
+    a.tile_links = E->nl == 1 && E->total_sites <= su2::split_sites(E->f32, E->sampler == SU2_CREUTZ) ? E->block : 0;
     return a;
 }
 
@@ -1217,6 +1218,7 @@ su2_status su2_heatbath_noalloc(void *device_links, int Nx, int Ny, int Nz, int 
     a.advance = 1;
     a.nslots = 0;
     a.every = 1;
+    a.tile_links = 2LL * D.vh <= su2::split_sites(prec == SU2_F32, false) ? NOALLOC_BLOCK : 0;
     for (int k = 0; k < nsweeps; ++k)
         for (int mu = 0; mu < 4; ++mu)
             for (int par = 0; par < 2; ++par)

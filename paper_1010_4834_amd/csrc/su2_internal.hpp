@@ -22,7 +22,18 @@ struct KArgs {
     int advance;                         // heat bath: substeps of whole sweeps (advance the counter)
     int nslots;                          // series slots of the partial buffers (0: no series)
     int every;                           // series: one measured sweep per `every` sweeps (>= 1)
+    int tile_links;                      // heat bath: links per tile where four lanes share a link, else 0
 };
+
+// Largest number of sites, all lattices together, at which four lanes share a
+// link (k_heatbath_split; single-link launch shapes).  us per substep with one
+// and with four lanes: Kennedy-Pendleton binary64 7.9 and 6.1 at 8192 sites,
+// 8.1 and 6.7 at 32768, 8.0 and 8.3 at 57344; Creutz binary32 13.6 and 6.6 at
+// 8192, 14.3 and 9.5 at 110592, binary64 15.5 and 8.4, 17.4 and 17.2.  A
+// binary32 Kennedy-Pendleton try is too short to gain (4.1 and 4.2 at 8192).
+constexpr long long split_sites(bool f32, bool creutz) {
+    return creutz ? (f32 ? 1LL << 17 : 98304) : f32 ? 0 : 1LL << 15;
+}
 
 // A call's sweeps of small lattices, one workgroup per lattice with its links
 // in LDS.

@@ -200,6 +200,66 @@ template <class T, int N> __device__ __forceinline__ void put(T (&a)[N], int m, 
 // plaquette sum (paper Sec. 2, eq. for <P>) of the configuration at the end
 // of the sweep; by linearity only the summed staple of those planes is
 // kept.  Each wavefront writes its binary64 sum to slot MU-1 of its tile.
+// Parts of a link update shared by the heat-bath kernels.
+// alpha = beta k of a staple V, k = |V|, its reciprocal (0 when alpha = 0) and
+// W^dag = (V/k)^dag (1 when V = 0); false for a non-finite staple.
+template <class T>
+__device__ __forceinline__ bool link_weight(const Q<T> &V, T beta, T &alpha, T &ial, Q<T> &Wd) {
+    using M = Mth<T>;
+    const T k2 = V.a * V.a + V.b * V.b + V.c * V.c + V.d * V.d;
+    T k, ik;
+    if (sizeof(T) == 4) {
+        ik = M::rsqrt_(k2);
+        k = k2 > T(0) ? k2 * ik : T(0);
+    } else {
+        k = M::sqrt_(k2);
+        ik = T(1) / k;
+    }
+    alpha = beta * k;
+    ial = T(0);
+    Wd = qone<T>();
+    if (alpha > T(0)) ial = M::rcp_(alpha);
+    if (k2 > T(0)) Wd = Q<T>{V.a * ik, -V.b * ik, -V.c * ik, -V.d * ik};
+    return k2 <= M::MAXV;
+}
+// Kennedy-Pendleton try: the logarithms of its random words, then 1 - a0 into
+// dl and whether it is accepted.
+template <class T> __device__ __forceinline__ T kp_logs(const uint4 &wd) {
+    using M = Mth<T>;
+    const T r1 = M::u(wd.x), r2 = M::u(wd.y), r3 = M::u(wd.z);
+    const T cs = M::cos2pi(r2);
+    return M::lg(r1) + cs * cs * M::lg(r3);
+}
+template <class T> __device__ __forceinline__ bool kp_try(const uint4 &wd, T logs, T ia, T &dl) {
+    using M = Mth<T>;
+    const T r4 = M::u(wd.w);
+    const T lam2 = -logs * (ia * (T(0.5) * M::LN_LG));
+    dl = T(2) * lam2;
+    return r4 * r4 <= T(1) - lam2;
+}
+// Creutz try; cf = -expm1(-2 alpha).
+template <class T> __device__ __forceinline__ bool creutz_try(const uint4 &wd, T al, T ia, T cf, T &dl) {
+    using M = Mth<T>;
+    const T u1 = M::u(wd.x), u2 = M::u(wd.y);
+    if (al >= T(1e-20)) dl = -M::log1p_(-(T(1) - u1) * cf) * ia;
+    else dl = T(2) * (T(1) - u1);
+    return u2 * u2 <= dl * (T(2) - dl);
+}
+// Direction of the vector part from its own Philox call (try word
+// 0xFFFFFFFF), and U' = X W^dag, renormalised.
+template <class T> struct Direction { T cth, sth, cph, sph; };
+template <class T> __device__ __forceinline__ Direction<T> draw_direction(const uint4 &wd) {
+    using M = Mth<T>;
+    const T u1 = M::u(wd.x), u2 = M::u(wd.y);
+    return Direction<T>{T(1) - T(2) * u1, T(2) * M::sqrt_(u1 * (T(1) - u1)), M::cos2pi(u2), M::sin2pi(u2)};
+}
+template <class T> __device__ __forceinline__ Q<T> compose_link(const Direction<T> &r, T dl, const Q<T> &Wd) {
+    const T ra = Mth<T>::sqrt_(dl * (T(2) - dl));
+    const T rs = ra * r.sth;
+    const Q<T> X{T(1) - dl, rs * r.cph, rs * r.sph, ra * r.cth};
+    return qnormalize(qmul(X, Wd));
+}
+
 // One pass of up to NL links per lane, those of parity `par` at half-sites
 // first, first + blockDim.x, ... below vh: staple_at(S, Vlow) the staple of the
 // link at S, store(cb, s, U, rec) the new link.  Adds the tries of the
@@ -226,23 +286,11 @@ __device__ __forceinline__ void heatbath_links(const LatDesc &d, int par, int fi
             Vl[m] = Q<T>{T(0), T(0), T(0), T(0)};
             const Site S = site_of(d, cb, par);
             const Q<T> V = staple_at(S, PLAQ ? &Vl[m] : nullptr);
-            const T k2 = V.a * V.a + V.b * V.b + V.c * V.c + V.d * V.d;
             // a non-finite staple (a non-finite neighbour link) is not
             // sampled: the link becomes NaN and the error word counts it
-            if (k2 <= M::MAXV) pend |= 1u << m;
+            if (link_weight(V, beta, alpha[m], ial[m], Wd[m])) pend |= 1u << m;
             else nonfinite |= 1u << m;
-            T k, ik;
-            if (sizeof(T) == 4) {
-                ik = M::rsqrt_(k2);
-                k = k2 > T(0) ? k2 * ik : T(0);
-            } else {
-                k = M::sqrt_(k2);
-                ik = T(1) / k;
-            }
             sidx[m] = S.s;
-            alpha[m] = beta * k;
-            if (alpha[m] > T(0)) ial[m] = M::rcp_(alpha[m]);
-            if (k2 > T(0)) Wd[m] = Q<T>{V.a * ik, -V.b * ik, -V.c * ik, -V.d * ik};
         }
     }
 
@@ -289,22 +337,8 @@ __device__ __forceinline__ void heatbath_links(const LatDesc &d, int par, int fi
         const uint4 wd = philox10((uint32_t)s, sweep, c2, j, k0, k1);
         bool acc;
         T dl;
-        if (creutz) {
-            const T u1 = M::u(wd.x), u2 = M::u(wd.y);
-            if (al >= T(1e-20)) {
-                const T cf = pick(cfv, m);
-                dl = -M::log1p_(-(T(1) - u1) * cf) * ia;
-            } else {
-                dl = T(2) * (T(1) - u1);
-            }
-            acc = u2 * u2 <= dl * (T(2) - dl);
-        } else {
-            const T r1 = M::u(wd.x), r2 = M::u(wd.y), r3 = M::u(wd.z), r4 = M::u(wd.w);
-            const T cs = M::cos2pi(r2);
-            const T lam2 = -(M::lg(r1) + cs * cs * M::lg(r3)) * (ia * (T(0.5) * M::LN_LG));
-            acc = r4 * r4 <= T(1) - lam2;
-            dl = T(2) * lam2;
-        }
+        if (creutz) acc = creutz_try(wd, al, ia, pick(cfv, m), dl);
+        else acc = kp_try(wd, kp_logs<T>(wd), ia, dl);
         ++j;
         if (acc || j >= MAX_TRIES) {
             if (!acc) {
@@ -325,14 +359,7 @@ __device__ __forceinline__ void heatbath_links(const LatDesc &d, int par, int fi
         const int cb = first + m * (int)blockDim.x;
         if (cb < d.vh) {
             const uint4 wd = philox10((uint32_t)sidx[m], sweep, c2, 0xFFFFFFFFu, k0, k1);
-            const T u1 = M::u(wd.x), u2 = M::u(wd.y);
-            const T dl = delta[m];
-            const T cth = T(1) - T(2) * u1;
-            const T sth = T(2) * M::sqrt_(u1 * (T(1) - u1));
-            const T ra = M::sqrt_(dl * (T(2) - dl));
-            const T rs = ra * sth;
-            const Q<T> X{T(1) - dl, rs * M::cos2pi(u2), rs * M::sin2pi(u2), ra * cth};
-            const Q<T> Un = qnormalize(qmul(X, Wd[m]));
+            const Q<T> Un = compose_link(draw_direction<T>(wd), delta[m], Wd[m]);
             store(cb, sidx[m], Un, rec[m]);
             if (PLAQ)  // 1/2 Re Tr(U' V_low)
                 pq += (double)(Un.a * Vl[m].a - Un.b * Vl[m].b - Un.c * Vl[m].c - Un.d * Vl[m].d);
@@ -384,6 +411,103 @@ __global__ __launch_bounds__(256) void k_heatbath(KArgs a, int par) {
         tile = w.tile();
         tl = load_tile(a.tiles, tile);
         d = load_desc(a.desc + tl.x);
+    }
+}
+
+// The same substep where it is only a few wavefronts (up to SPLIT_SITES sites in
+// all): such a launch lasts as long as one wavefront's chain of dependent work,
+// so four lanes share a link and shorten it.  All four gather the staple (the
+// same addresses, one request); lane j of the four makes tries j, j + 4, ...,
+// and the first accepted one in order composes and stores the link, so links,
+// tries and branches are those of k_heatbath.  The first try and the direction
+// depend on the random words alone and are evaluated while the links are on
+// their way.  A workgroup takes 64 links of its tile, as many workgroups per
+// tile as it has wavefronts in k_heatbath.
+template <class T, int MU, bool PLAQ>
+__global__ __launch_bounds__(256) void k_heatbath_split(KArgs a, int par) {
+    using M = Mth<T>;
+    __shared__ double red[4];
+    __shared__ uint32_t redt[4];
+    // neighbouring parts of the work on the same XCD (workgroup b runs on XCD b % 8)
+    const int parts = a.tile_links >> 6, item = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    const int tile = item / parts, part = item - tile * parts;
+    const bool first_sub = a.advance && MU == 0 && par == 0;
+    const uint32_t sweep = uni((first_sub || !a.advance) ? a.st->next : a.st->sweep);
+    const uint32_t k0 = uni((unsigned)a.st->seed), k1 = uni((unsigned)(a.st->seed >> 32));
+    if (a.advance && blockIdx.x == 0 && threadIdx.x == 0) {
+        if (first_sub) a.st->sweep = sweep;
+        if (MU == 3 && par == 1) a.st->next = sweep + 1u;
+    }
+    double *plaq_part = a.plaq_part;
+    if (PLAQ && a.nslots > 0)
+        plaq_part += (long long)(((sweep - uni(a.st->run_base)) / (uint32_t)a.every) % (uint32_t)a.nslots) * 12 *
+                     a.ntiles;
+    if (tile >= a.ntiles) return;
+    const Tile tl = load_tile(a.tiles, tile);
+    const LatDesc d = load_desc(a.desc + tl.x);
+    const Blocks<T, 4> B = blocks<T, 4>(a.links, d.off, d.vh);
+    const uint32_t c2 = tag(d.lat_id, PURPOSE_HEATBATH, MU, par);
+    const T beta = (sizeof(T) == 4) ? (T)d.betaf : (T)d.beta;
+    const int tid = (int)threadIdx.x, lane = tid & 63, j0 = tid & 3;
+    const int cb = tl.y + 64 * part + (tid >> 2);
+    const bool valid = cb < d.vh;
+    const Site S = site_of(d, valid ? cb : 0, par);
+    Q<T> L[18];
+    gather<T, MU>(d, B, S, par, L);
+    __builtin_amdgcn_sched_barrier(0);
+    const uint4 wd = philox10((uint32_t)S.s, sweep, c2, (uint32_t)j0, k0, k1);
+    const T lg0 = a.sampler == 1 ? T(0) : kp_logs<T>(wd);
+    const Direction<T> dir = draw_direction<T>(philox10((uint32_t)S.s, sweep, c2, 0xFFFFFFFFu, k0, k1));
+    __builtin_amdgcn_sched_barrier(0);
+    Q<T> Vl{T(0), T(0), T(0), T(0)};
+    const Q<T> V = combine<T>(L, MU, PLAQ ? &Vl : nullptr);
+    T alpha, ial;
+    Q<T> Wd;
+    const bool finite = link_weight(V, beta, alpha, ial, Wd);
+    const bool creutz = (a.sampler == 1) || !(alpha >= T(2));
+    bool open = valid && finite, win = valid && !finite && j0 == 0;
+    T cf = T(0), dl = M::nan_();
+    uint32_t wtries = 0, base = 0;
+    if (win) atomicAdd(a.err, 1u);
+    if (__ballot(open && creutz)) {
+        if (open && alpha >= T(1e-20)) cf = -M::expm1_(T(-2) * alpha);
+    }
+    while (true) {
+        if (__ballot(open) == 0ull) break;
+        bool acc = false;
+        T t = T(0);
+        if (open) {
+            uint4 w = wd;
+            if (base) w = philox10((uint32_t)S.s, sweep, c2, base + (uint32_t)j0, k0, k1);
+            acc = creutz ? creutz_try(w, alpha, ial, cf, t) : kp_try(w, base ? kp_logs<T>(w) : lg0, ial, t);
+        }
+        const uint32_t g = (uint32_t)(__ballot(acc) >> (lane & ~3)) & 15u;  // the four tries of this link
+        const int hit = g ? __builtin_ctz(g) : 4;
+        wtries += (uint32_t)__popcll(__ballot(open && j0 <= hit));
+        if (open) {
+            if (g) {
+                win = j0 == hit;
+                if (win) dl = t;
+                open = false;
+            } else if ((base += 4) >= MAX_TRIES) {
+                win = j0 == 0;  // the link becomes NaN
+                if (win) atomicAdd(a.err, 1u);
+                open = false;
+            }
+        }
+    }
+    double pq = 0.0;
+    if (win) {
+        const Q<T> Un = compose_link(dir, dl, Wd);
+        sts_(B, MU, par, (uint32_t)cb, Un);
+        if (PLAQ) pq = (double)(Un.a * Vl.a - Un.b * Vl.b - Un.c * Vl.c - Un.d * Vl.d);
+    }
+    if (PLAQ) pq = wave_sum_f64(pq);
+    if (lane == 0) red[tid >> 6] = pq, redt[tid >> 6] = wtries;
+    __syncthreads();
+    if (tid == 0) {
+        if (PLAQ) plaq_part[(3 * (long long)tile + (MU - 1)) * 4 + part] = (red[0] + red[1]) + (red[2] + red[3]);
+        atomicAdd(&a.tries_part[tile], (unsigned long long)(redt[0] + redt[1] + redt[2] + redt[3]));
     }
 }
 
@@ -1560,6 +1684,24 @@ static void launch_hb_mu(const KArgs &a, int par, int nl, int block, int grid, h
     }
 }
 
+template <class T, int MU>
+static void launch_hb_split_mu(const KArgs &a, int par, hipStream_t s, bool plaq, const Ev &ev) {
+    const dim3 g((unsigned)((a.ntiles * (a.tile_links >> 6) + 7) / 8 * 8)), b(256);
+    if constexpr (MU >= 1) {
+        if (plaq) return launch_ev(k_heatbath_split<T, MU, true>, g, b, s, ev, a, par);
+    }
+    launch_ev(k_heatbath_split<T, MU, false>, g, b, s, ev, a, par);
+}
+
+template <class T> static void launch_hb_split(const KArgs &a, int mu, int par, hipStream_t s, bool plaq, const Ev &ev) {
+    switch (mu) {
+    case 0: launch_hb_split_mu<T, 0>(a, par, s, false, ev); break;
+    case 1: launch_hb_split_mu<T, 1>(a, par, s, plaq, ev); break;
+    case 2: launch_hb_split_mu<T, 2>(a, par, s, plaq, ev); break;
+    default: launch_hb_split_mu<T, 3>(a, par, s, plaq, ev); break;
+    }
+}
+
 template <class T>
 static void launch_hb_t(const KArgs &a, int mu, int par, int nl, int block, int grid, hipStream_t s,
                         bool trace, bool plaq, const Ev &ev) {
@@ -1573,6 +1715,11 @@ static void launch_hb_t(const KArgs &a, int mu, int par, int nl, int block, int 
 
 void launch_heatbath(const KArgs &a, bool f32, int mu, int par, int nl, int block, int grid, hipStream_t s,
                      bool trace, bool plaq, const Ev &ev) {
+    if (a.tile_links && !trace) {
+        if (f32) launch_hb_split<float>(a, mu, par, s, plaq, ev);
+        else launch_hb_split<double>(a, mu, par, s, plaq, ev);
+        return;
+    }
     if (f32) launch_hb_t<float>(a, mu, par, nl, block, grid, s, trace, plaq, ev);
     else launch_hb_t<double>(a, mu, par, nl, block, grid, s, trace, plaq, ev);
 }
