@@ -75,6 +75,7 @@ struct su2_ensemble_s {
     long long max_sites = 0;    // of the largest lattice
 
     int block = 256, grid = 0, remap = 1, nl = 1;
+    bool own_shape = true;  // the launch shape is the library's choice at creation
     std::vector<Tile> htiles, hstiles, hvtiles, hmtiles, hmtiles_z, hmtiles_b, hmtiles_b3;
     Tile *tiles = nullptr, *stiles = nullptr, *vtiles = nullptr, *mtiles = nullptr;
     Tile *mtiles_z = nullptr;  // the heat-bath tiles of each lattice in (z, t, y, x) order
@@ -285,11 +286,19 @@ KArgs kargs(su2_ensemble_s *E, int which = 0) {
 }
 
 // Heat-bath tile list of direction mu in the handle's tile mode: modes 0
-// and 1 lexicographic, with (z, t, y, x) order for mu = 3; mode 2 (z, t, y,
-// x) for every mu; mode 3 the XCD blocks.  All lists hold the same tiles.
+// and 1 lexicographic, with (z, t, y, x) order for mu = 3 where the links are
+// more than the eight XCDs' L2s hold (4 MiB each); mode 2 (z, t, y, x) for every
+// mu; mode 3 the XCD blocks.  All lists hold the same tiles.  Up to that size an
+// XCD that takes the same region in every substep finds links of the substeps
+// before in its L2, which is worth more than the shorter halo of the other order
+// for mu = 3: us per substep, mu = 3 in (z, t, y, x) and lexicographic order,
+// 16^3 x 32 4.85 4.50 (binary32), 8.4 8.2 (binary64), 20 x 18 x 22 x 24 5.7 5.2
+// and 10.9 10.5; beyond it 24^3 x 48 10.5 10.4 and 23.7 23.9, 32^4 14.5 14.9
+// and 33.5 34.6.
+constexpr size_t XCD_L2_BYTES = size_t(8) * 4 << 20;
 const Tile *hb_tiles(const su2_ensemble_s *E, int mu) {
     if (E->remap == 3) return mu == 3 ? E->mtiles_b3 : E->mtiles_b;
-    return (mu == 3 || E->remap == 2) ? E->mtiles_z : E->mtiles;
+    return E->remap == 2 || (mu == 3 && E->link_bytes > XCD_L2_BYTES) ? E->mtiles_z : E->mtiles;
 }
 
 void drop_run_graphs(su2_ensemble_s *E) {
@@ -535,6 +544,22 @@ void fill_desc(LatDesc &D, const int *d, int l, long long off, long long sites, 
     D.betaf = (float)beta;
 }
 
+// Tile mode of a new single lattice (an ensemble starts in mode 1, its XCD
+// shares being whole lattices or nearly).  us per heat-bath substep under block
+// 256, binary32 and binary64:
+// Mode 3 reads fewer halo links than mode 1 where its blocks divide evenly and
+// are large: modes 1 and 3, 32^4 14.4 14.0 and 33.5 31.3, 56^4 140 140 and
+// 337 292, 32^3 x 16 8.8 8.3 and 20.0 19.2; 24^3 x 32 the same in both, and
+// the uneven 28 x 26 x 18 x 32 7.5 7.8 and 18.2 18.4.
+// Where a (direction, parity) block's time slices lie whole multiples of 2 MiB
+// apart the eight XCDs' separate regions are slower than one region in round
+// robin (mode 0): modes 3 and 0, 64^4 235 223 and 507 478, 64^3 x 8 28.3 24.1
+// and 58.6 60.5; not with the few slices of 128^3 x 4, 121 124 and 263 283.
+int default_mode(const LatDesc &d) {
+    if ((long long)d.ns * 8 % (2 << 20) == 0 && d.n[3] >= 8) return 0;
+    return d.vh > 1 << 18 && d.n[2] % 8 == 0 && d.n[3] % 8 == 0 ? 3 : 1;
+}
+
 // ---- creation ----------------------------------------------------------------
 su2_status create_common(int n, const int *dims, const double *betas, su2_start start, uint64_t seed,
                          su2_prec prec, void *device_links, size_t device_bytes, su2_ensemble_s *E) {
@@ -558,6 +583,7 @@ su2_status create_common(int n, const int *dims, const double *betas, su2_start 
     }
     E->total_links = off;
     E->total_sites = sites;
+    if (n == 1) E->remap = default_mode(E->hdesc[0]);
     E->link_bytes = (size_t)off * link_size(E->f32);
     if (hipStreamCreateWithFlags(&E->own, hipStreamNonBlocking) != hipSuccess) return SU2_EDEVICE;
     if (device_links) {
@@ -987,6 +1013,7 @@ su2_status set_launch_common(su2_ensemble_s *E, int block, int grid, int remap, 
     if (remap < 0 || remap > 3) return SU2_EINVAL;
     if (nl != 1 && nl != 2 && nl != 4) return SU2_EINVAL;
     const bool reshape = block != E->block || nl != E->nl;
+    E->own_shape = false;
     E->grid = grid;
     E->remap = remap;
     if (reshape) {
@@ -1490,12 +1517,14 @@ su2_status su2_overrelax(su2_lattice E, int nsweeps) {
     CHK(enter(E));
     if (nsweeps < 0) return SU2_EINVAL;
     hipStream_t s = E->stream();
-    const KArgs a = kargs(E);
+    KArgs a = kargs(E);
     bool err_enqueued = false;
     const bool small = nsweeps > 0 && small_run_ok(E) && run_small(E, nsweeps, 1, 0, 1, &err_enqueued);
     for (int k = 0; k < nsweeps && !small; ++k)
         for (int mu = 0; mu < 4; ++mu)
             for (int par = 0; par < 2; ++par) {
+                // the heat bath's XCD blocks where its tiles are the same
+                if (E->nl == 1 && E->remap == 3) a.tiles = hb_tiles(E, mu);
                 Timed t(E, SU2_K_OVERRELAX, s, true);
                 su2::launch_overrelax(a, E->f32, mu, par, E->block, E->grid, s, t.ev());
                 t.done(s);
@@ -1523,7 +1552,11 @@ su2_status su2_ape_smear(su2_lattice E, double alpha, int nsteps) {
     for (int b = 0; b < 2; ++b)
         if (!E->sm[b]) CHK(dalloc(E, &E->sm[b], bytes));
     hipStream_t s = E->stream();
-    const KArgs a = kargs(E);
+    KArgs a = kargs(E);
+    // default_mode() is about the heat bath: a smearing step reads each link's
+    // neighbours in one time slice only and stays XCD by XCD (64^3 x 8 binary32
+    // 47 us a step against 61 in round robin)
+    if (E->own_shape) a.xcd_remap = 1;
     const void *src = E->links;
     int raw = 1, cur = 0;
     if (nsteps == 0) {  // smeared copy = raw spatial links
