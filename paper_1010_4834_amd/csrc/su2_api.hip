@@ -1563,7 +1563,10 @@ su2_status su2_ape_smear(su2_lattice E, double alpha, int nsteps) {
         su2::launch_ape(a, E->f32, E->links, 1, E->sm[0], 0.0, E->block, E->grid, s);
         cur = 0;
     }
-    for (int k = 0; k < nsteps; ++k) {
+    const LatDesc &d = E->hdesc[0];
+    const bool slices = nsteps > 1 && !E->timing && !std::getenv("SU2_NO_GRAPH") &&
+                        su2::launch_ape_slices(a, E->f32, d.ns, d.n[3], src, 1, E->sm[0], alpha, nsteps, s);
+    for (int k = 0; k < nsteps && !slices; ++k) {
         cur = k & 1;
         Timed t(E, SU2_K_APE, s);
         su2::launch_ape(a, E->f32, src, raw, E->sm[cur], alpha, E->block, E->grid, s);

@@ -103,6 +103,10 @@ void launch_clear_err(DevState *st, hipStream_t s);
 void launch_err_to_host(const DevState *st, unsigned *out, hipStream_t s);
 void launch_ape(const KArgs &a, bool f32, const void *src, int src_raw, void *dst, double alpha, int block,
                 int grid, hipStream_t s);
+// All steps in one launch, for time slices of up to this many sites.
+constexpr int ape_slice(bool f32) { return f32 ? 1024 : 512; }
+bool launch_ape_slices(const KArgs &a, bool f32, int ns, int nt, const void *src, int src_raw, void *dst, double alpha,
+                       int nsteps, hipStream_t s);
 // Wilson loops: prefix products of the temporal links (times 0 .. next - 1),
 // the spatial links and weights in that gauge, line by line, the loop traces of one pass of times (several passes beyond T = 16) and
 // their final sums, written to mapped host memory with the error word.

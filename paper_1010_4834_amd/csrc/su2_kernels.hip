@@ -1120,6 +1120,32 @@ __global__ void k_clear_err(DevState *st) { st->err = 0u; }
 
 __global__ void k_err_to_host(const DevState *st, unsigned *out) { *out = st->err; }
 
+// Quaternions in LDS: float4, or two double2 planes n apart, so that
+// consecutive lanes read consecutive 16-byte words.
+template <class T> struct LdsQ;
+template <> struct LdsQ<float> {
+    float4 *z;
+    __device__ __forceinline__ LdsQ(void *p, int) : z((float4 *)p) {}
+    __device__ __forceinline__ Q<float> ld(int i) const {
+        const float4 v = z[i];
+        return Q<float>{v.x, v.y, v.z, v.w};
+    }
+    __device__ __forceinline__ void st(int i, const Q<float> &q) const { z[i] = make_float4(q.a, q.b, q.c, q.d); }
+};
+template <> struct LdsQ<double> {
+    double2 *z;
+    int n;
+    __device__ __forceinline__ LdsQ(void *p, int n_) : z((double2 *)p), n(n_) {}
+    __device__ __forceinline__ Q<double> ld(int i) const {
+        const double2 l = z[i], h = z[i + n];
+        return Q<double>{l.x, l.y, h.x, h.y};
+    }
+    __device__ __forceinline__ void st(int i, const Q<double> &q) const {
+        z[i] = make_double2(q.a, q.b);
+        z[i + n] = make_double2(q.c, q.d);
+    }
+};
+
 // ---------------------------------------------------------------------------
 // APE smearing step (paper Sec. 2, APE equation) of the spatial links, all
 // at once from the previous step: U' = normalise[(1-alpha) U + (alpha/4)
@@ -1148,33 +1174,28 @@ __global__ void k_err_to_host(const DevState *st, unsigned *out) { *out = st->er
 // two Newton steps (each squares the relative error; after the second it is
 // below binary64 rounding).  A smeared sum is in general far from unit
 // norm, so there is no near-group shortcut.
-template <class T>
-__device__ __forceinline__ void ape_site(const LatDesc &d, const Blocks<T, 3> &Bs, const Blocks<T, 3> &Bd, int cb,
-                                         int par, T alpha) {
-    const Site S = site_of(d, cb, par);
-    const int op = par ^ 1;
-    int f[3], b[3];
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-        f[m] = step_fwd(d, S, m);
-        b[m] = step_bwd(d, S, m);
-    }
+//
+// ld(m, s, same): link m of site s, of the parity of the updated site or the
+// other; f, b: the site's periodic steps; store(m, q): new link m.
+template <class T, class LD, class ST>
+__device__ __forceinline__ void ape_links(int s, const int (&f)[3], const int (&b)[3], T alpha, const LD &ld,
+                                          const ST &store) {
     Q<T> O[3], K[3], sum[3];
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
-        O[m] = lds_(Bs, m, par, (uint32_t)cb);
-        K[m] = lds_(Bs, m, op, (uint32_t)(S.s + b[m]) >> 1);
+        O[m] = ld(m, s, true);
+        K[m] = ld(m, s + b[m], false);
         sum[m] = Q<T>{T(0), T(0), T(0), T(0)};
     }
 #pragma unroll
     for (int pl = 0; pl < 3; ++pl) {
         const int m = pl == 2 ? 1 : 0, n = pl == 0 ? 1 : 2;
-        const Q<T> Fmn = lds_(Bs, m, op, (uint32_t)(S.s + f[n]) >> 1);
-        const Q<T> Fnm = lds_(Bs, n, op, (uint32_t)(S.s + f[m]) >> 1);
-        const Q<T> Mmn = lds_(Bs, m, op, (uint32_t)(S.s + b[n]) >> 1);
-        const Q<T> Mnm = lds_(Bs, n, op, (uint32_t)(S.s + b[m]) >> 1);
-        const Q<T> Dnm = lds_(Bs, n, par, (uint32_t)(S.s + f[m] + b[n]) >> 1);
-        const Q<T> Dmn = lds_(Bs, m, par, (uint32_t)(S.s + f[n] + b[m]) >> 1);
+        const Q<T> Fmn = ld(m, s + f[n], false);
+        const Q<T> Fnm = ld(n, s + f[m], false);
+        const Q<T> Mmn = ld(m, s + b[n], false);
+        const Q<T> Mnm = ld(n, s + b[m], false);
+        const Q<T> Dnm = ld(n, s + f[m] + b[n], true);
+        const Q<T> Dmn = ld(m, s + f[n] + b[m], true);
         qmul_acc(sum[m], qmul(O[n], Fmn), qdag(Fnm));
         qmul_acc(sum[m], qmul(qdag(K[n]), Mmn), Dnm);
         qmul_acc(sum[n], qmul(O[m], Fnm), qdag(Fmn));
@@ -1195,7 +1216,7 @@ __device__ __forceinline__ void ape_site(const LatDesc &d, const Blocks<T, 3> &B
             y = y * (1.5 - h * y * y);
             un = Q<T>{(T)(wa * y), (T)(wb * y), (T)(wc * y), (T)(wd * y)};
         }
-        sts_(Bd, mu, par, (uint32_t)cb, un);
+        store(mu, un);
     }
 }
 
@@ -1209,8 +1230,66 @@ __global__ __launch_bounds__(256) void k_ape(KArgs a, const void *src, int src_r
         const Blocks<T, 3> Bd = blocks<T, 3>(dst, d.soff, d.vh);
         const int cb = tl.y + (int)threadIdx.x;
         if (cb >= d.vh) return;
-        ape_site<T>(d, Bs, Bd, cb, par, alpha);
+        const Site S = site_of(d, cb, par);
+        int f[3], b[3];
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            f[m] = step_fwd(d, S, m);
+            b[m] = step_bwd(d, S, m);
+        }
+        ape_links<T>(S.s, f, b, alpha,
+                     [&](int m, int s, bool same) { return lds_(Bs, m, same ? par : par ^ 1, (uint32_t)s >> 1); },
+                     [&](int m, const Q<T> &q) { sts_(Bd, m, par, (uint32_t)cb, q); });
     });
+}
+
+// All steps of a lattice whose time slices have up to ape_slice() sites, one
+// workgroup per slice: a step reaches no other slice, so the slice stays in LDS
+// and one launch takes the place of one per step.  A thread updates one site;
+// the new links wait in registers for the barrier behind the last read of the
+// step.  The arithmetic is ape_links, the smeared links are bit for bit those of
+// k_ape.  us per step here and as launches: binary32 1.1 and 4.8 (4^3), 1.7 and
+// 4.5 (8^3), 2.8 and 4.5 (1024 sites); binary64 2.5 and 5.5 (8^3, the largest
+// whose registers hold one site per thread in a single workgroup).
+template <class T>
+__global__ __launch_bounds__(ape_slice(sizeof(T) == 4)) void k_ape_slices(KArgs a, const void *src, int src_raw,
+                                                                          void *dst, T alpha, int nsteps) {
+    extern __shared__ double4 ape_lds[];
+    const int t = (int)blockIdx.x;
+    const LatDesc d = load_desc(a.desc);
+    const Blocks<T, 3> Bs = blocks<T, 3>(src, src_raw ? d.off : d.soff, d.vh);
+    const Blocks<T, 3> Bd = blocks<T, 3>(dst, d.soff, d.vh);
+    const LdsQ<T> Z(ape_lds, 3 * d.ns);
+    const int xs = min((int)threadIdx.x, d.ns - 1);
+    const bool on = (int)threadIdx.x < d.ns;
+    const uint32_t cb = (uint32_t)(xs + t * d.ns) >> 1;
+    Site S;
+    int r, f[3], b[3];
+    udiv(xs, d.n[0], d.inv_nx, r, S.c[0]);
+    udiv(r, d.n[1], d.inv_ny, S.c[2], S.c[1]);
+    S.c[3] = t;
+    const int par = (S.c[0] + S.c[1] + S.c[2] + t) & 1;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        f[m] = step_fwd(d, S, m);
+        b[m] = step_bwd(d, S, m);
+        if (on) Z.st(m * d.ns + xs, lds_(Bs, m, par, cb));
+    }
+    __syncthreads();
+    for (int k = 0; k < nsteps; ++k) {
+        Q<T> un[3];
+        if (on)
+            ape_links<T>(xs, f, b, alpha, [&](int m, int s, bool) { return Z.ld(m * d.ns + s); },
+                         [&](int m, const Q<T> &q) { un[m] = q; });
+        __syncthreads();
+        if (on)
+#pragma unroll
+            for (int m = 0; m < 3; ++m) Z.st(m * d.ns + xs, un[m]);
+        __syncthreads();
+    }
+    if (on)
+#pragma unroll
+        for (int m = 0; m < 3; ++m) sts_(Bd, m, par, cb, Z.ld(m * d.ns + xs));
 }
 
 // ---------------------------------------------------------------------------
@@ -1379,32 +1458,6 @@ __global__ __launch_bounds__(512) void k_wlinks(KArgs a, const void *sp, int sp_
         __syncthreads();
     }
 }
-
-// Quaternions in LDS: float4, or two double2 planes n apart, so that
-// consecutive lanes read consecutive 16-byte words.
-template <class T> struct LdsQ;
-template <> struct LdsQ<float> {
-    float4 *z;
-    __device__ __forceinline__ LdsQ(void *p, int) : z((float4 *)p) {}
-    __device__ __forceinline__ Q<float> ld(int i) const {
-        const float4 v = z[i];
-        return Q<float>{v.x, v.y, v.z, v.w};
-    }
-    __device__ __forceinline__ void st(int i, const Q<float> &q) const { z[i] = make_float4(q.a, q.b, q.c, q.d); }
-};
-template <> struct LdsQ<double> {
-    double2 *z;
-    int n;
-    __device__ __forceinline__ LdsQ(void *p, int n_) : z((double2 *)p), n(n_) {}
-    __device__ __forceinline__ Q<double> ld(int i) const {
-        const double2 l = z[i], h = z[i + n];
-        return Q<double>{l.x, l.y, h.x, h.y};
-    }
-    __device__ __forceinline__ void st(int i, const Q<double> &q) const {
-        z[i] = make_double2(q.a, q.b);
-        z[i + n] = make_double2(q.c, q.d);
-    }
-};
 
 // s + 1/2 Tr(x y^dag), the trace in the precision of its operands, the sum in
 // binary64
@@ -1849,6 +1902,23 @@ void launch_ape(const KArgs &a, bool f32, const void *src, int src_raw, void *ds
     const dim3 g = grid_of(w, grid);
     if (f32) hipLaunchKernelGGL((k_ape<float>), g, dim3(block), 0, s, a, src, src_raw, dst, (float)alpha);
     else hipLaunchKernelGGL((k_ape<double>), g, dim3(block), 0, s, a, src, src_raw, dst, alpha);
+}
+
+// false: the slices are too large, or their LDS not to be had
+bool launch_ape_slices(const KArgs &a, bool f32, int ns, int nt, const void *src, int src_raw, void *dst, double alpha,
+                       int nsteps, hipStream_t s) {
+    if (ns > ape_slice(f32)) return false;
+    const size_t lds = (size_t)3 * ns * (f32 ? 16 : 32);
+    const void *k = f32 ? (const void *)k_ape_slices<float> : (const void *)k_ape_slices<double>;
+    if (lds > (48 << 10) &&
+        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const dim3 g((unsigned)nt), b((unsigned)((ns + 63) / 64 * 64));
+    if (f32) hipLaunchKernelGGL((k_ape_slices<float>), g, b, lds, s, a, src, src_raw, dst, (float)alpha, nsteps);
+    else hipLaunchKernelGGL((k_ape_slices<double>), g, b, lds, s, a, src, src_raw, dst, alpha, nsteps);
+    return true;
 }
 
 void launch_wgauge(const KArgs &a, bool f32, int ns, int next, void *P, hipStream_t s) {
