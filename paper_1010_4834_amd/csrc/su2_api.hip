@@ -782,15 +782,18 @@ su2_status capture_run(su2_ensemble_s *E, int meas, int every, int nsweeps, hipG
 }
 
 // Whether a call's sweeps run as one workgroup per lattice (k_small_run): no
-// lattice above SMALL_SITES and every workgroup resident at once -- at most
+// lattice above small_sites() and every workgroup resident at once -- at most
 // eight wavefronts per CU (what two per SIMD overlap) and the lattices of a CU
 // within its LDS.  Where lattices would queue for CUs the batched substeps
 // keep the whole chip busy instead.  Not while tries are recorded per link or
 // kernels timed one by one, nor under SU2_NO_GRAPH.
-bool small_run_ok(const su2_ensemble_s *E) {
+bool small_run_ok(const su2_ensemble_s *E, bool over) {
     if (E->trace || E->timing || E->n > 8 * 256 || std::getenv("SU2_NO_GRAPH")) return false;
-    const int per_cu = (E->n + 255) / 256, waves = (E->max_sites / 2 + 63) / 64;
-    return E->max_sites <= su2::SMALL_SITES && per_cu * waves <= 8 &&
+    const bool creutz = E->sampler == SU2_CREUTZ;
+    if (E->max_sites > su2::small_sites(E->f32, creutz, over)) return false;
+    const int lanes = su2::small_four(creutz, over) ? 4 : 1;
+    const int per_cu = (E->n + 255) / 256, waves = ((int)E->max_sites / 2 * lanes + 63) / 64;
+    return per_cu * waves <= 8 &&
            per_cu * (su2::small_lds_bytes(E->f32, (int)E->max_sites) + 1024) <= (size_t)160 << 10;
 }
 
@@ -828,7 +831,7 @@ su2_status run_sweeps(su2_ensemble_s *E, int nsweeps, int meas, int every, bool 
                       bool upload = false) {
     const int nm = meas ? nsweeps / every : 0;
     if (err_enqueued) *err_enqueued = false;
-    if (small_run_ok(E) && run_small(E, nsweeps, 0, meas, every, err_enqueued)) {
+    if (small_run_ok(E, false) && run_small(E, nsweeps, 0, meas, every, err_enqueued)) {
         HIPCHK(hipGetLastError());
         return SU2_OK;
     }
@@ -1519,7 +1522,7 @@ su2_status su2_overrelax(su2_lattice E, int nsweeps) {
     hipStream_t s = E->stream();
     KArgs a = kargs(E);
     bool err_enqueued = false;
-    const bool small = nsweeps > 0 && small_run_ok(E) && run_small(E, nsweeps, 1, 0, 1, &err_enqueued);
+    const bool small = nsweeps > 0 && small_run_ok(E, true) && run_small(E, nsweeps, 1, 0, 1, &err_enqueued);
     for (int k = 0; k < nsweeps && !small; ++k)
         for (int mu = 0; mu < 4; ++mu)
             for (int par = 0; par < 2; ++par) {

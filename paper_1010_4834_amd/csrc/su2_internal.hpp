@@ -36,9 +36,22 @@ constexpr long long split_sites(bool f32, bool creutz) {
 }
 
 // A call's sweeps of small lattices, one workgroup per lattice with its links
-// in LDS.
-constexpr int SMALL_SITES = 1024;  // largest lattice
-constexpr int SMALL_BLOCK = 512;   // threads at most: one link per lane
+// in LDS (k_small_run), and whether four lanes share a link there.
+// us per substep here and as replayed launches: Kennedy-Pendleton binary32 2.1
+// and 3.3 (256 sites), 2.6 and 3.7 (1024); binary64 4.3 and 5.6 (256), 4.9 and
+// 5.9 (512), 6.4 and 6.0 (768); over-relaxation binary32 1.3 and 2.4, 1.6 and
+// 2.8, binary64 1.6 and 2.7, 2.3 and 3.6 (256, 1024).  Creutz, whose tries are
+// many, with four lanes per link 4.0 and 5.3 (binary32, 256), 6.0 and 6.9
+// (binary64, 256), with one 7.6 and 12.8; more links than threads for four
+// lanes each stay with the launches.  Four lanes gain nothing for
+// Kennedy-Pendleton (4.6 in binary64 at 256 sites).
+constexpr int SMALL_SITES = 1024;  // largest lattice of any kind
+constexpr int SMALL_BLOCK = 512;   // threads at most
+constexpr int SMALL_FOUR = SMALL_BLOCK / 2;  // sites whose links have four lanes each
+constexpr bool small_four(bool creutz, bool over) { return creutz && !over; }
+constexpr int small_sites(bool f32, bool creutz, bool over) {
+    return over ? SMALL_SITES : creutz ? SMALL_FOUR : f32 ? SMALL_SITES : SMALL_SITES / 2;
+}
 struct SmallRun {
     unsigned long long seed;
     unsigned int sweep0;   // Philox sweep word of the first sweep

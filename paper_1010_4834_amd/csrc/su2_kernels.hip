@@ -414,61 +414,37 @@ __global__ __launch_bounds__(256) void k_heatbath(KArgs a, int par) {
     }
 }
 
-// The same substep where it is only a few wavefronts (up to SPLIT_SITES sites in
-// all): such a launch lasts as long as one wavefront's chain of dependent work,
-// so four lanes share a link and shorten it.  All four gather the staple (the
-// same addresses, one request); lane j of the four makes tries j, j + 4, ...,
-// and the first accepted one in order composes and stores the link, so links,
-// tries and branches are those of k_heatbath.  The first try and the direction
-// depend on the random words alone and are evaluated while the links are on
-// their way.  A workgroup takes 64 links of its tile, as many workgroups per
-// tile as it has wavefronts in k_heatbath.
-template <class T, int MU, bool PLAQ>
-__global__ __launch_bounds__(256) void k_heatbath_split(KArgs a, int par) {
+// A link updated by four lanes (those of equal threadIdx.x / 4), for substeps of
+// a few wavefronts, which last as long as one wavefront's chain of dependent
+// work.  All four gather the staple (the same addresses, one request); lane j of
+// the four makes tries j, j + 4, ..., and the first accepted one in order
+// composes and stores the link, so links, tries and branches are those of
+// heatbath_links.  The first try and the direction depend on the random words
+// alone and are evaluated while the links are on their way.  All lanes of a
+// wavefront call it; links beyond the lattice are not valid.
+template <class T, bool PLAQ, class GATHER, class STORE>
+__device__ __forceinline__ void heatbath_link4(const Site &S, bool valid, int mu, T beta, int sampler, uint32_t sweep,
+                                               uint32_t c2, uint32_t k0, uint32_t k1, unsigned *err, uint32_t &wtries,
+                                               double &pq, const GATHER &gather_at, const STORE &store) {
     using M = Mth<T>;
-    __shared__ double red[4];
-    __shared__ uint32_t redt[4];
-    // neighbouring parts of the work on the same XCD (workgroup b runs on XCD b % 8)
-    const int parts = a.tile_links >> 6, item = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
-    const int tile = item / parts, part = item - tile * parts;
-    const bool first_sub = a.advance && MU == 0 && par == 0;
-    const uint32_t sweep = uni((first_sub || !a.advance) ? a.st->next : a.st->sweep);
-    const uint32_t k0 = uni((unsigned)a.st->seed), k1 = uni((unsigned)(a.st->seed >> 32));
-    if (a.advance && blockIdx.x == 0 && threadIdx.x == 0) {
-        if (first_sub) a.st->sweep = sweep;
-        if (MU == 3 && par == 1) a.st->next = sweep + 1u;
-    }
-    double *plaq_part = a.plaq_part;
-    if (PLAQ && a.nslots > 0)
-        plaq_part += (long long)(((sweep - uni(a.st->run_base)) / (uint32_t)a.every) % (uint32_t)a.nslots) * 12 *
-                     a.ntiles;
-    if (tile >= a.ntiles) return;
-    const Tile tl = load_tile(a.tiles, tile);
-    const LatDesc d = load_desc(a.desc + tl.x);
-    const Blocks<T, 4> B = blocks<T, 4>(a.links, d.off, d.vh);
-    const uint32_t c2 = tag(d.lat_id, PURPOSE_HEATBATH, MU, par);
-    const T beta = (sizeof(T) == 4) ? (T)d.betaf : (T)d.beta;
-    const int tid = (int)threadIdx.x, lane = tid & 63, j0 = tid & 3;
-    const int cb = tl.y + 64 * part + (tid >> 2);
-    const bool valid = cb < d.vh;
-    const Site S = site_of(d, valid ? cb : 0, par);
+    const int lane = (int)threadIdx.x & 63, j0 = lane & 3;
     Q<T> L[18];
-    gather<T, MU>(d, B, S, par, L);
+    gather_at(L);
     __builtin_amdgcn_sched_barrier(0);
     const uint4 wd = philox10((uint32_t)S.s, sweep, c2, (uint32_t)j0, k0, k1);
-    const T lg0 = a.sampler == 1 ? T(0) : kp_logs<T>(wd);
+    const T lg0 = sampler == 1 ? T(0) : kp_logs<T>(wd);
     const Direction<T> dir = draw_direction<T>(philox10((uint32_t)S.s, sweep, c2, 0xFFFFFFFFu, k0, k1));
     __builtin_amdgcn_sched_barrier(0);
     Q<T> Vl{T(0), T(0), T(0), T(0)};
-    const Q<T> V = combine<T>(L, MU, PLAQ ? &Vl : nullptr);
+    const Q<T> V = combine<T>(L, mu, PLAQ ? &Vl : nullptr);
     T alpha, ial;
     Q<T> Wd;
     const bool finite = link_weight(V, beta, alpha, ial, Wd);
-    const bool creutz = (a.sampler == 1) || !(alpha >= T(2));
+    const bool creutz = (sampler == 1) || !(alpha >= T(2));
     bool open = valid && finite, win = valid && !finite && j0 == 0;
     T cf = T(0), dl = M::nan_();
-    uint32_t wtries = 0, base = 0;
-    if (win) atomicAdd(a.err, 1u);
+    uint32_t base = 0;
+    if (win) atomicAdd(err, 1u);
     if (__ballot(open && creutz)) {
         if (open && alpha >= T(1e-20)) cf = -M::expm1_(T(-2) * alpha);
     }
@@ -491,17 +467,55 @@ __global__ __launch_bounds__(256) void k_heatbath_split(KArgs a, int par) {
                 open = false;
             } else if ((base += 4) >= MAX_TRIES) {
                 win = j0 == 0;  // the link becomes NaN
-                if (win) atomicAdd(a.err, 1u);
+                if (win) atomicAdd(err, 1u);
                 open = false;
             }
         }
     }
-    double pq = 0.0;
     if (win) {
         const Q<T> Un = compose_link(dir, dl, Wd);
-        sts_(B, MU, par, (uint32_t)cb, Un);
-        if (PLAQ) pq = (double)(Un.a * Vl.a - Un.b * Vl.b - Un.c * Vl.c - Un.d * Vl.d);
+        store(Un);
+        if (PLAQ) pq += (double)(Un.a * Vl.a - Un.b * Vl.b - Un.c * Vl.c - Un.d * Vl.d);
     }
+}
+
+// The substep of up to split_sites() sites in all, four lanes per link.  A
+// workgroup takes 64 links of its tile, as many workgroups per tile as it has
+// wavefronts in k_heatbath.
+template <class T, int MU, bool PLAQ>
+__global__ __launch_bounds__(256) void k_heatbath_split(KArgs a, int par) {
+    __shared__ double red[4];
+    __shared__ uint32_t redt[4];
+    // neighbouring parts of the work on the same XCD (workgroup b runs on XCD b % 8)
+    const int parts = a.tile_links >> 6, item = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    const int tile = item / parts, part = item - tile * parts;
+    const bool first_sub = a.advance && MU == 0 && par == 0;
+    const uint32_t sweep = uni((first_sub || !a.advance) ? a.st->next : a.st->sweep);
+    const uint32_t k0 = uni((unsigned)a.st->seed), k1 = uni((unsigned)(a.st->seed >> 32));
+    if (a.advance && blockIdx.x == 0 && threadIdx.x == 0) {
+        if (first_sub) a.st->sweep = sweep;
+        if (MU == 3 && par == 1) a.st->next = sweep + 1u;
+    }
+    double *plaq_part = a.plaq_part;
+    if (PLAQ && a.nslots > 0)
+        plaq_part += (long long)(((sweep - uni(a.st->run_base)) / (uint32_t)a.every) % (uint32_t)a.nslots) * 12 *
+                     a.ntiles;
+    if (tile >= a.ntiles) return;
+    const Tile tl = load_tile(a.tiles, tile);
+    const LatDesc d = load_desc(a.desc + tl.x);
+    const Blocks<T, 4> B = blocks<T, 4>(a.links, d.off, d.vh);
+    const uint32_t c2 = tag(d.lat_id, PURPOSE_HEATBATH, MU, par);
+    const T beta = (sizeof(T) == 4) ? (T)d.betaf : (T)d.beta;
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int cb = tl.y + 64 * part + (tid >> 2);
+    const bool valid = cb < d.vh;
+    const Site S = site_of(d, valid ? cb : 0, par);
+    uint32_t wtries = 0;
+    double pq = 0.0;
+    heatbath_link4<T, PLAQ>(
+        S, valid, MU, beta, a.sampler, sweep, c2, k0, k1, a.err, wtries, pq,
+        [&](Q<T>(&L)[18]) { gather<T, MU>(d, B, S, par, L); },
+        [&](const Q<T> &U) { sts_(B, MU, par, (uint32_t)cb, U); });
     if (PLAQ) pq = wave_sum_f64(pq);
     if (lane == 0) red[tid >> 6] = pq, redt[tid >> 6] = wtries;
     __syncthreads();
@@ -554,10 +568,6 @@ __global__ __launch_bounds__(256) void k_overrelax(KArgs a, int par) {
 // between substeps, and one launch advances every lattice of the ensemble.
 // The update is heatbath_links / the formula of k_overrelax on the same
 // staples, so the links are bit for bit those of the substep kernels.
-// At 1024 sites (8 wavefronts a substep) one workgroup is still faster than
-// the launches in both precisions, by a tenth in binary64 (figures at
-// k_small_run); beyond it two wavefronts share a SIMD and lattices are faster
-// spread over the chip.
 
 // Links of one lattice in LDS, in the order of the link buffer.
 template <class T> struct LdsBlocks;
@@ -586,11 +596,11 @@ template <> struct LdsBlocks<double> {
     }
 };
 
-// staple() with the links in LDS and the direction a run-time (uniform) value
+// gather() and staple() with the links in LDS and the direction a run-time
+// (uniform) value
 template <class T>
-__device__ __forceinline__ Q<T> staple_lds(const LatDesc &d, const LdsBlocks<T> &B, const Site &S, int par, int mu,
-                                           Q<T> *Vlow) {
-    Q<T> L[18];
+__device__ __forceinline__ void gather_lds(const LatDesc &d, const LdsBlocks<T> &B, const Site &S, int par, int mu,
+                                           Q<T> (&L)[18]) {
     const int op = par ^ 1;
     const int s_mu = S.s + step_fwd_rt(d, S, mu);
 #pragma unroll
@@ -604,6 +614,12 @@ __device__ __forceinline__ Q<T> staple_lds(const LatDesc &d, const LdsBlocks<T> 
         L[q + 4] = B.ld(mu, op, (S.s + bn) >> 1);
         L[q + 5] = B.ld(nu, op, (S.s + bn) >> 1);
     }
+}
+template <class T>
+__device__ __forceinline__ Q<T> staple_lds(const LatDesc &d, const LdsBlocks<T> &B, const Site &S, int par, int mu,
+                                           Q<T> *Vlow) {
+    Q<T> L[18];
+    gather_lds(d, B, S, par, mu, L);
     return combine<T>(L, mu, Vlow);
 }
 
@@ -622,12 +638,10 @@ __device__ __forceinline__ void small_copy(const LatDesc &d, char *links, float4
 // over-relaxation) of lattice blockIdx.x.  Measured sweeps write the mean
 // plaquette, summed as in k_heatbath, and the Polyakov loop to
 // outp / outl[l * nm + measurement].
-// us per substep here and as launches: heat bath 2.1 and 3.8 (4^4 binary32),
-// 4.3 and 6.0 (4^4 binary64), 2.6 and 4.3 (1024 sites, binary32), 6.6 and 7.3
-// (1024 sites, binary64); over-relaxation 1.3 and 3.4 (4^4 binary32), 2.2 and
-// 4.1 (1024 sites, binary64).  The time is the instructions of one wavefront's
-// update, issued alone on its SIMD.
-template <class T>
+// FOUR: four lanes per link (heat bath; the workgroup holds them all).  Figures
+// at small_sites().  The time is the instructions of one wavefront's update,
+// issued alone on its SIMD.
+template <class T, bool FOUR>
 __global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, double *outp, double *outl,
                                                            unsigned *errp) {
     extern __shared__ double4 small_lds[];
@@ -646,12 +660,25 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, 
         for (int sub = 0; sub < 8; ++sub) {
             const int mu = sub >> 1, par = sub & 1;
             if (!r.over) {
-                const uint32_t c2 = tag(d.lat_id, PURPOSE_HEATBATH, mu, par);
-                for (int first = tid; first - lane < d.vh; first += nb) {
+                const uint32_t c2 = tag(d.lat_id, PURPOSE_HEATBATH, mu, par), sweep = r.sweep0 + (uint32_t)sw;
+                if (FOUR) {
+                    const int cb = tid >> 2;
+                    const bool valid = cb < d.vh;
+                    const Site S = site_of(d, valid ? cb : 0, par);
+                    uint32_t wt = 0;
+                    double pw = 0.0;
+                    heatbath_link4<T, true>(
+                        S, valid, mu, beta, a.sampler, sweep, c2, k0, k1, a.err, wt, pw,
+                        [&](Q<T>(&L)[18]) { gather_lds(d, B, S, par, mu, L); },
+                        [&](const Q<T> &U) { B.st(mu, par, cb, U); });
+                    tries += wt;
+                    if (par) pq += pw;
+                }
+                for (int first = tid; !FOUR && first - lane < d.vh; first += nb) {
                     uint32_t wt = 0;
                     double pw = 0.0;
                     heatbath_links<T, 1, true>(
-                        d, par, first, beta, a.sampler, r.sweep0 + (uint32_t)sw, c2, k0, k1, a.err, wt, pw,
+                        d, par, first, beta, a.sampler, sweep, c2, k0, k1, a.err, wt, pw,
                         [&](const Site &S, Q<T> *Vlow) { return staple_lds<T>(d, B, S, par, mu, Vlow); },
                         [&](int cb, int, const Q<T> &U, uint32_t) { B.st(mu, par, cb, U); });
                     tries += wt;
@@ -1820,16 +1847,16 @@ size_t small_lds_bytes(bool f32, int sites) { return (size_t)sites * (f32 ? 64 :
 bool launch_small_run(const KArgs &a, bool f32, int nlat, int sites, const SmallRun &r, double *outp, double *outl,
                       unsigned *errp, hipStream_t s) {
     const size_t lds = small_lds_bytes(f32, sites);
-    const int block = std::min(SMALL_BLOCK, std::max(64, (sites / 2 + 63) / 64 * 64));
-    const void *k = f32 ? (const void *)k_small_run<float> : (const void *)k_small_run<double>;
+    const bool four = small_four(a.sampler == 1, r.over != 0);
+    const int block = std::min(SMALL_BLOCK, ((four ? 4 : 1) * sites / 2 + 63) / 64 * 64);
+    const auto k = f32 ? (four ? k_small_run<float, true> : k_small_run<float, false>)
+                       : (four ? k_small_run<double, true> : k_small_run<double, false>);
     if (lds > (48 << 10) &&
-        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+        hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    const dim3 g((unsigned)nlat), b((unsigned)block);
-    if (f32) hipLaunchKernelGGL((k_small_run<float>), g, b, lds, s, a, r, outp, outl, errp);
-    else hipLaunchKernelGGL((k_small_run<double>), g, b, lds, s, a, r, outp, outl, errp);
+    hipLaunchKernelGGL(k, dim3((unsigned)nlat), dim3((unsigned)block), lds, s, a, r, outp, outl, errp);
     return true;
 }
 

@@ -31,7 +31,8 @@ class Direct:
 SHAPES = [
     [(2, 2, 2, 2)],                              # 8 links a substep
     [(4, 4, 4, 4)],
-    [(8, 4, 4, 8)],                              # the largest: 1024 sites
+    [(8, 4, 4, 8)],                              # the largest of binary32: 1024 sites
+    [(8, 4, 4, 4)],                              # the largest of binary64: 512 sites
     [(2, 6, 10, 4)],                             # 240 links: a partial wavefront
     [(4, 4, 4, 6), (2, 2, 2, 2), (6, 4, 4, 10)],  # uneven, one launch
     [(4, 4, 4, 4)] * 300,                        # two workgroups on a compute unit
@@ -63,7 +64,7 @@ def test_small_runs_match_substeps(su2, dims, prec):
 
 
 @pytest.mark.parametrize("prec", ["F32", "F64"])
-@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (4, 4, 4, 6), (8, 4, 4, 8)])
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (2, 6, 6, 2), (4, 4, 4, 4), (4, 4, 4, 6), (8, 4, 4, 8)])
 def test_small_updates_match_substeps(su2, dims, prec):
     """Heat bath (both samplers) mixed with over-relaxation on a lattice of
     given links."""
