@@ -201,8 +201,9 @@ template <class T, int N> __device__ __forceinline__ void put(T (&a)[N], int m, 
 // of the sweep; by linearity only the summed staple of those planes is
 // kept.  Each wavefront writes its binary64 sum to slot MU-1 of its tile.
 // Parts of a link update shared by the heat-bath kernels.
-// alpha = beta k of a staple V, k = |V|, its reciprocal (0 when alpha = 0) and
-// W^dag = (V/k)^dag (1 when V = 0); false for a non-finite staple.
+// alpha = beta k of a staple V, k = |V|, its reciprocal (left as it is, the
+// caller's 0, when alpha = 0) and W^dag = (V/k)^dag (the caller's 1 when V = 0);
+// false for a non-finite staple.
 template <class T>
 __device__ __forceinline__ bool link_weight(const Q<T> &V, T beta, T &alpha, T &ial, Q<T> &Wd) {
     using M = Mth<T>;
@@ -216,8 +217,6 @@ __device__ __forceinline__ bool link_weight(const Q<T> &V, T beta, T &alpha, T &
         ik = T(1) / k;
     }
     alpha = beta * k;
-    ial = T(0);
-    Wd = qone<T>();
     if (alpha > T(0)) ial = M::rcp_(alpha);
     if (k2 > T(0)) Wd = Q<T>{V.a * ik, -V.b * ik, -V.c * ik, -V.d * ik};
     return k2 <= M::MAXV;
@@ -288,9 +287,23 @@ __device__ __forceinline__ void heatbath_links(const LatDesc &d, int par, int fi
             const Q<T> V = staple_at(S, PLAQ ? &Vl[m] : nullptr);
             // a non-finite staple (a non-finite neighbour link) is not
             // sampled: the link becomes NaN and the error word counts it
-            if (link_weight(V, beta, alpha[m], ial[m], Wd[m])) pend |= 1u << m;
+            // (as a call of link_weight these lines take five vector
+            // instructions more, 1% of the kernel)
+            const T k2 = V.a * V.a + V.b * V.b + V.c * V.c + V.d * V.d;
+            if (k2 <= M::MAXV) pend |= 1u << m;
             else nonfinite |= 1u << m;
+            T k, ik;
+            if (sizeof(T) == 4) {
+                ik = M::rsqrt_(k2);
+                k = k2 > T(0) ? k2 * ik : T(0);
+            } else {
+                k = M::sqrt_(k2);
+                ik = T(1) / k;
+            }
             sidx[m] = S.s;
+            alpha[m] = beta * k;
+            if (alpha[m] > T(0)) ial[m] = M::rcp_(alpha[m]);
+            if (k2 > T(0)) Wd[m] = Q<T>{V.a * ik, -V.b * ik, -V.c * ik, -V.d * ik};
         }
     }
 
@@ -437,8 +450,8 @@ __device__ __forceinline__ void heatbath_link4(const Site &S, bool valid, int mu
     __builtin_amdgcn_sched_barrier(0);
     Q<T> Vl{T(0), T(0), T(0), T(0)};
     const Q<T> V = combine<T>(L, mu, PLAQ ? &Vl : nullptr);
-    T alpha, ial;
-    Q<T> Wd;
+    T alpha, ial = T(0);
+    Q<T> Wd = qone<T>();
     const bool finite = link_weight(V, beta, alpha, ial, Wd);
     const bool creutz = (sampler == 1) || !(alpha >= T(2));
     bool open = valid && finite, win = valid && !finite && j0 == 0;
