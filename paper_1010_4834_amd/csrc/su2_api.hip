@@ -900,12 +900,15 @@ su2_status set_seed(su2_ensemble_s *E, uint64_t seed) {
 su2_status measure_plaquette(su2_ensemble_s *E, int l, double *avg, double *sp, double *tp) {
     hipStream_t s = E->stream();
     const KArgs a = kargs(E);
-    {
+    const bool one = E->n == 1 && E->ntiles <= su2::ONE_TILES && !E->timing;
+    if (one) {
+        su2::launch_plaquette_one(a, E->f32, E->block, E->dres, E->derr, s);
+    } else {
         Timed t(E, SU2_K_PLAQUETTE, s);
         su2::launch_plaquette(a, E->f32, E->part_plaq, E->block, E->grid, s);
         t.done(s);
     }
-    {
+    if (!one) {
         Timed t(E, SU2_K_REDUCE, s);
         su2::launch_finalize(E->ddesc, E->n, E->fin_chunks, E->part_plaq, nullptr, E->fin_cnt, E->fin_chunk,
                              E->dres, nullptr, 4, E->st, E->derr, s);
@@ -922,12 +925,15 @@ su2_status measure_plaquette(su2_ensemble_s *E, int l, double *avg, double *sp, 
 su2_status measure_polyakov(su2_ensemble_s *E, int l, double *out) {
     hipStream_t s = E->stream();
     const KArgs a = kargs(E, 1);
-    {
+    const bool one = E->n == 1 && E->nstiles <= su2::ONE_TILES && !E->timing;
+    if (one) {
+        su2::launch_polyakov_one(a, E->f32, E->block, E->dres, E->derr, s);
+    } else {
         Timed t(E, SU2_K_POLYAKOV, s);
         su2::launch_polyakov(a, E->f32, E->part_poly, E->block, E->grid, s);
         t.done(s);
     }
-    {
+    if (!one) {
         Timed t(E, SU2_K_REDUCE, s);
         su2::launch_finalize(E->ddesc, E->n, E->fin_chunks, nullptr, E->part_poly, E->fin_cnt, E->fin_chunk,
                              nullptr, E->dres, 4, E->st, E->derr, s);

@@ -86,6 +86,11 @@ void launch_plaquette(const KArgs &a, bool f32, double *part, int block, int gri
 // they go to series slot ((sweep - run_base) / every) % nslots (2 * ntiles
 // doubles per slot).
 void launch_polyakov(const KArgs &a, bool f32, double *part, int block, int grid, hipStream_t s);
+// The same measurements of a single lattice of at most ONE_TILES tiles in one
+// launch: results and error word straight to mapped host memory.
+constexpr int ONE_TILES = 2;
+void launch_plaquette_one(const KArgs &a, bool f32, int block, double *out, unsigned *err, hipStream_t s);
+void launch_polyakov_one(const KArgs &a, bool f32, int block, double *out, unsigned *err, hipStream_t s);
 // Final reduction of the standalone measurements: `chunks` workgroups per
 // lattice, cnt[nlat] arrival tickets (zero between launches), chunk scratch
 // of 6 doubles per workgroup.  pp: k_plaquette partials (4 per tile) ->

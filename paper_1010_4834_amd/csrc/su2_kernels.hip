@@ -866,9 +866,13 @@ __global__ __launch_bounds__(256) void k_unit_defect(KArgs a, unsigned long long
 // = 1/2 Tr[(U_mu(s) U_nu(s+mu)) (U_nu(s) U_mu(s+nu))^dag], traced in link
 // precision, accumulated in binary64 per lane, then a compensated block sum
 // per tile (spatial, temporal planes).
-template <class T>
-__global__ __launch_bounds__(256) void k_plaquette(KArgs a, double *part) {
+// ONE: a lattice of a few tiles (ONE_TILES) in one workgroup, which writes the
+// averages and the error word to mapped host memory itself; k_finalize and the
+// gap before it are 5.5 us of such a call.
+template <class T, bool ONE>
+__global__ __launch_bounds__(256) void k_plaquette(KArgs a, double *part, double *out, unsigned *err) {
     __shared__ DD lds[2 * 4];
+    DD tot[2] = {{0.0, 0.0}, {0.0, 0.0}};
     for_each_tile(a.ntiles, a.xcd_remap, [&](int tile) {
         const Tile tl = load_tile(a.tiles, tile);
         const LatDesc d = load_desc(a.desc + tl.x);
@@ -901,19 +905,36 @@ __global__ __launch_bounds__(256) void k_plaquette(KArgs a, double *part) {
             acc[0] = DD{sp, 0.0};
             acc[1] = DD{tp, 0.0};
         }
+        if (ONE) {
+            tot[0] = dd_add(tot[0], acc[0]);
+            tot[1] = dd_add(tot[1], acc[1]);
+            return;
+        }
         dd_block_sum<2>(acc, lds);
         if (threadIdx.x == 0) {
             part[4 * tile + 0] = acc[0].hi; part[4 * tile + 1] = acc[0].lo;
             part[4 * tile + 2] = acc[1].hi; part[4 * tile + 3] = acc[1].lo;
         }
     });
+    if (ONE) {
+        dd_block_sum<2>(tot, lds);
+        if (threadIdx.x == 0) {
+            const double V = 2.0 * (double)uni(a.desc->vh);
+            const double sp = tot[0].hi + tot[0].lo, tp = tot[1].hi + tot[1].lo;
+            out[0] = (sp + tp) / (6.0 * V);
+            out[1] = sp / (3.0 * V);
+            out[2] = tp / (3.0 * V);
+            *err = *a.err;
+        }
+    }
 }
 
 // Polyakov loop partial sums (paper Sec. 2): per spatial site, the product
 // of the temporal links t = 0 .. Nt-1 in ascending t, half trace.
-template <class T>
-__global__ __launch_bounds__(256) void k_polyakov(KArgs a, double *part) {
+template <class T, bool ONE>
+__global__ __launch_bounds__(256) void k_polyakov(KArgs a, double *part, double *out, unsigned *err) {
     __shared__ DD lds[4];
+    DD tot[1] = {{0.0, 0.0}};
     if (a.nslots > 0)
         part += (long long)(((uni(a.st->sweep) - uni(a.st->run_base)) / (uint32_t)a.every) % (uint32_t)a.nslots) *
                 2 * a.ntiles;
@@ -938,12 +959,23 @@ __global__ __launch_bounds__(256) void k_polyakov(KArgs a, double *part) {
             }
             acc[0] = DD{(double)P.a, 0.0};
         }
+        if (ONE) {
+            tot[0] = dd_add(tot[0], acc[0]);
+            return;
+        }
         dd_block_sum<1>(acc, lds);
         if (threadIdx.x == 0) {
             part[2 * tile + 0] = acc[0].hi;
             part[2 * tile + 1] = acc[0].lo;
         }
     });
+    if (ONE) {
+        dd_block_sum<1>(tot, lds);
+        if (threadIdx.x == 0) {
+            out[0] = (tot[0].hi + tot[0].lo) / (double)uni(a.desc->ns);
+            *err = *a.err;
+        }
+    }
 }
 
 // Final per-lattice reduction of the standalone measurements' tile
@@ -1895,13 +1927,23 @@ void launch_unit_defect(const KArgs &a, bool f32, unsigned long long *out, int b
 }
 
 void launch_plaquette(const KArgs &a, bool f32, double *part, int block, int grid, hipStream_t s) {
-    if (f32) hipLaunchKernelGGL((k_plaquette<float>), grid_of(a, grid), dim3(block), 0, s, a, part);
-    else hipLaunchKernelGGL((k_plaquette<double>), grid_of(a, grid), dim3(block), 0, s, a, part);
+    if (f32) hipLaunchKernelGGL((k_plaquette<float, false>), grid_of(a, grid), dim3(block), 0, s, a, part, nullptr, nullptr);
+    else hipLaunchKernelGGL((k_plaquette<double, false>), grid_of(a, grid), dim3(block), 0, s, a, part, nullptr, nullptr);
 }
 
 void launch_polyakov(const KArgs &a, bool f32, double *part, int block, int grid, hipStream_t s) {
-    if (f32) hipLaunchKernelGGL((k_polyakov<float>), grid_of(a, grid), dim3(block), 0, s, a, part);
-    else hipLaunchKernelGGL((k_polyakov<double>), grid_of(a, grid), dim3(block), 0, s, a, part);
+    if (f32) hipLaunchKernelGGL((k_polyakov<float, false>), grid_of(a, grid), dim3(block), 0, s, a, part, nullptr, nullptr);
+    else hipLaunchKernelGGL((k_polyakov<double, false>), grid_of(a, grid), dim3(block), 0, s, a, part, nullptr, nullptr);
+}
+
+void launch_plaquette_one(const KArgs &a, bool f32, int block, double *out, unsigned *err, hipStream_t s) {
+    if (f32) hipLaunchKernelGGL((k_plaquette<float, true>), dim3(1), dim3(block), 0, s, a, nullptr, out, err);
+    else hipLaunchKernelGGL((k_plaquette<double, true>), dim3(1), dim3(block), 0, s, a, nullptr, out, err);
+}
+
+void launch_polyakov_one(const KArgs &a, bool f32, int block, double *out, unsigned *err, hipStream_t s) {
+    if (f32) hipLaunchKernelGGL((k_polyakov<float, true>), dim3(1), dim3(block), 0, s, a, nullptr, out, err);
+    else hipLaunchKernelGGL((k_polyakov<double, true>), dim3(1), dim3(block), 0, s, a, nullptr, out, err);
 }
 
 void launch_finalize(const LatDesc *desc, int nlat, int chunks, const double *pp, const double *pl,
