@@ -45,15 +45,11 @@ INFINITY_CACHE_BYTES = 256 << 20
 # per lane; a grid of 0 counts as its effective size, one workgroup per
 # tile).  Valid only for the sources whose code (comments and layout aside)
 # has this hash: the kernels and the host code that orders their tiles.
-HB_TRAFFIC = {"sources_sha256": "f3d9d7bd90f0ae9b097c8e2a2b0890fce0f860495d8cef363ed0e4064d967e98",
-              "by_launch": {(128, 4096, 3, 1): 74249104, (64, 8192, 3, 1): 74273863,
-                            (256, 2048, 3, 1): 74094736, (64, 8192, 1, 1): 78245785,
-                            (64, 7168, 3, 1): 76533206, (128, 3584, 3, 1): 77228460,
-                            (256, 1792, 3, 1): 76072259, (64, 4096, 3, 1): 74261637,
-                            (128, 2048, 3, 1): 74268106, (256, 1024, 3, 1): 74100859,
-                            (64, 4096, 3, 2): 75724088, (128, 2048, 3, 2): 75571729},
+HB_TRAFFIC = {"sources_sha256": "94a5459ea1caddc2eb18baaa48acb5f7da9d0dbcaf5446c38d476ae1c756f281",
+              "by_launch": {(128, 4096, 3, 1): 74342025, (64, 8192, 3, 1): 74305155,
+                            (256, 2048, 3, 1): 74133833},
               # the 64^4 control: 1 GiB algorithmic per launch
-              "control64": {(256, 32768, 0, 1): 1267011584}}
+              "control64": {(256, 32768, 0, 1): 1305338423}}
 KERNEL_SOURCES = ("su2_kernels.hip", "su2_device.hpp", "su2_internal.hpp", "su2_api.hip")
 
 

@@ -985,8 +985,7 @@ __global__ __launch_bounds__(256) void k_polyakov(KArgs a, double *part, double 
 // (ticket in cnt[l]) combines the C pairs in chunk order and writes the
 // plaquette (avg, spatial, temporal) and / or the Polyakov loop, and with the
 // first lattice the error word, to mapped host memory: a measurement call ends
-// with its synchronisation, without a copy or a kernel for the error word
-// (4^4 plaquette: 24 us).
+// with its synchronisation, without a copy or a kernel for the error word.
 __device__ __forceinline__ void chunk_range(int n, int C, int c, int &lo, int &hi) {
     lo = (int)(((long long)n * c) / C);
     hi = (int)(((long long)n * (c + 1)) / C);
@@ -1610,8 +1609,8 @@ template <int N> __device__ __forceinline__ double wave_sum_many(double (&v)[N],
 // line that is held whole wraps around (XE = XC = N); a piece carries
 // XE - XC = Rmax elements beyond it, whose last values are not used.
 // For the traces a lane owns NC successive times of one x and meets each
-// later Z once for all of them: NC + Tp LDS reads, as many conversions and
-// 4 NC Tp binary64 multiply-adds per R.  The lane sums of one R are added over
+// later Z once for all of them: NC + Tp LDS reads per R for NC Tp four-term
+// products, taken in link precision and summed in binary64.  The lane sums of one R are added over
 // the wavefront and kept per (wavefront, R, T) in LDS until the last unit.
 // Rows beyond the lattice or the unit enter as zero times a valid Z.
 // At 24^3 x 48, R <= 12, T <= 16 in binary32: 127 us, with k_wgauge, k_wlinks
