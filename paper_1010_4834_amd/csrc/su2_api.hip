@@ -132,8 +132,8 @@ struct su2_ensemble_s {
     size_t wl_p_bytes = 0;
     double *wpart = nullptr;
     size_t wpart_bytes = 0;
-    su2::WPlan wl_plan[2];          // work split of the last Wilson-loop call, for
-    int wl_plan_r = 0, wl_plan_t = 0;  // these bounds
+    su2::WPlan wl_plan[8];          // work split of the last Wilson-loop call, for
+    int wl_plan_r = 0, wl_plan_t = 0, wl_npass = 0;  // these bounds, passes over the times
 
     uint32_t *trace = nullptr;
 
@@ -1600,18 +1600,23 @@ su2_status su2_wilson_loops(su2_lattice E, int Rmax, int Tmax, double *out) {
     const LatDesc &d = E->hdesc[0];
     const int smin = std::min(d.n[0], std::min(d.n[1], d.n[2]));
     if (!out || Rmax < 1 || Tmax < 1 || Rmax > smin || Tmax > d.n[3] || Tmax > 32) return SU2_EINVAL;
-    const int npass = Tmax > 16 ? 2 : 1;
     if (E->wl_plan_r != Rmax || E->wl_plan_t != Tmax) {
         E->wl_plan_r = 0;
-        int grid = 0;
-        for (int k = 0; k < npass; ++k) {
-            if (!su2::wloops_plan(E->f32, d.n, Rmax, Tmax, 16 * k, E->wl_plan[k])) return SU2_ENOMEM;
-            grid = std::max(grid, E->wl_plan[k].grid);
+        int grid = 0, step = 16, k = 0;
+        while (step * k < Tmax) {
+            if (su2::wloops_plan(E->f32, d.n, Rmax, Tmax, step * k, step, E->wl_plan[k])) {
+                grid = std::max(grid, E->wl_plan[k++].grid);
+            } else {  // long lines: fewer times at once
+                if (step == 4) return SU2_ENOMEM;
+                step /= 2, grid = k = 0;
+            }
         }
-        for (int k = 0; k < npass; ++k) E->wl_plan[k].grid = grid;
+        E->wl_npass = k;
+        while (k > 0) E->wl_plan[--k].grid = grid;
         E->wl_plan_r = Rmax, E->wl_plan_t = Tmax;
     }
     const su2::WPlan *plan = E->wl_plan;
+    const int npass = E->wl_npass;
     const int nparts = plan[0].grid;
     // per spatial site and time: the prefix product (32 bytes), three links
     // in its gauge and their weights

@@ -138,8 +138,11 @@ struct WPlan {
     int block, grid, nc, lds;   // threads, workgroups, rows per lane, LDS bytes
     int toff, Tp, Tall;         // times toff < T <= toff + Tp of Tall
 };
-// false if no split fits the LDS
-bool wloops_plan(bool f32, const int *n, int Rmax, int Tmax, int toff, WPlan &out);
+// Split of the times after toff, at most `step` (16, 8 or 4) of them; false if
+// none fits the LDS.  The sums of a pass take 8 Rmax step bytes per wavefront,
+// which at 16 times leaves no room for the lines from some Rmax on (binary64:
+// 62 sites, T > 16).
+bool wloops_plan(bool f32, const int *n, int Rmax, int Tmax, int toff, int step, WPlan &out);
 void launch_wgauge(const KArgs &a, bool f32, int ns, int next, void *P, hipStream_t s);
 void launch_wlinks(const KArgs &a, bool f32, const int *n, const void *sp, int sp_raw, int next, const void *P, void *L,
                    void *w, hipStream_t s);

@@ -1602,8 +1602,9 @@ template <int N> __device__ __forceinline__ double wave_sum_many(double (&v)[N],
 // Loop traces of the times toff < T <= toff + Tp (Tp <= TMAX) and every
 // R <= Rmax.  A work unit is a group of G lattice lines along direction mu (or
 // a piece of XC sites of one line), times t0 .. t0 + TC - 1: the workgroup
-// holds Z of its elements (line, x, t) for the current R in LDS, times up to
-// t0 + TC - 1 + toff + Tp, and the single transformed link P(x,t) U(x,t)
+// holds Z of its elements (line, x, t) for the current R in LDS, times t0 ..
+// t0 + TC - 1 and, without the gap that a large toff leaves, up to t0 + TC - 1
+// + toff + Tp, and the single transformed link P(x,t) U(x,t)
 // P(x+mu,t)^-1 of an element in the registers of the lane that owns it, so
 // that Z(x,t;R+1) = link(x,t) Z(x+mu,t;R) reads only its LDS neighbour.  A
 // line that is held whole wraps around (XE = XC = N); a piece carries
@@ -1642,7 +1643,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64, 512), amdgpu_waves_per
         v /= D.ntc;
         const int xc = v % D.nxc, grp = v / D.nxc;
         const int t0 = tc * D.TC, x0 = xc * D.XC, rows = min(D.TC, d.n[3] - t0), W = D.G * D.XE;
-        const int nrow = D.NB * NC, nel = W * (nrow + pl.toff + TMAX), ke = (nel + nb - 1) / nb;
+        const int nrow = D.NB * NC, off = min(pl.toff, nrow - 1), nel = W * (nrow + off + TMAX), ke = (nel + nb - 1) / nb;
         const float iW = 1.0f / (float)W, iX = 1.0f / (float)D.XE;
         const long long first = (long long)mu * d.ns * next;
         const Q<T> *Lm = L + first;
@@ -1662,7 +1663,8 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64, 512), amdgpu_waves_per
                 const int g = (int)(((float)gx + 0.5f) * iX), xi = gx - g * D.XE;
                 const uint32_t up = (uint32_t)(xi + 1 < D.XE ? e + 1 : D.XE == D.XC ? e - (D.XE - 1) : e);
                 nbr[k >> 1] = k & 1 ? nbr[k >> 1] | up << 16 : up;
-                const int line = min(grp * D.G + g, D.lines - 1), t = min(t0 + te, next - 1);
+                const int line = min(grp * D.G + g, D.lines - 1);
+                const int t = min(t0 + te + (te < nrow ? 0 : pl.toff - off), next - 1);
                 int xa = x0 + xi;
                 while (xa >= D.N) xa -= D.N;
                 const long long o = ((long long)line * next + t) * D.N + xa;
@@ -1705,7 +1707,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64, 512), amdgpu_waves_per
                     A[j] = r0 + j < rows ? qscale1p(q, fma(f, h, f + h)) : Q<T>{T(0), T(0), T(0), T(0)};
                     o += W;
                 }
-                o = (r0 + pl.toff) * W + gx;
+                o = (r0 + off) * W + gx;
                 __asm__ volatile("" : "+v"(o));
 #pragma unroll
                 for (int m = 1; m < NC + TMAX; ++m) {
@@ -2050,14 +2052,15 @@ bool wl_plan_at(bool f32, const int *n, int Rmax, int toff, int Tp, int TM, int 
         int punits = 0;
         for (int nbl = std::min(block, (Nt + nc - 1) / nc); nbl >= 1; --nbl) {
             const int ntc = (Nt + nbl * nc - 1) / (nbl * nc), TC = (Nt + ntc - 1) / ntc;
-            const int NB = (TC + nc - 1) / nc, TE = NB * nc + toff + TM;
+            const int NB = (TC + nc - 1) / nc, TE = NB * nc + std::min(toff, NB * nc - 1) + TM;
             const int emax = wl_ke(f32) * block;
             int XC = D.N, XE = D.N;
             if ((long long)XE * TE > emax || D.N * NB > block ||
                 wl_bytes(f32, XE * TE, block, Rmax, TM) > lds_max) {
                 // a piece of a line with Rmax sites beyond it, only for lines too long for any unit
-                if ((long long)D.N * (nc + toff + TM) <= emax && D.N <= block &&
-                    wl_bytes(f32, D.N * (nc + toff + TM), block, Rmax, TM) <= lds_max)
+                const int TE1 = nc + std::min(toff, nc - 1) + TM;
+                if ((long long)D.N * TE1 <= emax && D.N <= block &&
+                    wl_bytes(f32, D.N * TE1, block, Rmax, TM) <= lds_max)
                     continue;
                 XC = std::min(block / NB, emax / TE - Rmax);
                 while (XC > 0 && wl_bytes(f32, (XC + Rmax) * TE, block, Rmax, TM) > lds_max) --XC;
@@ -2088,7 +2091,7 @@ bool wl_plan_at(bool f32, const int *n, int Rmax, int toff, int Tp, int TM, int 
         if (dbest >= 1e300) return false;
         D = pick;
         p.nunits += punits;
-        const int e = D.G * D.XE * (D.NB * nc + toff + TM);
+        const int e = D.G * D.XE * (D.NB * nc + std::min(toff, D.NB * nc - 1) + TM);
         p.nel = std::max(p.nel, (e + block - 1) / block * block);
         total += dbest;
     }
@@ -2098,8 +2101,8 @@ bool wl_plan_at(bool f32, const int *n, int Rmax, int toff, int Tp, int TM, int 
 }
 }  // namespace
 
-bool wloops_plan(bool f32, const int *n, int Rmax, int Tmax, int toff, WPlan &out) {
-    const int Tp = std::min(16, Tmax - toff), TM = Tp <= 4 ? 4 : Tp <= 8 ? 8 : 16;
+bool wloops_plan(bool f32, const int *n, int Rmax, int Tmax, int toff, int step, WPlan &out) {
+    const int Tp = std::min(step, Tmax - toff), TM = Tp <= 4 ? 4 : Tp <= 8 ? 8 : 16;
     WChoice best{};
     best.cost = 1e300;
     for (int block : {64, 128, 192, 256})

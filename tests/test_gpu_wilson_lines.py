@@ -53,3 +53,16 @@ def test_links_off_the_group(su2, orc):
     lat.set_links(U)
     assert np.abs(lat.wilson_loops(4, 8) - orc.wilson(dims, U, 4, 8)).max() < 1e-13
     lat.close()
+
+
+@pytest.mark.parametrize("dims,Rm,Tm", [((64, 64, 64, 32), 64, 32), ((82, 82, 82, 12), 82, 12)])
+def test_long_lines_take_fewer_times_at_once(su2, dims, Rm, Tm):
+    """Binary64 bounds whose sums and lines do not fit the LDS at sixteen times
+    a pass: the same values as calls of fewer R, or of fewer T, which fit."""
+    lat = su2.Lattice(dims, start=su2.HOT, seed=64, prec=su2.F64)
+    lat.ape_smear(0.6, 5)
+    W = np.asarray(lat.wilson_loops(Rm, Tm))
+    assert np.isfinite(W).all() and W.shape == (Rm, Tm)
+    for R, T in ((Rm // 2, Tm), (Rm, 4)):
+        assert np.abs(W[:R, :T] - np.asarray(lat.wilson_loops(R, T))).max() < 1e-13, (R, T)
+    lat.close()
