@@ -1459,7 +1459,7 @@ __device__ __forceinline__ double rcp_newton(double x) {  // 1/x, relative error
 }
 
 template <class T>
-__global__ __launch_bounds__(512) void k_wlinks(KArgs a, const void *sp, int sp_raw, int next,
+__global__ __launch_bounds__(512) void k_wlinks(KArgs a, const void *sp, int sp_raw, int next, int tbase,
                                                 const double2 *__restrict__ P, Q<T> *__restrict__ L,
                                                 T *__restrict__ w) {
     __shared__ Q<T> tq[32 * 33];
@@ -1470,7 +1470,7 @@ __global__ __launch_bounds__(512) void k_wlinks(KArgs a, const void *sp, int sp_
     // three directions of a time one after another: its P and links are
     // fetched into that XCD's L2 once (with the directions as separate passes
     // over all times 28 us at 24^3 x 48)
-    const int per = gridDim.x >> 3, q8 = (int)blockIdx.x >> 3, t = ((int)blockIdx.x & 7) + 8 * (int)blockIdx.y;
+    const int per = gridDim.x >> 3, q8 = (int)blockIdx.x >> 3, t = tbase + ((int)blockIdx.x & 7) + 8 * (int)blockIdx.y;
     if (t >= next) return;
     const int mu = q8 / (per / 3);
     const int ntx = (d.n[0] + 31) >> 5;
@@ -2015,10 +2015,16 @@ void launch_wlinks(const KArgs &a, bool f32, const int *n, const void *sp, int s
     const auto tiles = [](int k) { return (k + 31) / 32; };
     const int gx = std::min(1 << 16, tiles(n[0]) * std::max(tiles(n[1]) * n[2], tiles(n[2]) * n[1]));
     const int most = std::min(32, n[0]) * std::min(32, std::max(n[1], n[2]));
-    const dim3 g((unsigned)(8 * 3 * gx), (unsigned)((next + 7) / 8)), b((unsigned)((most + 127) / 128 * 64));  // two elements per thread
+    const dim3 b((unsigned)((most + 127) / 128 * 64));  // two elements per thread
     const double2 *p = (const double2 *)P;
-    if (f32) hipLaunchKernelGGL((k_wlinks<float>), g, b, 0, s, a, sp, sp_raw, next, p, (Q<float> *)L, (float *)w);
-    else hipLaunchKernelGGL((k_wlinks<double>), g, b, 0, s, a, sp, sp_raw, next, p, (Q<double> *)L, (double *)w);
+    // 4096 rows of the grid at most (its limit is 65535): 32768 times a launch
+    for (int t = 0; t < next; t += 8 * 4096) {
+        const dim3 g((unsigned)(8 * 3 * gx), (unsigned)std::min(4096, (next - t + 7) / 8));
+        if (f32)
+            hipLaunchKernelGGL((k_wlinks<float>), g, b, 0, s, a, sp, sp_raw, next, t, p, (Q<float> *)L, (float *)w);
+        else
+            hipLaunchKernelGGL((k_wlinks<double>), g, b, 0, s, a, sp, sp_raw, next, t, p, (Q<double> *)L, (double *)w);
+    }
 }
 
 // Work split of the Wilson loops of times toff < T <= toff + Tp.  Among the

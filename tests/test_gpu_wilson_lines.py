@@ -66,3 +66,13 @@ def test_long_lines_take_fewer_times_at_once(su2, dims, Rm, Tm):
     for R, T in ((Rm // 2, Tm), (Rm, 4)):
         assert np.abs(W[:R, :T] - np.asarray(lat.wilson_loops(R, T))).max() < 1e-13, (R, T)
     lat.close()
+
+
+def test_more_times_than_grid_rows(su2, orc):
+    """Nt + Tmax beyond 8 x 4096 times, the rows of one grid."""
+    dims = (2, 2, 4, 32780)
+    U = inputs.random_config(dims, 65)
+    lat = su2.Lattice(dims, start=su2.COLD, prec=su2.F64)
+    lat.set_links(U)
+    assert np.abs(lat.wilson_loops(2, 3) - orc.wilson(dims, U, 2, 3)).max() < 1e-13
+    lat.close()
