@@ -224,6 +224,17 @@ su2_status dalloc(su2_ensemble_s *E, P **p, size_t bytes) {
     return SU2_OK;
 }
 
+// A buffer of at least `bytes`, kept between calls: *cap is what it holds, 0
+// while there is none (dalloc has freed the old one when it reports ENOMEM).
+template <class P>
+su2_status grow(su2_ensemble_s *E, P **p, size_t *cap, size_t bytes) {
+    if (bytes <= *cap) return SU2_OK;
+    *cap = 0;
+    CHK(dalloc(E, p, bytes));
+    *cap = bytes;
+    return SU2_OK;
+}
+
 // Mapped, coherent pinned host memory of `bytes` and its device address.
 su2_status host_mapped(su2_ensemble_s *E, void **host, void **dev, size_t bytes) {
     (void)E;
@@ -1622,15 +1633,8 @@ su2_status su2_wilson_loops(su2_lattice E, int Rmax, int Tmax, double *out) {
     // in its gauge and their weights
     const int next = d.n[3] + Tmax;
     const size_t nst = (size_t)d.ns * next, gb = nst * (32 + 3 * (E->f32 ? 20 : 40));
-    if (gb > E->wl_p_bytes) {
-        CHK(dalloc(E, &E->wl_p, gb));
-        E->wl_p_bytes = gb;
-    }
-    const size_t pb = sizeof(double) * 2 * (size_t)Rmax * nparts * Tmax;
-    if (pb > E->wpart_bytes) {
-        CHK(dalloc(E, &E->wpart, pb));
-        E->wpart_bytes = pb;
-    }
+    CHK(grow(E, &E->wl_p, &E->wl_p_bytes, gb));
+    CHK(grow(E, &E->wpart, &E->wpart_bytes, sizeof(double) * 2 * (size_t)Rmax * nparts * Tmax));
     CHK(ensure_series(E, Rmax * Tmax));
     hipStream_t s = E->stream();
     const bool sm = E->sm_cur >= 0;
