@@ -10,7 +10,9 @@
  * Conventions shared by every call
  *  - Every call returns su2_status (SU2_OK = 0); nothing aborts or throws
  *    across the ABI.  After SU2_EDEVICE the handle is failed and every later
- *    call on it returns SU2_ESTATE (su2_destroy excepted).
+ *    call on it returns SU2_ESTATE (su2_destroy excepted).  After SU2_ENOMEM
+ *    it is as it was before the call (a change of the launch shape keeps the
+ *    old shape), unless not even that can be had again: then it is failed too.
  *  - Lattice extents Nx, Ny, Nz, Nt are even and >= 2 (the even/odd
  *    checkerboard of a periodic lattice needs even extents).  mu = 0,1,2 are
  *    x,y,z and mu = 3 is time (the paper's U_4).

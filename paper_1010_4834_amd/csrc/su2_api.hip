@@ -1032,15 +1032,22 @@ su2_status set_launch_common(su2_ensemble_s *E, int block, int grid, int remap, 
     if (grid < 0 || (grid & 7)) return SU2_EINVAL;
     if (remap < 0 || remap > 3) return SU2_EINVAL;
     if (nl != 1 && nl != 2 && nl != 4) return SU2_EINVAL;
-    const bool reshape = block != E->block || nl != E->nl;
+    if (block != E->block || nl != E->nl) {
+        const int block0 = E->block, nl0 = E->nl;
+        E->block = block;
+        E->nl = nl;
+        const su2_status st = build_tiles(E);
+        if (st == SU2_ENOMEM) {  // some tables are gone: those of the old shape again
+            E->block = block0;
+            E->nl = nl0;
+            E->ntiles = 0;  // the try counts are folded already
+            if (build_tiles(E) != SU2_OK) E->failed = true;
+        }
+        CHK(st);
+    }
     E->own_shape = false;
     E->grid = grid;
     E->remap = remap;
-    if (reshape) {
-        E->block = block;
-        E->nl = nl;
-        CHK(build_tiles(E));
-    }
     drop_graphs(E);
     return SU2_OK;
 }
@@ -1100,6 +1107,7 @@ su2_status autotune_common(su2_ensemble_s *E) {
     HIPCHK(hipEventCreate(&ev.b));
     hipEvent_t ea = ev.a, eb = ev.b;
     float best = 1e30f;
+    su2_status st = SU2_OK;
     Shape bestc{E->block, E->grid, E->remap, E->nl};
     for (int nl : nls)
         for (int b : blocks)
@@ -1108,7 +1116,9 @@ su2_status autotune_common(su2_ensemble_s *E) {
                     const int per_cu = gm >= 0 ? gm : su2::heatbath_blocks_per_cu(E->f32, nl, b);
                     const int g = per_cu > 0 ? per_cu * cus / 8 * 8 : 0;
                     if (gm < 0 && per_cu <= 0) continue;
-                    CHK(set_launch_common(E, b, g, rm, nl));
+                    st = set_launch_common(E, b, g, rm, nl);
+                    if (st == SU2_ENOMEM && !E->failed) continue;  // no room for its tables
+                    CHK(st);
                     // series slots 0..3 of this candidate's four sweeps
                     E->hst = st0;
                     E->hst.run_base = st0.sweep;
@@ -1125,7 +1135,8 @@ su2_status autotune_common(su2_ensemble_s *E) {
                         bestc = Shape{b, g, rm, nl};
                     }
                 }
-    CHK(set_launch_common(E, bestc.block, bestc.grid, bestc.remap, bestc.nl));
+    st = set_launch_common(E, bestc.block, bestc.grid, bestc.remap, bestc.nl);
+    if (st != SU2_ENOMEM || E->failed) CHK(st);
     HIPCHK(hipMemcpyAsync(E->links, backup.p, E->link_bytes, hipMemcpyDeviceToDevice, s));
     HIPCHK(hipMemsetAsync(E->tries_part, 0, sizeof(unsigned long long) * E->ntiles, s));
     HIPCHK(hipStreamSynchronize(s));
@@ -1133,8 +1144,9 @@ su2_status autotune_common(su2_ensemble_s *E) {
     E->updates = upd0;
     E->hst = st0;
     CHK(upload_state(E));
-    tune_cache_put(key, bestc);
     invalidate_measure_buffers(E);
+    CHK(st);
+    tune_cache_put(key, bestc);
     return SU2_OK;
 }
 

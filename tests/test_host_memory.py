@@ -2,7 +2,7 @@
 calls can use: no launch gets a null pointer in place of a buffer."""
 import pytest
 
-from tests.host_lib import ENOMEM, OK, host_lib
+from tests.host_lib import ENOMEM, ESTATE, OK, host_lib
 
 
 @pytest.fixture
@@ -10,6 +10,7 @@ def host(tmp_path_factory):
     h = host_lib(tmp_path_factory)
     yield h
     h.lib.stub_malloc_countdown(-1)
+    h.lib.stub_malloc_limit(-1)
 
 
 @pytest.mark.parametrize("nth", [0, 1])
@@ -35,4 +36,50 @@ def test_smeared_buffers(host, nth):
     host.lib.stub_clear()
     assert host.lib.su2_ape_smear(h, 0.5, 2) == OK and host.wilson(h, 2, 2) == OK
     assert host.names() and host.lib.stub_nulls() == 0
+    assert host.lib.su2_destroy(h) == OK
+
+
+def sweep(host, h):
+    """Every kind of launch that reads the tables."""
+    host.lib.stub_clear()
+    assert host.lib.su2_heatbath(h, 2.3, 3, 1) == OK and host.lib.su2_overrelax(h, 1) == OK
+    assert host.plaquette(h) == OK and host.lib.su2_ape_smear(h, 0.5, 1) == OK
+    assert host.names() and host.lib.stub_nulls() == 0
+
+
+def test_launch_shape(host):
+    """A launch shape one of whose tables, each in turn, cannot be had is
+    refused, and the old one stays."""
+    st, nth = ENOMEM, 0
+    while st != OK:
+        h = host.create((8, 8, 8, 8))
+        shape = host.launch(h)
+        host.lib.stub_malloc_countdown(nth)
+        st = host.lib.su2_set_launch(h, 64, 512, 1, 2)
+        host.lib.stub_malloc_countdown(-1)
+        assert st in (ENOMEM, OK)
+        assert host.launch(h) == (shape if st else (64, 512, 1, 2))
+        sweep(host, h)
+        assert host.lib.su2_destroy(h) == OK
+        nth += 1
+    assert nth > 10
+
+
+def test_launch_shape_without_any(host):
+    """Neither the new shape's tables nor the old one's: the handle is failed."""
+    h = host.create((8, 8, 8, 8))
+    host.lib.stub_malloc_limit(0)
+    assert host.lib.su2_set_launch(h, 64, 0, 1, 1) == ENOMEM
+    host.lib.stub_malloc_limit(-1)
+    assert host.lib.su2_heatbath(h, 2.3, 1, 1) == ESTATE and host.plaquette(h) == ESTATE
+    assert host.lib.su2_destroy(h) == OK
+
+
+@pytest.mark.parametrize("nth", [1, 5, 60])
+def test_autotune(host, nth):
+    """A candidate without room for its tables is passed over."""
+    h = host.create((8, 8, 8, 8 + 2 * nth))   # a size of its own: nothing is tuned yet
+    host.lib.stub_malloc_countdown(nth)
+    assert host.lib.su2_autotune(h, 2.3) == OK
+    sweep(host, h)
     assert host.lib.su2_destroy(h) == OK
