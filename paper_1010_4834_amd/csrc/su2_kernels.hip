@@ -1897,8 +1897,11 @@ bool launch_small_run(const KArgs &a, bool f32, int nlat, int sites, const Small
     const int block = std::min(SMALL_BLOCK, ((four ? 4 : 1) * sites / 2 + 63) / 64 * 64);
     const auto k = f32 ? (four ? k_small_run<float, true> : k_small_run<float, false>)
                        : (four ? k_small_run<double, true> : k_small_run<double, false>);
+    // the same limit from every call: it belongs to the kernel, and another
+    // thread's launch may come between this one and its own
     if (lds > (48 << 10) &&
-        hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
+        hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)small_lds_bytes(f32, SMALL_SITES)) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
@@ -1987,17 +1990,11 @@ void launch_ape(const KArgs &a, bool f32, const void *src, int src_raw, void *ds
     else hipLaunchKernelGGL((k_ape<double>), g, dim3(block), 0, s, a, src, src_raw, dst, alpha);
 }
 
-// false: the slices are too large, or their LDS not to be had
+// false: the slices are too large
 bool launch_ape_slices(const KArgs &a, bool f32, int ns, int nt, const void *src, int src_raw, void *dst, double alpha,
                        int nsteps, hipStream_t s) {
     if (ns > ape_slice(f32)) return false;
-    const size_t lds = (size_t)3 * ns * (f32 ? 16 : 32);
-    const void *k = f32 ? (const void *)k_ape_slices<float> : (const void *)k_ape_slices<double>;
-    if (lds > (48 << 10) &&
-        hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
+    const size_t lds = (size_t)3 * ns * (f32 ? 16 : 32);  // 48 KiB at most
     const dim3 g((unsigned)nt), b((unsigned)((ns + 63) / 64 * 64));
     if (f32) hipLaunchKernelGGL((k_ape_slices<float>), g, b, lds, s, a, src, src_raw, dst, (float)alpha, nsteps);
     else hipLaunchKernelGGL((k_ape_slices<double>), g, b, lds, s, a, src, src_raw, dst, alpha, nsteps);
@@ -2035,6 +2032,7 @@ void launch_wlinks(const KArgs &a, bool f32, const int *n, const void *sp, int s
 // unless the smallest unit of it does not fit, which takes lines of several
 // hundred sites.
 namespace {
+constexpr int WL_LDS = 160 << 10;  // of one workgroup at most
 struct WChoice {
     WPlan p;
     double cost;
@@ -2113,7 +2111,7 @@ bool wloops_plan(bool f32, const int *n, int Rmax, int Tmax, int toff, int step,
     best.cost = 1e300;
     for (int block : {64, 128, 192, 256})
         for (int nc : {4, 5, 6}) wl_plan_at(f32, n, Rmax, toff, Tp, TM, nc, block, 48 << 10, best);
-    if (best.cost >= 1e300) wl_plan_at(f32, n, Rmax, toff, Tp, TM, 4, 512, 160 << 10, best);
+    if (best.cost >= 1e300) wl_plan_at(f32, n, Rmax, toff, Tp, TM, 4, 512, WL_LDS, best);
     if (best.cost >= 1e300) return false;
     out = best.p;
     out.lds = (int)best.lds;
@@ -2129,8 +2127,10 @@ template <class T, int TM, int NC>
 static void launch_wloops_k(const KArgs &a, const WPlan &p, int Rmax, int next, const void *L, const void *w, double *part,
                             hipStream_t s) {
     const auto kern = k_wloops<T, TM, NC, wl_ke(sizeof(T) == 4)>;
+    // the same limit from every call, as in launch_small_run; an error stays
+    // for the check at the end of the call
     if (p.lds > (64 << 10))
-        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, p.lds);
+        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, WL_LDS);
     hipLaunchKernelGGL(kern, dim3((unsigned)p.grid), dim3((unsigned)p.block), (size_t)p.lds, s, a, p, Rmax, next,
                        (const Q<T> *)L, (const T *)w, part);
 }

@@ -68,14 +68,14 @@ int stub_nulls() {
     for (const Launch &l : g_launches) n += l.nulls;
     return n;
 }
-// Dynamic LDS limits set for the kernels so far: number of different values
-// over all of them where one kernel was given more than one, else 0.
+// Dynamic LDS limits set for the kernels so far: how often one was changed.
 int stub_attr_changes() {
     int n = 0;
     for (const auto &a : g_attrs)
         for (size_t i = 1; i < a.second.size(); ++i) n += a.second[i] != a.second[i - 1];
     return n;
 }
+// Number of kernels given one.
 int stub_attrs() { return (int)g_attrs.size(); }
 
 void **__hipRegisterFatBinary(const void *) {
