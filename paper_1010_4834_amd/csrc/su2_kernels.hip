@@ -649,8 +649,9 @@ __device__ __forceinline__ void small_copy(const LatDesc &d, char *links, float4
 
 // Sweeps (with over = 0: heat bath, sweep words sweep0 ..; else
 // over-relaxation) of lattice blockIdx.x.  Measured sweeps write the mean
-// plaquette, summed as in k_heatbath, and the Polyakov loop to
-// outp / outl[l * nm + measurement].
+// plaquette, of the links' terms as in k_heatbath, and the Polyakov loop to
+// outp / outl[l * nm + measurement], both summed in (hi, lo) pairs from the
+// lane on.
 // FOUR: four lanes per link (heat bath; the workgroup holds them all).  Figures
 // at small_sites().  The time is the instructions of one wavefront's update,
 // issued alone on its SIMD.
@@ -658,8 +659,8 @@ template <class T, bool FOUR>
 __global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, double *outp, double *outl,
                                                            unsigned *errp) {
     extern __shared__ double4 small_lds[];
-    __shared__ double red[SMALL_BLOCK / 64][2];
-    const int l = (int)blockIdx.x, tid = (int)threadIdx.x, nb = (int)blockDim.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ DD red[SMALL_BLOCK / 64 * 2];
+    const int l = (int)blockIdx.x, tid = (int)threadIdx.x, nb = (int)blockDim.x, lane = tid & 63;
     const LatDesc d = load_desc(a.desc + l);
     const LdsBlocks<T> B{(decltype(LdsBlocks<T>::p))small_lds, d.vh};
     const T beta = (sizeof(T) == 4) ? (T)d.betaf : (T)d.beta;
@@ -669,7 +670,8 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, 
     unsigned long long tries = 0;
     int next = r.every - 1, m = 0;  // sweep of the next measurement
     for (int sw = 0; sw < r.nsweeps; ++sw) {
-        double pq = 0.0;
+        const bool measured = sw == next && m < r.nm;
+        DD sum[2] = {{0.0, 0.0}, {0.0, 0.0}};  // plaquette, Polyakov loop
         for (int sub = 0; sub < 8; ++sub) {
             const int mu = sub >> 1, par = sub & 1;
             if (!r.over) {
@@ -685,7 +687,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, 
                         [&](Q<T>(&L)[18]) { gather_lds(d, B, S, par, mu, L); },
                         [&](const Q<T> &U) { B.st(mu, par, cb, U); });
                     tries += wt;
-                    if (par) pq += pw;
+                    if (par && measured) sum[0] = dd_add(sum[0], DD{pw, 0.0});
                 }
                 for (int first = tid; !FOUR && first - lane < d.vh; first += nb) {
                     uint32_t wt = 0;
@@ -695,7 +697,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, 
                         [&](const Site &S, Q<T> *Vlow) { return staple_lds<T>(d, B, S, par, mu, Vlow); },
                         [&](int cb, int, const Q<T> &U, uint32_t) { B.st(mu, par, cb, U); });
                     tries += wt;
-                    if (par) pq += pw;
+                    if (par && measured) sum[0] = dd_add(sum[0], DD{pw, 0.0});
                 }
             } else {
                 for (int cb = tid; cb < d.vh; cb += nb) {
@@ -707,8 +709,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, 
             }
             __syncthreads();
         }
-        if (sw == next && m < r.nm) {
-            double pl = 0.0;
+        if (measured) {
             if (outl)
                 for (int xs = tid; xs < d.ns; xs += nb) {
                     int row, x, z, y;
@@ -717,22 +718,13 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, 
                     Q<T> P = qone<T>();
                     const int p0 = (x + y + z) & 1;
                     for (int t = 0; t < d.n[3]; ++t) P = qmul(P, B.ld(3, (p0 + t) & 1, (xs + d.ns * t) >> 1));
-                    pl += (double)P.a;
+                    sum[1] = dd_add(sum[1], DD{(double)P.a, 0.0});
                 }
-            pq = wave_sum_f64(pq);
-            pl = wave_sum_f64(pl);
-            if (lane == 0) red[wave][0] = pq, red[wave][1] = pl;
-            __syncthreads();
+            dd_block_sum<2>(sum, red);
             if (tid == 0) {
-                DD s{0.0, 0.0}, q{0.0, 0.0};
-                for (int v = 0; v < (nb >> 6); ++v) {
-                    s = dd_add(s, DD{red[v][0], 0.0});
-                    q = dd_add(q, DD{red[v][1], 0.0});
-                }
-                if (outp) outp[(long long)l * r.nm + m] = (s.hi + s.lo) / (12.0 * (double)d.vh);
-                if (outl) outl[(long long)l * r.nm + m] = (q.hi + q.lo) / (double)d.ns;
+                if (outp) outp[(long long)l * r.nm + m] = (sum[0].hi + sum[0].lo) / (12.0 * (double)d.vh);
+                if (outl) outl[(long long)l * r.nm + m] = (sum[1].hi + sum[1].lo) / (double)d.ns;
             }
-            __syncthreads();
             next += r.every;
             ++m;
         }
