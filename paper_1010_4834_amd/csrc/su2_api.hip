@@ -128,7 +128,7 @@ struct su2_ensemble_s {
     void *sm[2] = {nullptr, nullptr};
     int sm_cur = -1;  // index of the valid smeared buffer, -1 none
 
-    void *wl_p = nullptr;  // temporal prefix products of the Wilson loops
+    void *wl_p = nullptr;  // links in the temporal gauge, or lines, of the Wilson loops
     size_t wl_p_bytes = 0;
     double *wpart = nullptr;
     size_t wpart_bytes = 0;
@@ -293,6 +293,14 @@ KArgs kargs(su2_ensemble_s *E, int which = 0) {
     a.nslots = 0;
     a.every = 1;
     a.tile_links = E->nl == 1 && E->total_sites <= su2::split_sites(E->f32, E->sampler == SU2_CREUTZ) ? E->block : 0;
+    return a;
+}
+
+// The same for kernels that the tile mode of a new lattice, chosen for the
+// heat bath, does not suit: XCD by XCD unless the caller set a shape.
+KArgs xcd_args(su2_ensemble_s *E, int which = 0) {
+    KArgs a = kargs(E, which);
+    if (E->own_shape) a.xcd_remap = 1;
     return a;
 }
 
@@ -1584,11 +1592,9 @@ su2_status su2_ape_smear(su2_lattice E, double alpha, int nsteps) {
     for (int b = 0; b < 2; ++b)
         if (!E->sm[b]) CHK(dalloc(E, &E->sm[b], bytes));
     hipStream_t s = E->stream();
-    KArgs a = kargs(E);
-    // default_mode() is about the heat bath: a smearing step reads each link's
-    // neighbours in one time slice only and stays XCD by XCD (64^3 x 8 binary32
-    // 47 us a step against 61 in round robin)
-    if (E->own_shape) a.xcd_remap = 1;
+    // a smearing step reads each link's neighbours in one time slice only
+    // (64^3 x 8 binary32 47 us a step XCD by XCD, 61 in round robin)
+    const KArgs a = xcd_args(E);
     const void *src = E->links;
     int raw = 1, cur = 0;
     if (nsteps == 0) {  // smeared copy = raw spatial links
@@ -1618,47 +1624,79 @@ su2_status su2_get_smeared(su2_lattice E, double *host) {
     return get_links_l(E, 0, E->sm[E->sm_cur], 3, host);
 }
 
+// Work split and buffers of the Wilson loops in the temporal gauge or by
+// transport; partials per (R, T).  ENOMEM without room for them.
+static su2_status wilson_reserve(su2_ensemble_s *E, bool transport, int Rmax, int Tmax, int *nparts) {
+    const LatDesc &d = E->hdesc[0];
+    size_t bytes;
+    if (transport) {
+        *nparts = su2::wtrace_groups(E->total_sites, E->block);
+        bytes = (size_t)3 * Rmax * E->total_sites * link_size(E->f32);
+    } else {
+        if (E->wl_plan_r != Rmax || E->wl_plan_t != Tmax) {
+            E->wl_plan_r = 0;
+            int grid = 0, step = 16, k = 0;
+            while (step * k < Tmax) {
+                if (su2::wloops_plan(E->f32, d.n, Rmax, Tmax, step * k, step, E->wl_plan[k])) {
+                    grid = std::max(grid, E->wl_plan[k++].grid);
+                } else {  // long lines: fewer times at once
+                    if (step == 4) return SU2_ENOMEM;
+                    step /= 2, grid = k = 0;
+                }
+            }
+            E->wl_npass = k;
+            while (k > 0) E->wl_plan[--k].grid = grid;
+            E->wl_plan_r = Rmax, E->wl_plan_t = Tmax;
+        }
+        *nparts = E->wl_plan[0].grid;
+        // per spatial site and time: the prefix product (32 bytes), three links
+        // in its gauge and their weights
+        bytes = (size_t)d.ns * (d.n[3] + Tmax) * (32 + 3 * (E->f32 ? 20 : 40));
+    }
+    CHK(grow(E, &E->wl_p, &E->wl_p_bytes, bytes));
+    return grow(E, &E->wpart, &E->wpart_bytes, sizeof(double) * 2 * (size_t)Rmax * *nparts * Tmax);
+}
+
+static void wilson_launch(su2_ensemble_s *E, bool transport, int Rmax, int Tmax) {
+    const LatDesc &d = E->hdesc[0];
+    hipStream_t s = E->stream();
+    const bool sm = E->sm_cur >= 0;
+    const void *sp = sm ? E->sm[E->sm_cur] : E->links;
+    const KArgs a = xcd_args(E);
+    if (transport) {
+        su2::launch_wlines(a, E->f32, E->total_sites, sp, sm ? 0 : 1, Rmax, E->wl_p, E->block, s);
+        su2::launch_wtrace(a, E->f32, Rmax, Tmax, E->total_sites, d.n[3], E->wl_p, E->wpart, E->block, s);
+        return;
+    }
+    const int next = d.n[3] + Tmax;
+    const size_t nst = (size_t)d.ns * next;
+    char *L = (char *)E->wl_p + nst * 32, *w = L + nst * 3 * link_size(E->f32);
+    su2::launch_wgauge(a, E->f32, d.ns, next, E->wl_p, s);
+    su2::launch_wlinks(a, E->f32, d.n, sp, sm ? 0 : 1, next, E->wl_p, L, w, s);
+    for (int k = 0; k < E->wl_npass; ++k)
+        su2::launch_wloops(a, E->f32, E->wl_plan[k], Rmax, next, L, w, E->wpart, s);
+}
+
 su2_status su2_wilson_loops(su2_lattice E, int Rmax, int Tmax, double *out) {
     CHK(enter(E));
     const LatDesc &d = E->hdesc[0];
     const int smin = std::min(d.n[0], std::min(d.n[1], d.n[2]));
     if (!out || Rmax < 1 || Tmax < 1 || Rmax > smin || Tmax > d.n[3] || Tmax > 32) return SU2_EINVAL;
-    if (E->wl_plan_r != Rmax || E->wl_plan_t != Tmax) {
-        E->wl_plan_r = 0;
-        int grid = 0, step = 16, k = 0;
-        while (step * k < Tmax) {
-            if (su2::wloops_plan(E->f32, d.n, Rmax, Tmax, step * k, step, E->wl_plan[k])) {
-                grid = std::max(grid, E->wl_plan[k++].grid);
-            } else {  // long lines: fewer times at once
-                if (step == 4) return SU2_ENOMEM;
-                step /= 2, grid = k = 0;
-            }
-        }
-        E->wl_npass = k;
-        while (k > 0) E->wl_plan[--k].grid = grid;
-        E->wl_plan_r = Rmax, E->wl_plan_t = Tmax;
+    bool transport = su2::wloops_transport(E->f32, d.n, Rmax, Tmax);
+    int nparts = 0;
+    su2_status st = wilson_reserve(E, transport, Rmax, Tmax, &nparts);
+    if (st == SU2_ENOMEM) {  // the other way's buffers may be smaller
+        transport = !transport;
+        st = wilson_reserve(E, transport, Rmax, Tmax, &nparts);
     }
-    const su2::WPlan *plan = E->wl_plan;
-    const int npass = E->wl_npass;
-    const int nparts = plan[0].grid;
-    // per spatial site and time: the prefix product (32 bytes), three links
-    // in its gauge and their weights
-    const int next = d.n[3] + Tmax;
-    const size_t nst = (size_t)d.ns * next, gb = nst * (32 + 3 * (E->f32 ? 20 : 40));
-    CHK(grow(E, &E->wl_p, &E->wl_p_bytes, gb));
-    CHK(grow(E, &E->wpart, &E->wpart_bytes, sizeof(double) * 2 * (size_t)Rmax * nparts * Tmax));
+    CHK(st);
     CHK(ensure_series(E, Rmax * Tmax));
     hipStream_t s = E->stream();
-    const bool sm = E->sm_cur >= 0;
-    const KArgs a = kargs(E);
-    char *L = (char *)E->wl_p + nst * 32, *w = L + nst * 3 * link_size(E->f32);
     Timed t(E, SU2_K_WILSON, s);
-    su2::launch_wgauge(a, E->f32, d.ns, next, E->wl_p, s);
-    su2::launch_wlinks(a, E->f32, d.n, sm ? E->sm[E->sm_cur] : E->links, sm ? 0 : 1, next, E->wl_p, L, w, s);
-    for (int k = 0; k < npass; ++k) su2::launch_wloops(a, E->f32, plan[k], Rmax, next, L, w, E->wpart, s);
+    wilson_launch(E, transport, Rmax, Tmax);
     su2::launch_wfinal(E->ddesc, nparts, Rmax, Tmax, E->wpart, E->dser, E->st, E->derr, s);
     t.done(s);
-    const su2_status st = finish(E, true);
+    st = finish(E, true);
     if (st != SU2_EDEVICE) std::memcpy(out, E->hser, sizeof(double) * Rmax * Tmax);
     return st;
 }

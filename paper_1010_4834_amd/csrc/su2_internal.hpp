@@ -148,6 +148,15 @@ void launch_wlinks(const KArgs &a, bool f32, const int *n, const void *sp, int s
                    void *w, hipStream_t s);
 void launch_wloops(const KArgs &a, bool f32, const WPlan &p, int Rmax, int next, const void *L, const void *w,
                    double *part, hipStream_t s);
+// The same by transport: the lines of every R <= Rmax (3 Rmax V quaternions),
+// then the traces, wtrace_groups() partials per (R, T).
+void launch_wlines(const KArgs &a, bool f32, long long V, const void *sp, int sp_raw, int Rmax, void *sl, int block,
+                   hipStream_t s);
+void launch_wtrace(const KArgs &a, bool f32, int Rmax, int Tmax, long long V, int Nt, const void *sl, double *part,
+                   int block, hipStream_t s);
+int wtrace_groups(long long V, int block);
+// Whether a call goes by transport.
+bool wloops_transport(bool f32, const int *n, int Rmax, int Tmax);
 void launch_wfinal(const LatDesc *desc, int nparts, int Rmax, int Tmax, const double *part, double *out,
                    const DevState *st, unsigned *err, hipStream_t s);
 

@@ -1743,7 +1743,157 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64, 512), amdgpu_waves_per
     }
 }
 
-// One block per (R, T): fixed-order sum over the k_wloops workgroups'
+// ---------------------------------------------------------------------------
+// Wilson loops by transport: the temporal sides carried around each loop.
+// Nothing is prepared but the spatial lines of the R asked for, so it is the
+// shorter way for few (R, T) and for small time slices over many times
+// (wloops_transport has the line between the two and figures), and its lines
+// are the smaller buffer where the other is not to be had.  Spatial lines first:
+// S_mu(x;R) = U_mu(x) .. U_mu(x+(R-1)mu), stored per site as Q<T> arrays
+// sl[(mu*Rmax + R-1)*V + s].  `sp` / `sp_raw`: the spatial links (smeared
+// buffer or raw links).  Temporal lines are not stored: the trace kernel
+// builds them by transport from the raw temporal links.
+template <class T>
+__global__ __launch_bounds__(256) void k_wlines(KArgs a, const void *sp, int sp_raw, int Rmax, Q<T> *sl) {
+    const LatDesc d = load_desc(a.desc);
+    const Blocks<T, 3> Bs = blocks<T, 3>(sp, sp_raw ? d.off : d.soff, d.vh);
+    const int V = 2 * d.vh;
+    for_each_tile(a.ntiles, a.xcd_remap, [&](int tile) {
+        const int s = tile * (int)blockDim.x + (int)threadIdx.x;
+        if (s >= V) return;
+        int c[4], r = s;
+        udiv(r, d.n[0], d.inv_nx, r, c[0]);
+        udiv(r, d.n[1], d.inv_ny, r, c[1]);
+        udiv(r, d.n[2], d.inv_nz, c[3], c[2]);
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu) {
+            const int st = mu == 0 ? 1 : mu == 1 ? d.n[0] : d.n[0] * d.n[1];
+            Q<T> P = qone<T>();
+            int cm = c[mu];
+            for (int R = 1; R <= Rmax; ++R) {
+                const int y = s + (cm - c[mu]) * st;
+                const int par = (c[0] + c[1] + c[2] + c[3] - c[mu] + cm) & 1;
+                P = qmul(P, lds_(Bs, mu, par, (uint32_t)y >> 1));
+                sl[((long long)mu * Rmax + R - 1) * V + s] = P;
+                cm = (cm + 1 == d.n[mu]) ? 0 : cm + 1;
+            }
+        }
+    });
+}
+
+// W(R,T) partials: blockIdx.y = R-1; per site x and spatial mu the loop
+// 1/2 Tr[S(x;R) T(x+R mu;T) S(x+T t;R)^dag T(x;T)^dag] = 1/2 Tr[A_T S(x+T t;R)^dag]
+// with A_T = T(x;T)^dag S(x;R) T(x+R mu;T), built by transport up the two
+// temporal sides: A_0 = S(x;R), A_T = U_t(x+(T-1)t)^dag A_{T-1} U_t(x+R mu+(T-1)t).
+// Temporal links come from the raw link buffer, the spatial lines from sl.
+//
+// A lane owns a column of NC sites x_j = x_0 + j t (j < NC; NC divides Nt)
+// of lattice 0 and takes the three directions mu one after another: at
+// temporal offset m from x_0 every column site with step k = m - j < Tmax
+// applies the same two temporal links and meets the same spatial line at
+// x_0 + (m+1) t, so each is loaded once per column instead of once per site
+// (NC + Tmax - 1 offsets of three loads per mu).  Column q = (spatial site
+// q % Ns, t block q / Ns); column tile i is columns [i B, (i+1) B) for block
+// size B.  A workgroup walks its share of the column tiles (a fixed
+// assignment), each lane summing in binary64, then one compensated block sum
+// per (R, workgroup, T).
+template <class T, int TMAX, int NC>
+__device__ __forceinline__ void wtrace_body(const KArgs &a, int Rmax, int Tmax, int ncols, int nctiles,
+                                            const Q<T> *sl, double *part) {
+    __shared__ DD lds[TMAX * 4];
+    const int R = blockIdx.y + 1;
+    double sum[TMAX];
+#pragma unroll
+    for (int k = 0; k < TMAX; ++k) sum[k] = 0.0;
+    const LatDesc d = load_desc(a.desc);
+    const Blocks<T, 4> B = blocks<T, 4>(a.links, d.off, d.vh);
+    const long long V = 2LL * d.vh;
+    const Q<T> *slR = sl + (long long)(R - 1) * V;
+    const long long mstride = (long long)Rmax * V;
+    for (TileWalk w(nctiles, a.xcd_remap); w.ok(); w.next()) {
+        const int q = w.tile() * (int)blockDim.x + (int)threadIdx.x;
+        if (q >= ncols) continue;
+        // q = sp + Ns tb: spatial site sp = x + Nx (y + Ny z), t0 = NC tb
+        int c[3], r, tb, sp;
+        udiv(q, d.n[0], d.inv_nx, r, c[0]);
+        udiv(r, d.n[1], d.inv_ny, r, c[1]);
+        udiv(r, d.n[2], d.inv_nz, tb, c[2]);
+        sp = q - tb * d.ns;
+        const int t0 = NC * tb;
+        const int s0 = sp + t0 * d.ns;  // site of x_0
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu) {
+            const int st = mu == 0 ? 1 : mu == 1 ? d.n[0] : d.n[0] * d.n[1];
+            int cm = c[mu] + R;
+            if (cm >= d.n[mu]) cm -= d.n[mu];
+            const int sR = s0 + (cm - c[mu]) * st;  // x_0 + R mu
+            Q<T> A[NC];
+#pragma unroll
+            for (int j = 0; j < NC; ++j) A[j] = slR[mu * mstride + s0 + j * d.ns];
+            // parity of x_0 + m t and of x_0 + R mu + m t (R flips it when odd)
+            const int p0 = (c[0] + c[1] + c[2] + t0) & 1, pR = p0 ^ (R & 1);
+            int tm = t0;  // t of x_0 + m t
+#pragma unroll
+            for (int m = 0; m < NC + TMAX - 1; ++m) {
+                if (m < NC + Tmax - 1) {
+                    const int dt = (tm - t0) * d.ns;  // x_0 + m t = s0 + dt
+                    const int pm = (p0 + m) & 1, pRm = (pR + m) & 1;
+                    const Q<T> ua = qdag(lds_(B, 3, pm, (uint32_t)(s0 + dt) >> 1));
+                    const Q<T> ub = lds_(B, 3, pRm, (uint32_t)(sR + dt) >> 1);
+                    tm = (tm + 1 == d.n[3]) ? 0 : tm + 1;
+                    const Q<T> top = slR[mu * mstride + s0 + (tm - t0) * d.ns];  // S(x_0 + (m+1) t; R)
+#pragma unroll
+                    for (int j = 0; j < NC; ++j) {
+                        const int k = m - j;
+                        if (k >= 0 && k < TMAX && k < Tmax) {
+                            A[j] = qmul(qmul(ua, A[j]), ub);
+                            sum[k] += (double)half_tr_xyd(A[j], top);
+                        }
+                    }
+                }
+            }
+        }
+    }
+    // Wavefront sums by binary64 butterflies in a fixed order (each lane holds
+    // a plain binary64 sum; a compensated butterfly cost as much as a tenth of
+    // the kernel's instructions), then the workgroup's wavefronts combined by
+    // compensated sums in thread 0.
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
+#pragma unroll
+    for (int k = 0; k < TMAX; ++k) {
+        const double ws = wave_sum_f64(sum[k]);
+        if (lane == 0) lds[wave * TMAX + k] = DD{ws, 0.0};
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int k = 0; k < TMAX; ++k)
+            if (k < Tmax) {
+                DD acc = lds[k];
+                for (int w = 1; w < nw; ++w) acc = dd_add(acc, lds[w * TMAX + k]);
+                double *p = part + 2 * (((long long)(R - 1) * Tmax + k) * gridDim.x + blockIdx.x);
+                p[0] = acc.hi;
+                p[1] = acc.lo;
+            }
+}
+
+// Binary32 traces are held to 128 registers (4 waves per SIMD): under that
+// bound the compiler also schedules the unrolled offsets without copying the
+// binary64 sums around their run-time bounds, 10% faster at 24^3 x 48 than
+// the same code unbounded (122 registers, also 4 waves).  Binary64 traces
+// need more registers and run unbounded (the bound would spill).
+template <int TMAX, int NC>
+__global__ __launch_bounds__(256, 4) void k_wtrace(KArgs a, int Rmax, int Tmax, int ncols, int nctiles,
+                                                   const Q<float> *sl, double *part) {
+    wtrace_body<float, TMAX, NC>(a, Rmax, Tmax, ncols, nctiles, sl, part);
+}
+template <int TMAX, int NC>
+__global__ __launch_bounds__(256) void k_wtrace64(KArgs a, int Rmax, int Tmax, int ncols, int nctiles,
+                                                  const Q<double> *sl, double *part) {
+    wtrace_body<double, TMAX, NC>(a, Rmax, Tmax, ncols, nctiles, sl, part);
+}
+
+// One block per (R, T): fixed-order sum over the workgroups'
 // partials (nparts per (R, T)), written straight into mapped host memory, the
 // error word with them.
 __global__ __launch_bounds__(256) void k_wfinal(const LatDesc *desc, int nparts, const double *part, double *out,
@@ -2016,6 +2166,71 @@ void launch_wlinks(const KArgs &a, bool f32, const int *n, const void *sp, int s
     }
 }
 
+static int wlines_tiles(long long V, int block) { return (int)((V + block - 1) / block); }
+
+void launch_wlines(const KArgs &arg, bool f32, long long V, const void *sp, int sp_raw, int Rmax, void *sl, int block,
+                   hipStream_t s) {
+    KArgs a = arg;
+    a.ntiles = wlines_tiles(V, block);
+    if (f32)
+        hipLaunchKernelGGL((k_wlines<float>), grid_of(a, 0), dim3(block), 0, s, a, sp, sp_raw, Rmax,
+                           (Q<float> *)sl);
+    else
+        hipLaunchKernelGGL((k_wlines<double>), grid_of(a, 0), dim3(block), 0, s, a, sp, sp_raw, Rmax,
+                           (Q<double> *)sl);
+}
+
+// Workgroups per R of the Wilson trace: enough to fill the chip a few times
+// over, each taking several column tiles (a multiple of 8, one share per XCD).
+int wtrace_groups(long long V, int block) {
+    const int g = ((wlines_tiles(V, block) + 7) / 8) * 8;
+    return g < 1024 ? (g < 8 ? 8 : g) : 1024;
+}
+
+// Column height of the Wilson trace: in binary32 with up to 16 time steps,
+// 6 or else 4 when it divides Nt (the same four waves per SIMD; 8 would
+// spill registers); otherwise 2 (extents are even).
+template <class T> static int wtrace_nc(int Nt, int Tmax) {
+    if (sizeof(T) == 4 && Tmax <= 16) return Nt % 6 == 0 ? 6 : Nt % 4 == 0 ? 4 : 2;
+    return 2;
+}
+
+template <class T, int NC>
+static void launch_wtrace_nc(const KArgs &a, int Rmax, int Tmax, long long V, const void *sl, double *part,
+                             int block, hipStream_t s) {
+    const dim3 g((unsigned)wtrace_groups(V, block), (unsigned)Rmax), b((unsigned)block);
+    const int ncols = (int)(V / NC), nct = (ncols + block - 1) / block;
+    const Q<T> *l = (const Q<T> *)sl;
+    if constexpr (sizeof(T) == 4) {
+        if (Tmax <= 4) hipLaunchKernelGGL((k_wtrace<4, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
+        else if (Tmax <= 8) hipLaunchKernelGGL((k_wtrace<8, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
+        else if (Tmax <= 16) hipLaunchKernelGGL((k_wtrace<16, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
+        else if constexpr (NC == 2) hipLaunchKernelGGL((k_wtrace<32, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
+    } else {
+        if (Tmax <= 4) hipLaunchKernelGGL((k_wtrace64<4, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
+        else if (Tmax <= 8) hipLaunchKernelGGL((k_wtrace64<8, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
+        else if (Tmax <= 16) hipLaunchKernelGGL((k_wtrace64<16, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
+        else if constexpr (NC == 2) hipLaunchKernelGGL((k_wtrace64<32, NC>), g, b, 0, s, a, Rmax, Tmax, ncols, nct, l, part);
+    }
+}
+
+template <class T>
+static void launch_wtrace_t(const KArgs &a, int Rmax, int Tmax, long long V, int Nt, const void *sl, double *part,
+                            int block, hipStream_t s) {
+    const int nc = wtrace_nc<T>(Nt, Tmax);
+    if constexpr (sizeof(T) == 4) {
+        if (nc == 6) return launch_wtrace_nc<T, 6>(a, Rmax, Tmax, V, sl, part, block, s);
+        if (nc == 4) return launch_wtrace_nc<T, 4>(a, Rmax, Tmax, V, sl, part, block, s);
+    }
+    launch_wtrace_nc<T, 2>(a, Rmax, Tmax, V, sl, part, block, s);
+}
+
+void launch_wtrace(const KArgs &a, bool f32, int Rmax, int Tmax, long long V, int Nt, const void *sl, double *part,
+                   int block, hipStream_t s) {
+    if (f32) launch_wtrace_t<float>(a, Rmax, Tmax, V, Nt, sl, part, block, s);
+    else launch_wtrace_t<double>(a, Rmax, Tmax, V, Nt, sl, part, block, s);
+}
+
 // Work split of the Wilson loops of times toff < T <= toff + Tp.  Among the
 // splits that fit (elements in WL_KE per lane, rows in one per lane, LDS) it
 // takes the least modelled time: wavefront instructions per R of a unit times
@@ -2096,6 +2311,30 @@ bool wl_plan_at(bool f32, const int *n, int Rmax, int toff, int Tp, int TM, int 
     return true;
 }
 }  // namespace
+
+// Which way a call of the Wilson loops takes: the shorter of two estimates in us
+// (V in millions of sites), fitted to 732 calls of both, in both precisions, on
+// 24 lattices of 4^4 to 64^3 x 16 and 2^3 x 4096 sites, R from 1 to 12, T from 1 to
+// 32.  By transport: the lines and traces of every R, cheaper where the lines of
+// a few time slices stay in an L2, and a chain of Tmax steps.  In the gauge: the
+// rotation of Nt + Tmax times, its bytes, its chain of 64 times at a time and its
+// 32 x 32 tiles (few sites each where x and y are short), then the traces.
+// us by transport and in the gauge, binary32: 64^3 x 16 156 and 343 (R = T = 1);
+// 24^3 x 48 45 and 64 (R = T = 1), 59 and 68 (2), 101 and 74 (4); 8^3 x 12 32 and 31
+// (2), 49 and 35 (R = 4, T = 8); 4^3 x 2048 92 and 173 (R = 4, T = 16).
+bool wloops_transport(bool f32, const int *n, int Rmax, int Tmax) {
+    const auto tiles = [](int k) { return (k + 31) / 32; };
+    const long long slice = (long long)n[0] * n[1] * n[2];
+    const double ns = 1e-6 * slice, V = ns * n[3], R = Rmax, T = Tmax, next = n[3] + Tmax;
+    const double chain = (n[3] + Tmax + 63) / 64;
+    const double wg = 1e-4 * next * tiles(n[0]) * std::max(tiles(n[1]) * n[2], tiles(n[2]) * n[1]);
+    const bool near = slice <= 2048;
+    if (f32)
+        return 25.2 + R * V * (20.5 + (near ? 2.02 : 3.10) * T) + 1.84 * T <
+               27.0 + 35.0 * ns * next + (2.77 + 234.0 * ns) * chain + R * V * (3.46 + 0.443 * T) + 1.22 * R + 25.7 * wg;
+    return 24.5 + R * V * (46.9 + (near ? 5.81 : 10.3) * T) + 1.90 * T <
+           1.04 * (25.4 + 61.1 * ns * next + (3.57 + 333.0 * ns) * chain + R * V * (6.63 + 0.815 * T) + 1.27 * R + 52.4 * wg);
+}
 
 bool wloops_plan(bool f32, const int *n, int Rmax, int Tmax, int toff, int step, WPlan &out) {
     const int Tp = std::min(step, Tmax - toff), TM = Tp <= 4 ? 4 : Tp <= 8 ? 8 : 16;

@@ -26,7 +26,7 @@ std::map<const void *, std::string> &kernels() {
 }
 std::vector<Launch> g_launches;
 std::map<std::string, std::vector<int>> g_attrs;
-long long g_limit = -1, g_countdown = -1;  // see stub_malloc_limit, stub_malloc_countdown
+long long g_limit = -1, g_countdown = -1, g_room = -1;  // see stub_malloc_limit, _countdown, _room
 struct Conf {
     dim3 g, b;
     size_t lds;
@@ -59,6 +59,8 @@ extern "C" {
 void stub_malloc_limit(long long bytes) { g_limit = bytes; }
 // The n-th allocation from now fails, and no other (negative: none).
 void stub_malloc_countdown(long long n) { g_countdown = n; }
+// The next n allocations succeed, later ones do not (negative: all).
+void stub_malloc_room(long long n) { g_room = n; }
 void stub_clear() { g_launches.clear(); }
 int stub_launches() { return (int)g_launches.size(); }
 const char *stub_name(int i) { return g_launches[i].name.c_str(); }
@@ -107,6 +109,8 @@ hipError_t hipMalloc(void **p, size_t bytes) {
     *p = nullptr;
     if (g_limit >= 0 && (long long)bytes > g_limit) return hipErrorOutOfMemory;
     if (g_countdown >= 0 && g_countdown-- == 0) return hipErrorOutOfMemory;
+    if (g_room == 0) return hipErrorOutOfMemory;
+    if (g_room > 0) --g_room;
     *p = std::calloc(1, bytes);
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }

@@ -45,7 +45,8 @@ class Host:
     def __init__(self, folder):
         self.lib = build(str(folder))
         self.lib.stub_name.restype = C.c_char_p
-        self.lib.stub_malloc_limit.argtypes = self.lib.stub_malloc_countdown.argtypes = [C.c_longlong]
+        for f in ("limit", "countdown", "room"):
+            getattr(self.lib, "stub_malloc_" + f).argtypes = [C.c_longlong]
         self.lib.su2_create.argtypes = [C.c_int] * 5 + [C.c_uint64, C.c_int, C.c_void_p, C.c_size_t, C.c_void_p]
         self.lib.su2_ensemble_run.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_uint64, C.c_void_p, C.c_void_p]
         self.lib.su2_ape_smear.argtypes = [C.c_void_p, C.c_double, C.c_int]

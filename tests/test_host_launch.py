@@ -2,7 +2,7 @@
 HIP runtime."""
 import pytest
 
-from tests.host_lib import F32, F64, OK, host_lib
+from tests.host_lib import ENOMEM, F32, F64, OK, host_lib
 
 
 @pytest.fixture
@@ -22,3 +22,54 @@ def test_lds_limits_do_not_depend_on_the_call(host):
     assert host.wilson(h, 80, 12) == OK and host.wilson(h, 82, 8) == OK
     assert host.lib.su2_destroy(h) == OK
     assert host.lib.stub_attrs() >= 2 and host.lib.stub_attr_changes() == 0
+
+
+def wilson_kernels(host, dims, prec, R, T, limit=-1):
+    """Kernels of one call, as (name, number of times): 'wloops4' takes up to 4
+    times at once, 'wtrace' is the other way."""
+    h = host.create(dims, prec)
+    host.lib.stub_clear()
+    host.lib.stub_malloc_limit(limit)
+    st = host.wilson(h, R, T)
+    host.lib.stub_malloc_limit(-1)
+    assert host.lib.stub_nulls() == 0 and host.lib.su2_destroy(h) == OK
+    names = ["wloops" + n.split("wloopsI")[1].split("Li")[1].split("E")[0] if "wloops" in n else
+             "wtrace" if "wtrace" in n else n for n in host.names() if "wloops" in n or "wtrace" in n]
+    return st, sorted((n, names.count(n)) for n in set(names))
+
+
+@pytest.mark.parametrize("dims,R,T,f64,f32", [
+    ((24, 24, 24, 48), 12, 16, "wloops16", "wloops16"),
+    ((24, 24, 24, 48), 4, 4, "wloops4", "wloops4"),
+    ((24, 24, 24, 48), 1, 1, "wtrace", "wtrace"),       # few (R, T): the rotation costs more than it saves
+    ((64, 64, 64, 16), 1, 16, "wloops16", "wtrace"),
+    ((4, 4, 4, 2048), 4, 16, "wtrace", "wtrace"),       # few sites over many times
+    ((8, 8, 8, 12), 4, 6, "wloops8", "wloops8"),
+    ((2, 2, 2, 2), 1, 1, "wtrace", "wtrace"),
+])
+def test_wilson_ways(host, dims, R, T, f64, f32):
+    for prec, kernel in ((F64, f64), (F32, f32)):
+        assert wilson_kernels(host, dims, prec, R, T) == (OK, [(kernel, 1)])
+
+
+@pytest.mark.parametrize("dims,R,T,limit,kernel", [
+    ((24, 24, 24, 48), 2, 8, 66 << 20, "wtrace"),   # 71 MB of rotated links, 64 MB of lines
+    ((48, 48, 48, 4), 4, 1, 60 << 20, "wloops4"),   # 85 MB of lines, 51 MB of rotated links
+])
+def test_wilson_other_way_without_memory(host, dims, R, T, limit, kernel):
+    st, names = wilson_kernels(host, dims, F32, R, T)
+    assert st == OK and names != [(kernel, 1)]
+    assert wilson_kernels(host, dims, F32, R, T, limit) == (OK, [(kernel, 1)])
+    assert wilson_kernels(host, dims, F32, R, T, 1 << 20)[0] == ENOMEM
+
+
+@pytest.mark.parametrize("n,nt,T,prec,kernels", [
+    (80, 32, 32, F64, [("wloops16", 2)]),
+    (82, 12, 12, F64, [("wloops4", 1), ("wloops8", 1)]),
+    (138, 16, 16, F64, [("wloops4", 4)]),
+    (110, 16, 16, F32, [("wloops16", 1)]),
+    (112, 16, 16, F32, [("wloops8", 2)]),
+])
+def test_long_lines_take_fewer_times(host, n, nt, T, prec, kernels):
+    """Rmax = n: the sums of sixteen times leave no room for the lines."""
+    assert wilson_kernels(host, (n, n, n, nt), prec, n, T) == (OK, kernels)

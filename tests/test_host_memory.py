@@ -11,16 +11,18 @@ def host(tmp_path_factory):
     yield h
     h.lib.stub_malloc_countdown(-1)
     h.lib.stub_malloc_limit(-1)
+    h.lib.stub_malloc_room(-1)
 
 
-@pytest.mark.parametrize("nth", [0, 1])
-def test_wilson_buffers(host, nth):
-    """The nth of the buffers that a larger call needs cannot be had: the
-    smaller call that fitted before allocates its own again."""
+@pytest.mark.parametrize("room", [0, 1])
+def test_wilson_buffers(host, room):
+    """The first or the second of the buffers that a larger call needs cannot be
+    had: the smaller call that fitted before allocates its own again."""
     h = host.create((4, 4, 4, 32))
     assert host.wilson(h, 2, 4) == OK
-    host.lib.stub_malloc_countdown(nth)
+    host.lib.stub_malloc_room(room)
     assert host.wilson(h, 4, 32) == ENOMEM
+    host.lib.stub_malloc_room(-1)
     host.lib.stub_clear()
     for R, T in ((2, 4), (4, 32)):
         assert host.wilson(h, R, T) == OK
