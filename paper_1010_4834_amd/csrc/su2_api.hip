@@ -112,7 +112,8 @@ struct su2_ensemble_s {
     size_t hser_cap = 0;            // doubles
     double *run_plaq = nullptr, *run_poly = nullptr;  // device targets of the current run
     int run_nm = 0;
-    // mapped host words: [0] the error word written by the device, [4..7]
+    // mapped host words: [0] the error word written by the device, [1] the
+    // state's off_group after Wilson loops, [4..7]
     // the run state (seed low and high, sweep, run base) written by the host
     // for the first node of a captured run
     unsigned *herr = nullptr, *derr = nullptr;
@@ -1657,24 +1658,28 @@ static su2_status wilson_reserve(su2_ensemble_s *E, bool transport, int Rmax, in
     return grow(E, &E->wpart, &E->wpart_bytes, sizeof(double) * 2 * (size_t)Rmax * *nparts * Tmax);
 }
 
-static void wilson_launch(su2_ensemble_s *E, bool transport, int Rmax, int Tmax) {
+static su2_status wilson_run(su2_ensemble_s *E, bool transport, int Rmax, int Tmax, int nparts) {
     const LatDesc &d = E->hdesc[0];
     hipStream_t s = E->stream();
     const bool sm = E->sm_cur >= 0;
     const void *sp = sm ? E->sm[E->sm_cur] : E->links;
     const KArgs a = xcd_args(E);
+    Timed t(E, SU2_K_WILSON, s);
     if (transport) {
         su2::launch_wlines(a, E->f32, E->total_sites, sp, sm ? 0 : 1, Rmax, E->wl_p, E->block, s);
         su2::launch_wtrace(a, E->f32, Rmax, Tmax, E->total_sites, d.n[3], E->wl_p, E->wpart, E->block, s);
-        return;
+    } else {
+        const int next = d.n[3] + Tmax;
+        const size_t nst = (size_t)d.ns * next;
+        char *L = (char *)E->wl_p + nst * 32, *w = L + nst * 3 * link_size(E->f32);
+        su2::launch_wgauge(a, E->f32, d.ns, next, E->wl_p, s);
+        su2::launch_wlinks(a, E->f32, d.n, sp, sm ? 0 : 1, next, E->wl_p, L, w, s);
+        for (int k = 0; k < E->wl_npass; ++k)
+            su2::launch_wloops(a, E->f32, E->wl_plan[k], Rmax, next, L, w, E->wpart, s);
     }
-    const int next = d.n[3] + Tmax;
-    const size_t nst = (size_t)d.ns * next;
-    char *L = (char *)E->wl_p + nst * 32, *w = L + nst * 3 * link_size(E->f32);
-    su2::launch_wgauge(a, E->f32, d.ns, next, E->wl_p, s);
-    su2::launch_wlinks(a, E->f32, d.n, sp, sm ? 0 : 1, next, E->wl_p, L, w, s);
-    for (int k = 0; k < E->wl_npass; ++k)
-        su2::launch_wloops(a, E->f32, E->wl_plan[k], Rmax, next, L, w, E->wpart, s);
+    su2::launch_wfinal(E->ddesc, nparts, Rmax, Tmax, E->wpart, E->dser, E->st, E->derr, s);
+    t.done(s);
+    return finish(E, true);
 }
 
 su2_status su2_wilson_loops(su2_lattice E, int Rmax, int Tmax, double *out) {
@@ -1691,13 +1696,15 @@ su2_status su2_wilson_loops(su2_lattice E, int Rmax, int Tmax, double *out) {
     }
     CHK(st);
     CHK(ensure_series(E, Rmax * Tmax));
-    hipStream_t s = E->stream();
-    Timed t(E, SU2_K_WILSON, s);
-    wilson_launch(E, transport, Rmax, Tmax);
-    su2::launch_wfinal(E->ddesc, nparts, Rmax, Tmax, E->wpart, E->dser, E->st, E->derr, s);
-    t.done(s);
-    st = finish(E, true);
-    if (st != SU2_EDEVICE) std::memcpy(out, E->hser, sizeof(double) * Rmax * Tmax);
+    st = wilson_run(E, transport, Rmax, Tmax, nparts);
+    if (st == SU2_EDEVICE) return st;
+    if (!transport && E->herr[1]) {  // temporal lines off unit norm
+        CHK(wilson_reserve(E, true, Rmax, Tmax, &nparts));
+        const su2_status again = wilson_run(E, true, Rmax, Tmax, nparts);
+        if (again != SU2_OK) st = again;
+        if (st == SU2_EDEVICE) return st;
+    }
+    std::memcpy(out, E->hser, sizeof(double) * Rmax * Tmax);
     return st;
 }
 

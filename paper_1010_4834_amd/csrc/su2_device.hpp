@@ -50,6 +50,7 @@ struct DevState {
     unsigned int next;      // sweep word of the following sweep
     unsigned int run_base;  // sweep index of the first sweep of a series
     unsigned int err;       // non-finite staples and sampler try-cap hits
+    unsigned int off_group; // Wilson loops: temporal lines too far off unit norm for their gauge
 };
 
 // A tile: lattice index and first index (half-site, spatial site or site).

@@ -1358,7 +1358,7 @@ __global__ __launch_bounds__(ape_slice(sizeof(T) == 4)) void k_ape_slices(KArgs 
 // ---------------------------------------------------------------------------
 // Wilson loops (paper Sec. 2, W(R,T)) in the temporal gauge.  With the
 // prefix products P(x,t) = U_4(x,0) .. U_4(x,t-1) of a spatial site's temporal
-// links the loop is, for any links (unitary or not),
+// links the loop is, for temporal links of any norm but zero,
 //   1/2 Tr[S(x,t;R) T(x+R) S(x,t+T;R)^dag T(x)^dag]
 //     = w(x,t) w(x+R,t) Z(x,t;R) . Z(x,t+T;R),
 //   Z(x,t;R) = P(x,t) S(x,t;R) P(x+R,t)^dag,  w = 1/|P|^2,
@@ -1368,7 +1368,11 @@ __global__ __launch_bounds__(ape_slice(sizeof(T) == 4)) void k_ape_slices(KArgs 
 // products over the periodic links, so a loop that wraps needs nothing of its
 // own.  Products of P, the dot products and their sums are binary64; the
 // lines Z are held in link precision.
-//
+// Links in a caller's buffer may have any norm.  Where a |P|^2 is further than
+// 2^-6 from 1 (the links that set_links takes and the sampler leaves stay closer
+// over 15000 times), k_wlinks says so in the state, and the call is made again by
+// transport, which has no use for inverses: 1/|P|^2 would leave binary32, and is
+// infinite behind a zero link.
 template <class T> __device__ __forceinline__ Q<double> qwide(const Q<T> &q) {
     return Q<double>{(double)q.a, (double)q.b, (double)q.c, (double)q.d};
 }
@@ -1386,6 +1390,7 @@ __global__ __launch_bounds__(512) void k_wgauge(KArgs a, int next, double2 *__re
     __shared__ double2 seg[8][2][64];
     const LatDesc d = load_desc(a.desc);
     const Blocks<T, 4> B = blocks<T, 4>(a.links, d.off, d.vh);
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.st->off_group = 0u;  // for k_wlinks
     const int lane = (int)threadIdx.x & 63, wave = uni((int)threadIdx.x >> 6);
     const int xs = min((int)blockIdx.x * 64 + lane, d.ns - 1);  // lanes beyond the lattice repeat its last site
     int r, x, y, z;
@@ -1500,6 +1505,7 @@ __global__ __launch_bounds__(512) void k_wlinks(KArgs a, const void *sp, int sp_
             const Q<double> m = qmul(qmul(Q<double>{al[h].x, al[h].y, ah[h].x, ah[h].y}, qwide(U[h])),
                                      Q<double>{bl[h].x, -bl[h].y, -bh[h].x, -bh[h].y});
             const double n2 = al[h].x * al[h].x + al[h].y * al[h].y + ah[h].x * ah[h].x + ah[h].y * ah[h].y;
+            if (fabs(1.0 - n2) > 0x1p-6) a.st->off_group = 1u;  // not for NaN: the loops are NaN either way
             const T wv = (T)((1.0 - n2) * rcp_newton(n2));
             const Q<T> q{(T)m.a, (T)m.b, (T)m.c, (T)m.d};
             if (mu == 0) {
@@ -1895,7 +1901,7 @@ __global__ __launch_bounds__(256) void k_wtrace64(KArgs a, int Rmax, int Tmax, i
 
 // One block per (R, T): fixed-order sum over the workgroups'
 // partials (nparts per (R, T)), written straight into mapped host memory, the
-// error word with them.
+// error word and off_group with them.
 __global__ __launch_bounds__(256) void k_wfinal(const LatDesc *desc, int nparts, const double *part, double *out,
                                                 const DevState *st, unsigned *err) {
     __shared__ DD lds[4];
@@ -1906,7 +1912,10 @@ __global__ __launch_bounds__(256) void k_wfinal(const LatDesc *desc, int nparts,
     dd_block_sum<1>(acc, lds);
     if (threadIdx.x == 0) {
         out[blockIdx.x] = (acc[0].hi + acc[0].lo) / (6.0 * vh);
-        if (blockIdx.x == 0) *err = st->err;
+        if (blockIdx.x == 0) {
+            err[0] = st->err;
+            err[1] = st->off_group;
+        }
     }
 }
 
