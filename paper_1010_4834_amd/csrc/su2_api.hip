@@ -99,9 +99,10 @@ struct su2_ensemble_s {
     unsigned *fin_cnt = nullptr;    // per-lattice arrival tickets of the final reduction
     double *fin_chunk = nullptr;    // per-workgroup chunk sums of the final reduction
     int fin_chunks = 1;             // workgroups per lattice in the final reduction
-    // single results, written by kernels into mapped host memory (device
-    // address dres)
+    // results of single calls, written by kernels into mapped host memory
+    // (device address dres)
     double *hres = nullptr, *dres = nullptr;
+    size_t hres_cap = 0;            // doubles
 
     int ser_C = 1;                  // chunks per (lattice, sweep) of the series reduction
     double *ser_chunk = nullptr;    // their (hi, lo) pairs
@@ -133,8 +134,12 @@ struct su2_ensemble_s {
     size_t wl_p_bytes = 0;
     double *wpart = nullptr;
     size_t wpart_bytes = 0;
-    su2::WPlan wl_plan[8];          // work split of the last Wilson-loop call, for
-    int wl_plan_r = 0, wl_plan_t = 0, wl_npass = 0;  // these bounds, passes over the times
+    // work splits of the last few bounds of Wilson loops: passes over the times
+    struct WSplit {
+        int Rmax = 0, Tmax = 0, npass = 0;
+        su2::WPlan pass[8];
+    } wl_split[4];
+    int wl_next = 0;  // the one to replace next
 
     uint32_t *trace = nullptr;
 
@@ -615,7 +620,10 @@ su2_status create_common(int n, const int *dims, const double *betas, su2_start 
     }
     CHK(dalloc(E, &E->ddesc, sizeof(LatDesc) * n));
     CHK(dalloc(E, &E->st, sizeof(DevState)));
-    if (host_mapped(E, (void **)&E->hres, (void **)&E->dres, sizeof(double) * 4 * n) != SU2_OK) return SU2_ENOMEM;
+    // four per lattice, and one page at least, which holds the Wilson loops of
+    // 512 (R, T) (a first call that had to allocate them took 30 us more)
+    E->hres_cap = std::max((size_t)4 * n, (size_t)512);
+    CHK(host_mapped(E, (void **)&E->hres, (void **)&E->dres, sizeof(double) * E->hres_cap));
     if (host_mapped(E, (void **)&E->herr, (void **)&E->derr, sizeof(unsigned) * 16) != SU2_OK) return SU2_ENOMEM;
     E->hst.seed = seed;
     E->hst.sweep = 0;
@@ -1625,59 +1633,62 @@ su2_status su2_get_smeared(su2_lattice E, double *host) {
     return get_links_l(E, 0, E->sm[E->sm_cur], 3, host);
 }
 
-// Work split and buffers of the Wilson loops in the temporal gauge or by
-// transport; partials per (R, T).  ENOMEM without room for them.
-static su2_status wilson_reserve(su2_ensemble_s *E, bool transport, int Rmax, int Tmax, int *nparts) {
-    const LatDesc &d = E->hdesc[0];
-    size_t bytes;
-    if (transport) {
-        *nparts = su2::wtrace_groups(E->total_sites, E->block);
-        bytes = (size_t)3 * Rmax * E->total_sites * link_size(E->f32);
-    } else {
-        if (E->wl_plan_r != Rmax || E->wl_plan_t != Tmax) {
-            E->wl_plan_r = 0;
-            int grid = 0, step = 16, k = 0;
-            while (step * k < Tmax) {
-                if (su2::wloops_plan(E->f32, d.n, Rmax, Tmax, step * k, step, E->wl_plan[k])) {
-                    grid = std::max(grid, E->wl_plan[k++].grid);
-                } else {  // long lines: fewer times at once
-                    if (step == 4) return SU2_ENOMEM;
-                    step /= 2, grid = k = 0;
-                }
-            }
-            E->wl_npass = k;
-            while (k > 0) E->wl_plan[--k].grid = grid;
-            E->wl_plan_r = Rmax, E->wl_plan_t = Tmax;
+// Work split of these bounds, nullptr if there is none.
+static const su2_ensemble_s::WSplit *wilson_split(su2_ensemble_s *E, int Rmax, int Tmax) {
+    for (const auto &w : E->wl_split)
+        if (w.Rmax == Rmax && w.Tmax == Tmax) return &w;
+    auto &w = E->wl_split[E->wl_next];
+    w.Rmax = 0;
+    int grid = 0, step = 16, k = 0;
+    while (step * k < Tmax) {
+        if (su2::wloops_plan(E->f32, E->hdesc[0].n, Rmax, Tmax, step * k, step, w.pass[k])) {
+            grid = std::max(grid, w.pass[k++].grid);
+        } else {  // long lines: fewer times at once
+            if (step == 4) return nullptr;
+            step /= 2, grid = k = 0;
         }
-        *nparts = E->wl_plan[0].grid;
-        // per spatial site and time: the prefix product (32 bytes), three links
-        // in its gauge and their weights
-        bytes = (size_t)d.ns * (d.n[3] + Tmax) * (32 + 3 * (E->f32 ? 20 : 40));
     }
+    w.npass = k;
+    while (k > 0) w.pass[--k].grid = grid;
+    w.Rmax = Rmax, w.Tmax = Tmax;
+    E->wl_next = (E->wl_next + 1) % 4;
+    return &w;
+}
+
+// Buffers of the Wilson loops by transport (w null) or in the temporal gauge,
+// for nparts partials per (R, T).
+static su2_status wilson_reserve(su2_ensemble_s *E, const su2_ensemble_s::WSplit *w, int Rmax, int Tmax, int *nparts) {
+    const LatDesc &d = E->hdesc[0];
+    *nparts = w ? w->pass[0].grid : su2::wtrace_groups(E->total_sites, E->block);
+    // in the gauge, per spatial site and time: the prefix product (32 bytes), three
+    // links and their weights
+    const size_t bytes = w ? (size_t)d.ns * (d.n[3] + Tmax) * (32 + 3 * (E->f32 ? 20 : 40))
+                           : (size_t)3 * Rmax * E->total_sites * link_size(E->f32);
     CHK(grow(E, &E->wl_p, &E->wl_p_bytes, bytes));
     return grow(E, &E->wpart, &E->wpart_bytes, sizeof(double) * 2 * (size_t)Rmax * *nparts * Tmax);
 }
 
-static su2_status wilson_run(su2_ensemble_s *E, bool transport, int Rmax, int Tmax, int nparts) {
+static su2_status wilson_run(su2_ensemble_s *E, const su2_ensemble_s::WSplit *w, int Rmax, int Tmax, int nparts,
+                             double *out) {
     const LatDesc &d = E->hdesc[0];
     hipStream_t s = E->stream();
     const bool sm = E->sm_cur >= 0;
     const void *sp = sm ? E->sm[E->sm_cur] : E->links;
     const KArgs a = xcd_args(E);
     Timed t(E, SU2_K_WILSON, s);
-    if (transport) {
+    if (!w) {
         su2::launch_wlines(a, E->f32, E->total_sites, sp, sm ? 0 : 1, Rmax, E->wl_p, E->block, s);
         su2::launch_wtrace(a, E->f32, Rmax, Tmax, E->total_sites, d.n[3], E->wl_p, E->wpart, E->block, s);
     } else {
         const int next = d.n[3] + Tmax;
         const size_t nst = (size_t)d.ns * next;
-        char *L = (char *)E->wl_p + nst * 32, *w = L + nst * 3 * link_size(E->f32);
+        char *L = (char *)E->wl_p + nst * 32, *f = L + nst * 3 * link_size(E->f32);
         su2::launch_wgauge(a, E->f32, d.ns, next, E->wl_p, s);
-        su2::launch_wlinks(a, E->f32, d.n, sp, sm ? 0 : 1, next, E->wl_p, L, w, s);
-        for (int k = 0; k < E->wl_npass; ++k)
-            su2::launch_wloops(a, E->f32, E->wl_plan[k], Rmax, next, L, w, E->wpart, s);
+        su2::launch_wlinks(a, E->f32, d.n, sp, sm ? 0 : 1, next, E->wl_p, L, f, s);
+        for (int k = 0; k < w->npass; ++k)
+            su2::launch_wloops(a, E->f32, w->pass[k], Rmax, next, L, f, E->wpart, s);
     }
-    su2::launch_wfinal(E->ddesc, nparts, Rmax, Tmax, E->wpart, E->dser, E->st, E->derr, s);
+    su2::launch_wfinal(E->ddesc, nparts, Rmax, Tmax, E->wpart, out, E->st, E->derr, s);
     t.done(s);
     return finish(E, true);
 }
@@ -1687,24 +1698,27 @@ su2_status su2_wilson_loops(su2_lattice E, int Rmax, int Tmax, double *out) {
     const LatDesc &d = E->hdesc[0];
     const int smin = std::min(d.n[0], std::min(d.n[1], d.n[2]));
     if (!out || Rmax < 1 || Tmax < 1 || Rmax > smin || Tmax > d.n[3] || Tmax > 32) return SU2_EINVAL;
-    bool transport = su2::wloops_transport(E->f32, d.n, Rmax, Tmax);
+    const bool transport = su2::wloops_transport(E->f32, d.n, Rmax, Tmax);
+    const su2_ensemble_s::WSplit *w = transport ? nullptr : wilson_split(E, Rmax, Tmax);
     int nparts = 0;
-    su2_status st = wilson_reserve(E, transport, Rmax, Tmax, &nparts);
-    if (st == SU2_ENOMEM) {  // the other way's buffers may be smaller
-        transport = !transport;
-        st = wilson_reserve(E, transport, Rmax, Tmax, &nparts);
+    su2_status st = wilson_reserve(E, w, Rmax, Tmax, &nparts);
+    if (st == SU2_ENOMEM && (w || transport)) {  // the other way's buffers may be smaller
+        w = w ? nullptr : wilson_split(E, Rmax, Tmax);
+        if (w || !transport) st = wilson_reserve(E, w, Rmax, Tmax, &nparts);
     }
     CHK(st);
-    CHK(ensure_series(E, Rmax * Tmax));
-    st = wilson_run(E, transport, Rmax, Tmax, nparts);
+    const bool own = (size_t)Rmax * Tmax <= E->hres_cap;
+    if (!own) CHK(ensure_series(E, Rmax * Tmax));
+    double *const res = own ? E->dres : E->dser;
+    st = wilson_run(E, w, Rmax, Tmax, nparts, res);
     if (st == SU2_EDEVICE) return st;
-    if (!transport && E->herr[1]) {  // temporal lines off unit norm
-        CHK(wilson_reserve(E, true, Rmax, Tmax, &nparts));
-        const su2_status again = wilson_run(E, true, Rmax, Tmax, nparts);
+    if (w && E->herr[1]) {  // temporal lines off unit norm
+        CHK(wilson_reserve(E, nullptr, Rmax, Tmax, &nparts));
+        const su2_status again = wilson_run(E, nullptr, Rmax, Tmax, nparts, res);
         if (again != SU2_OK) st = again;
         if (st == SU2_EDEVICE) return st;
     }
-    std::memcpy(out, E->hser, sizeof(double) * Rmax * Tmax);
+    std::memcpy(out, own ? E->hres : E->hser, sizeof(double) * Rmax * Tmax);
     return st;
 }
 

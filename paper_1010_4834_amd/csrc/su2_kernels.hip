@@ -2262,61 +2262,57 @@ bool wl_plan_at(bool f32, const int *n, int Rmax, int toff, int Tp, int TM, int 
     WPlan p{};
     p.block = block, p.nc = nc, p.toff = toff, p.Tp = Tp;
     const int ns = n[0] * n[1] * n[2], Nt = n[3];
-    double total = 0;
+    const size_t sums = wl_bytes(f32, 0, block, Rmax, TM);
+    if (sums >= lds_max) return false;
+    // LDS elements of a unit at most
+    const int cap = (int)std::min<size_t>(wl_ke(f32), (lds_max - sums) / (f32 ? 20 : 40) / block) * block;
+    const auto rows = [&](int NB) { return NB * nc + std::min(toff, NB * nc - 1) + TM; };
+    const double wv = block / 64, fixed = (f32 ? 6.0 : 3.0) * (nc + TM) + 4.0 * nc * TM + 8.0 * nc + 120.0;
+    double cost[3], total = 0;
     for (int mu = 0; mu < 3; ++mu) {
         WDir &D = p.d[mu];
         D.N = n[mu];
         D.lines = ns / D.N;
         double dbest = 1e300;
         WDir pick{};
-        int punits = 0;
-        for (int nbl = std::min(block, (Nt + nc - 1) / nc); nbl >= 1; --nbl) {
-            const int ntc = (Nt + nbl * nc - 1) / (nbl * nc), TC = (Nt + ntc - 1) / ntc;
-            const int NB = (TC + nc - 1) / nc, TE = NB * nc + std::min(toff, NB * nc - 1) + TM;
-            const int emax = wl_ke(f32) * block;
-            int XC = D.N, XE = D.N;
-            if ((long long)XE * TE > emax || D.N * NB > block ||
-                wl_bytes(f32, XE * TE, block, Rmax, TM) > lds_max) {
-                // a piece of a line with Rmax sites beyond it, only for lines too long for any unit
-                const int TE1 = nc + std::min(toff, nc - 1) + TM;
-                if ((long long)D.N * TE1 <= emax && D.N <= block &&
-                    wl_bytes(f32, D.N * TE1, block, Rmax, TM) <= lds_max)
-                    continue;
-                XC = std::min(block / NB, emax / TE - Rmax);
-                while (XC > 0 && wl_bytes(f32, (XC + Rmax) * TE, block, Rmax, TM) > lds_max) --XC;
-                XC = std::min(XC, D.N);
-                if (XC < 1) continue;
-                XE = XC + Rmax;
-            }
-            for (int G = 1; G <= D.lines && G <= 64; ++G) {
-                if (G > 1 && XE != XC) break;
-                if (G * XC * NB > block || (long long)G * XE * TE > emax ||
-                    wl_bytes(f32, G * XE * TE, block, Rmax, TM) > lds_max)
-                    break;
-                const int ngrp = (D.lines + G - 1) / G, nxc = (D.N + XC - 1) / XC, ntcs = (Nt + TC - 1) / TC;
+        const int like = n[mu] == n[0] ? 0 : n[mu] == n[1] ? 1 : 2;  // a direction with the same split
+        if (like < mu) pick = p.d[like], dbest = cost[like];
+        // whole lines, or for lines too long for any unit pieces of one with
+        // Rmax sites beyond it
+        const bool whole = D.N <= block && (long long)D.N * rows(1) <= cap;
+        for (int NB = std::min(block, (Nt + nc - 1) / nc), last = 0; like == mu && NB >= 1; --NB) {
+            if (whole && (D.N * NB > block || D.N * rows(NB) > cap)) continue;
+            const int ntc = (Nt + NB * nc - 1) / (NB * nc);
+            if (ntc == last) continue;  // the same times per unit
+            last = ntc;
+            const int TC = (Nt + ntc - 1) / ntc, nb = (TC + nc - 1) / nc, TE = rows(nb);
+            const int XC = whole ? D.N : std::min({block / nb, cap / TE - Rmax, D.N}), XE = whole ? D.N : XC + Rmax;
+            if (XC < 1) continue;
+            const double per = (D.N + XC - 1) / XC * ((Nt + TC - 1) / TC);  // units per line
+            for (int G = 1, ngrp = 0; G <= (whole ? std::min(D.lines, 64) : 1); ++G) {
+                if (G * XC * nb > block || G * XE * TE > cap) break;
+                if ((D.lines + G - 1) / G == ngrp) continue;  // as many groups of fewer lines
+                ngrp = (D.lines + G - 1) / G;
                 const double ke = (G * XE * TE + block - 1) / block;
-                const double len = 30.0 * ke + (f32 ? 6.0 : 3.0) * (nc + TM) + 4.0 * nc * TM + 8.0 * nc + 120.0;
-                const double units = (double)ngrp * nxc * ntcs, wv = block / 64;
-                const double c = std::max(units * wv * len / 1024.0, 1.5 * len);
+                const double len = 30.0 * ke + fixed;
+                const double c = std::max(ngrp * per * wv * len / 1024.0, 1.5 * len);
                 if (c < dbest) {
                     dbest = c;
                     pick = D;
-                    pick.XC = XC, pick.XE = XE, pick.G = G, pick.TC = TC, pick.NB = NB;
-                    pick.ngrp = ngrp, pick.nxc = nxc, pick.ntc = ntcs;
-                    punits = ngrp * nxc * ntcs;
-                    pick.unit0 = p.nunits;
+                    pick.XC = XC, pick.XE = XE, pick.G = G, pick.TC = TC, pick.NB = nb;
+                    pick.ngrp = ngrp, pick.nxc = (D.N + XC - 1) / XC, pick.ntc = (Nt + TC - 1) / TC;
                 }
             }
         }
         if (dbest >= 1e300) return false;
+        pick.unit0 = p.nunits;
         D = pick;
-        p.nunits += punits;
-        const int e = D.G * D.XE * (D.NB * nc + std::min(toff, D.NB * nc - 1) + TM);
+        p.nunits += D.ngrp * D.nxc * D.ntc;
+        const int e = D.G * D.XE * rows(D.NB);
         p.nel = std::max(p.nel, (e + block - 1) / block * block);
-        total += dbest;
+        total += cost[mu] = dbest;
     }
-    const size_t lds = wl_bytes(f32, p.nel, block, Rmax, TM);
-    if (total < best.cost) best = WChoice{p, total, lds};
+    if (total < best.cost) best = WChoice{p, total, wl_bytes(f32, p.nel, block, Rmax, TM)};
     return true;
 }
 }  // namespace
@@ -2330,7 +2326,8 @@ bool wl_plan_at(bool f32, const int *n, int Rmax, int toff, int Tp, int TM, int 
 // 32 x 32 tiles (few sites each where x and y are short), then the traces.
 // us by transport and in the gauge, binary32: 64^3 x 16 156 and 343 (R = T = 1);
 // 24^3 x 48 45 and 64 (R = T = 1), 59 and 68 (2), 101 and 74 (4); 8^3 x 12 32 and 31
-// (2), 49 and 35 (R = 4, T = 8); 4^3 x 2048 92 and 173 (R = 4, T = 16).
+// (2), 49 and 35 (R = 4, T = 8); 4^3 x 2048 92 and 173 (R = 4, T = 16).  Calls that
+// the estimates hardly tell apart (1.04) go by transport.
 bool wloops_transport(bool f32, const int *n, int Rmax, int Tmax) {
     const auto tiles = [](int k) { return (k + 31) / 32; };
     const long long slice = (long long)n[0] * n[1] * n[2];
@@ -2340,7 +2337,7 @@ bool wloops_transport(bool f32, const int *n, int Rmax, int Tmax) {
     const bool near = slice <= 2048;
     if (f32)
         return 25.2 + R * V * (20.5 + (near ? 2.02 : 3.10) * T) + 1.84 * T <
-               27.0 + 35.0 * ns * next + (2.77 + 234.0 * ns) * chain + R * V * (3.46 + 0.443 * T) + 1.22 * R + 25.7 * wg;
+               1.04 * (27.0 + 35.0 * ns * next + (2.77 + 234.0 * ns) * chain + R * V * (3.46 + 0.443 * T) + 1.22 * R + 25.7 * wg);
     return 24.5 + R * V * (46.9 + (near ? 5.81 : 10.3) * T) + 1.90 * T <
            1.04 * (25.4 + 61.1 * ns * next + (3.57 + 333.0 * ns) * chain + R * V * (6.63 + 0.815 * T) + 1.27 * R + 52.4 * wg);
 }

@@ -59,6 +59,9 @@ extern "C" {
 void stub_malloc_limit(long long bytes) { g_limit = bytes; }
 // The n-th allocation from now fails, and no other (negative: none).
 void stub_malloc_countdown(long long n) { g_countdown = n; }
+// Host allocations so far.
+int g_host = 0;
+int stub_host_mallocs() { return g_host; }
 // The next n allocations succeed, later ones do not (negative: all).
 void stub_malloc_room(long long n) { g_room = n; }
 void stub_clear() { g_launches.clear(); }
@@ -119,6 +122,7 @@ hipError_t hipFree(void *p) {
     return hipSuccess;
 }
 hipError_t hipHostMalloc(void **p, size_t bytes, unsigned) {
+    ++g_host;
     *p = std::calloc(1, bytes);
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }

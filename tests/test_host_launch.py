@@ -1,5 +1,7 @@
 """What the library's host code launches, followed on the CPU over a stub of the
 HIP runtime."""
+import time
+
 import pytest
 
 from tests.host_lib import ENOMEM, F32, F64, OK, host_lib
@@ -73,3 +75,32 @@ def test_wilson_other_way_without_memory(host, dims, R, T, limit, kernel):
 def test_long_lines_take_fewer_times(host, n, nt, T, prec, kernels):
     """Rmax = n: the sums of sixteen times leave no room for the lines."""
     assert wilson_kernels(host, (n, n, n, nt), prec, n, T) == (OK, kernels)
+
+
+def test_wilson_first_call_allocates_no_host_memory(host):
+    h = host.create((8, 8, 8, 12))
+    n = host.lib.stub_host_mallocs()
+    assert host.wilson(h, 4, 6) == OK and host.wilson(h, 8, 12) == OK and host.lib.stub_host_mallocs() == n
+    assert host.lib.su2_destroy(h) == OK
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 8, 48), (16, 16, 16, 512)])
+def test_wilson_bounds_in_turn(host, dims):
+    """A program that alternates between two bounds pays for no new work split on
+    each call (searched anew, 10 to 100 times the rest of a call's host work here)."""
+    h = host.create(dims)
+
+    def fastest(bounds):
+        best = 1.0
+        for _ in range(30):
+            t = time.perf_counter()
+            for _ in range(10):
+                for b in bounds:
+                    host.wilson(h, *b)
+            best = min(best, time.perf_counter() - t)
+        host.lib.stub_clear()
+        return best
+
+    same = fastest([(8, 16), (8, 16)])
+    assert fastest([(8, 16), (8, 15)]) < 3 * same
+    assert host.lib.su2_destroy(h) == OK
