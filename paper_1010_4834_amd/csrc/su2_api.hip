@@ -1611,8 +1611,8 @@ su2_status su2_ape_smear(su2_lattice E, double alpha, int nsteps) {
         cur = 0;
     }
     const LatDesc &d = E->hdesc[0];
-    const bool slices = nsteps > 1 && !E->timing && !std::getenv("SU2_NO_GRAPH") &&
-                        su2::launch_ape_slices(a, E->f32, d.ns, d.n[3], src, 1, E->sm[0], alpha, nsteps, s);
+    const bool slices = !E->timing && !std::getenv("SU2_NO_GRAPH") && su2::ape_in_slices(E->f32, d.ns, d.n[3], nsteps);
+    if (slices) su2::launch_ape_slices(a, E->f32, d.ns, d.n[3], src, 1, E->sm[0], alpha, nsteps, s);
     for (int k = 0; k < nsteps && !slices; ++k) {
         cur = k & 1;
         Timed t(E, SU2_K_APE, s);

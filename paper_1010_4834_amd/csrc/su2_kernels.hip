@@ -2141,15 +2141,12 @@ void launch_ape(const KArgs &a, bool f32, const void *src, int src_raw, void *ds
     else hipLaunchKernelGGL((k_ape<double>), g, dim3(block), 0, s, a, src, src_raw, dst, alpha);
 }
 
-// false: the slices are too large
-bool launch_ape_slices(const KArgs &a, bool f32, int ns, int nt, const void *src, int src_raw, void *dst, double alpha,
+void launch_ape_slices(const KArgs &a, bool f32, int ns, int nt, const void *src, int src_raw, void *dst, double alpha,
                        int nsteps, hipStream_t s) {
-    if (ns > ape_slice(f32)) return false;
     const size_t lds = (size_t)3 * ns * (f32 ? 16 : 32);  // 48 KiB at most
     const dim3 g((unsigned)nt), b((unsigned)((ns + 63) / 64 * 64));
     if (f32) hipLaunchKernelGGL((k_ape_slices<float>), g, b, lds, s, a, src, src_raw, dst, (float)alpha, nsteps);
     else hipLaunchKernelGGL((k_ape_slices<double>), g, b, lds, s, a, src, src_raw, dst, alpha, nsteps);
-    return true;
 }
 
 void launch_wgauge(const KArgs &a, bool f32, int ns, int next, void *P, hipStream_t s) {

@@ -104,3 +104,27 @@ def test_wilson_bounds_in_turn(host, dims):
     same = fastest([(8, 16), (8, 16)])
     assert fastest([(8, 16), (8, 15)]) < 3 * same
     assert host.lib.su2_destroy(h) == OK
+
+
+@pytest.mark.parametrize("dims,steps,f64,f32", [
+    ((2, 2, 2, 512), 25, True, True),
+    ((2, 2, 2, 514), 25, False, False),    # idle lanes: one launch per step
+    ((4, 2, 2, 65536), 5, False, False),
+    ((6, 4, 2, 65536), 3, True, True),
+    ((4, 4, 4, 4), 2, True, True),
+    ((4, 4, 4, 4), 1, False, False),
+    ((6, 4, 4, 64), 2, True, False),       # a partly filled wavefront
+    ((8, 8, 4, 64), 2, True, True),
+    ((8, 8, 8, 64), 5, True, False),       # large slices
+    ((8, 8, 8, 64), 6, True, True),
+    ((16, 8, 8, 4), 6, False, True),
+    ((16, 8, 10, 4), 25, False, False),
+])
+def test_smearing_ways(host, dims, steps, f64, f32):
+    for prec, slices in ((F64, f64), (F32, f32)):
+        h = host.create(dims, prec)
+        host.lib.stub_clear()
+        assert host.lib.su2_ape_smear(h, 0.5, steps) == OK
+        names = host.names()
+        assert len(names) == (1 if slices else steps) and all(("k_ape_slices" in n) == slices for n in names), prec
+        assert host.lib.su2_destroy(h) == OK
