@@ -571,18 +571,29 @@ void fill_desc(LatDesc &D, const int *d, int l, long long off, long long sites, 
 
 // Tile mode of a new single lattice (an ensemble starts in mode 1, its XCD
 // shares being whole lattices or nearly).  us per heat-bath substep under block
-// 256, binary32 and binary64:
+// 256, binary32 and binary64; over-relaxation substeps go the same way.
+// Mode 0 (round robin): where a (direction, parity) block's time slices lie
+// whole multiples of 2 MiB apart the eight XCDs' separate regions collide, and
+// one region for all is faster once the links are more than the Infinity Cache
+// holds by half: modes 1 and 0, 64^4 247 220 and 648 480, 64 x 64 x 128 x 16 140 118
+// and 291 253, 128^2 x 64 x 12 224 182 and 484 377.  Below that, or with one time
+// slice per XCD, not: 64^2 x 128 x 12 90 96 (binary32), 64^3 x 12 97 99 (binary64), 96 x
+// 64 x 128 x 8 90 117 and 191 232, 128^3 x 8 238 242 and 550 548; but in binary32
+// with slices of just 2 MiB always: 64^3 x 8 29.8 26.9, x 12 43.7 37.1.
 // Mode 3 reads fewer halo links than mode 1 where its blocks divide evenly and
-// are large: modes 1 and 3, 32^4 14.4 14.0 and 33.5 31.3, 56^4 140 140 and
-// 337 292, 32^3 x 16 8.8 8.3 and 20.0 19.2; 24^3 x 32 the same in both, and
-// the uneven 28 x 26 x 18 x 32 7.5 7.8 and 18.2 18.4.
-// Where a (direction, parity) block's time slices lie whole multiples of 2 MiB
-// apart the eight XCDs' separate regions are slower than one region in round
-// robin (mode 0): modes 3 and 0, 64^4 235 223 and 507 478, 64^3 x 8 28.3 24.1
-// and 58.6 60.5; not with the few slices of 128^3 x 4, 121 124 and 263 283.
-int default_mode(const LatDesc &d) {
-    if ((long long)d.ns * 8 % (2 << 20) == 0 && d.n[3] >= 8) return 0;
-    return d.vh > 1 << 18 && d.n[2] % 8 == 0 && d.n[3] % 8 == 0 ? 3 : 1;
+// are large: modes 1 and 3, 32^4 14.4 14.0 and 33.5 31.3, 56^4 140 140 and 337 292,
+// 80^3 x 24 213 178 and 455 430.  Not with large slices over few times (112^3 x 8
+// 161 192 and 343 397, 80^3 x 16 binary64 283 296, but 80^3 x 16 binary32 130 120),
+// with blocks of two slices in z (64^2 x 8 x 128 48.7 50.9), or with small slices,
+// the more so where tiles straddle them (20 x 24^2 x 48 over-relaxation 8.8 10.2,
+// 26^2 x 32 x 40 14.3 14.7; 24^2 x 32 x 32 11.5 11.1, 34^2 x 32 x 32 18.3 17.5).
+int default_mode(const LatDesc &d, bool f32) {
+    const long long slice = (long long)d.ns * (f32 ? 8 : 16);  // bytes, of one direction and parity
+    const int Nt = d.n[3];
+    if ((long long)d.ns * 8 % (2 << 20) == 0)
+        return (f32 && slice == 2 << 20 && Nt >= 8) || (Nt >= 10 && 8 * slice * Nt > (384LL << 20)) ? 0 : 1;
+    const bool even = d.vh > 1 << 18 && d.n[2] % 8 == 0 && d.n[2] >= 16 && Nt % 8 == 0;
+    return even && (Nt >= 24 || slice <= 6 << 20) && d.ns >= (d.ns % 512 ? 1 << 15 : 1 << 14) ? 3 : 1;
 }
 
 // ---- creation ----------------------------------------------------------------
@@ -608,7 +619,7 @@ su2_status create_common(int n, const int *dims, const double *betas, su2_start 
     }
     E->total_links = off;
     E->total_sites = sites;
-    if (n == 1) E->remap = default_mode(E->hdesc[0]);
+    if (n == 1) E->remap = default_mode(E->hdesc[0], E->f32);
     E->link_bytes = (size_t)off * link_size(E->f32);
     if (hipStreamCreateWithFlags(&E->own, hipStreamNonBlocking) != hipSuccess) return SU2_EDEVICE;
     if (device_links) {
@@ -927,7 +938,11 @@ su2_status set_seed(su2_ensemble_s *E, uint64_t seed) {
 // ---- measurements -------------------------------------------------------------
 su2_status measure_plaquette(su2_ensemble_s *E, int l, double *avg, double *sp, double *tp) {
     hipStream_t s = E->stream();
-    const KArgs a = kargs(E);
+    // mode 0 of a new lattice only for binary32 slices of up to 4 MiB: us XCD by
+    // XCD and in round robin, 64^3 x 16 138 111 and 268 265, 64^2 x 128 x 16 241 221
+    // and 502 528, 128^2 x 64 x 16 437 476 and 963 1045
+    const bool robin = E->f32 && E->hdesc[0].ns <= (4 << 20) / 8;
+    const KArgs a = robin ? kargs(E) : xcd_args(E);
     const bool one = E->n == 1 && E->ntiles <= su2::ONE_TILES && !E->timing;
     if (one) {
         su2::launch_plaquette_one(a, E->f32, E->block, E->dres, E->derr, s);
@@ -952,7 +967,7 @@ su2_status measure_plaquette(su2_ensemble_s *E, int l, double *avg, double *sp, 
 
 su2_status measure_polyakov(su2_ensemble_s *E, int l, double *out) {
     hipStream_t s = E->stream();
-    const KArgs a = kargs(E, 1);
+    const KArgs a = xcd_args(E, 1);  // 128^3 x 8 73 us, 79 in round robin; 64^3 x 8 28 and 30
     const bool one = E->n == 1 && E->nstiles <= su2::ONE_TILES && !E->timing;
     if (one) {
         su2::launch_polyakov_one(a, E->f32, E->block, E->dres, E->derr, s);
@@ -1567,13 +1582,15 @@ su2_status su2_overrelax(su2_lattice E, int nsweeps) {
     if (nsweeps < 0) return SU2_EINVAL;
     hipStream_t s = E->stream();
     KArgs a = kargs(E);
+    const bool blocks = default_mode(E->hdesc[0], E->f32) == 3;
     bool err_enqueued = false;
     const bool small = nsweeps > 0 && small_run_ok(E, true) && run_small(E, nsweeps, 1, 0, 1, &err_enqueued);
     for (int k = 0; k < nsweeps && !small; ++k)
         for (int mu = 0; mu < 4; ++mu)
             for (int par = 0; par < 2; ++par) {
-                // the heat bath's XCD blocks where its tiles are the same
-                if (E->nl == 1 && E->remap == 3) a.tiles = hb_tiles(E, mu);
+                // the heat bath's XCD blocks where its tiles are the same and
+                // the lattice is one for them
+                if (E->nl == 1 && E->remap == 3 && blocks) a.tiles = hb_tiles(E, mu);
                 Timed t(E, SU2_K_OVERRELAX, s, true);
                 su2::launch_overrelax(a, E->f32, mu, par, E->block, E->grid, s, t.ev());
                 t.done(s);

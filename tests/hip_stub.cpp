@@ -18,6 +18,8 @@ struct Launch {
     unsigned grid[3], block;
     size_t lds;
     int nulls;  // null pointers among the arguments named in ARGS below
+    int xcd;    // of a kernel(KArgs, ...): its walk and tile list
+    const void *tiles;
 };
 // registered while the library is loaded, before this file's own objects
 std::map<const void *, std::string> &kernels() {
@@ -41,12 +43,14 @@ struct ArgSet {
 const ArgSet ARGS[] = {{"k_wgauge", {2}}, {"k_wlinks", {1, 5, 6, 7}}, {"k_wloops", {4, 5, 6}}, {"k_wfinal", {0, 2, 3, 4, 5}}};
 
 hipError_t record(const void *f, dim3 g, dim3 b, void **args, size_t lds) {
-    Launch l{kernels()[f], {g.x, g.y, g.z}, b.x, lds, 0};
+    Launch l{kernels()[f], {g.x, g.y, g.z}, b.x, lds, 0, -1, nullptr};
     for (const ArgSet &s : ARGS)
         if (l.name.find(s.kernel) != std::string::npos)
             for (int i : s.at) l.nulls += *(void **)args[i] == nullptr;
     if (l.name.find("EvNS_5KArgsE") != std::string::npos) {  // kernel(KArgs, ...)
         const su2::KArgs &a = *(const su2::KArgs *)args[0];
+        l.xcd = a.xcd_remap;
+        l.tiles = a.tiles;
         l.nulls += !a.desc + !a.tiles + !a.links + !a.st + !a.tries_part;
     }
     g_launches.push_back(l);
@@ -68,6 +72,8 @@ void stub_clear() { g_launches.clear(); }
 int stub_launches() { return (int)g_launches.size(); }
 const char *stub_name(int i) { return g_launches[i].name.c_str(); }
 int stub_block(int i) { return (int)g_launches[i].block; }
+int stub_xcd(int i) { return g_launches[i].xcd; }
+const void *stub_tiles(int i) { return g_launches[i].tiles; }
 int stub_nulls() {
     int n = 0;
     for (const Launch &l : g_launches) n += l.nulls;

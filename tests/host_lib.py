@@ -45,6 +45,7 @@ class Host:
     def __init__(self, folder):
         self.lib = build(str(folder))
         self.lib.stub_name.restype = C.c_char_p
+        self.lib.stub_tiles.restype = C.c_void_p
         for f in ("limit", "countdown", "room"):
             getattr(self.lib, "stub_malloc_" + f).argtypes = [C.c_longlong]
         self.lib.su2_create.argtypes = [C.c_int] * 5 + [C.c_uint64, C.c_int, C.c_void_p, C.c_size_t, C.c_void_p]

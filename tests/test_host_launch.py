@@ -1,5 +1,6 @@
 """What the library's host code launches, followed on the CPU over a stub of the
 HIP runtime."""
+import ctypes as C
 import time
 
 import pytest
@@ -128,3 +129,64 @@ def test_smearing_ways(host, dims, steps, f64, f32):
         names = host.names()
         assert len(names) == (1 if slices else steps) and all(("k_ape_slices" in n) == slices for n in names), prec
         assert host.lib.su2_destroy(h) == OK
+
+
+@pytest.mark.parametrize("dims,f64,f32", [
+    ((64, 64, 64, 64), 0, 0),
+    ((64, 64, 64, 8), 1, 0),
+    ((64, 64, 64, 12), 1, 0),
+    ((64, 64, 64, 14), 0, 0),
+    ((64, 64, 128, 12), 0, 1),
+    ((64, 64, 128, 14), 0, 0),
+    ((96, 64, 128, 8), 1, 1),      # one time slice per XCD: 30% slower in round robin
+    ((128, 128, 64, 8), 1, 1),
+    ((32, 32, 32, 32), 3, 3),
+    ((80, 80, 80, 16), 1, 3),      # large slices over few times
+    ((112, 112, 112, 8), 1, 1),
+    ((64, 64, 8, 128), 1, 1),
+    ((20, 24, 24, 48), 1, 1),      # small slices
+    ((24, 24, 32, 32), 3, 3),
+    ((26, 26, 32, 40), 1, 1),
+    ((34, 34, 32, 32), 3, 3),
+    ((24, 24, 24, 32), 1, 1),
+])
+def test_tile_mode_of_a_new_lattice(host, dims, f64, f32):
+    for prec, mode in ((F64, f64), (F32, f32)):
+        h = host.create(dims, prec)
+        assert host.launch(h) == (256, 0, mode, 1)
+        assert host.lib.su2_destroy(h) == OK
+
+
+def launches(host, what):
+    host.lib.stub_clear()
+    assert what() == OK
+    return [(n, host.lib.stub_xcd(i), host.lib.stub_tiles(i)) for i, n in enumerate(host.names())]
+
+
+@pytest.mark.parametrize("dims,prec,walk", [((64, 64, 64, 16), F32, 0), ((64, 64, 64, 16), F64, 1),
+                                            ((128, 128, 64, 16), F32, 1)])
+def test_measurements_of_a_round_robin_lattice(host, dims, prec, walk):
+    """The tile mode chosen for the heat bath is not the plaquette's everywhere,
+    and never the Polyakov loop's; a mode that the caller sets is both's."""
+    h = host.create(dims, prec)
+    assert host.launch(h)[2] == 0
+    out = (C.c_double * 1)()
+    for mode, want in ((None, (walk, 1)), (0, (0, 0)), (1, (1, 1))):
+        if mode is not None:
+            assert host.lib.su2_set_launch(h, 256, 0, mode, 1) == OK
+        seen = {n.split("k_")[1][:4]: x for n, x, _ in launches(host, lambda: host.plaquette(h)) +
+                launches(host, lambda: host.lib.su2_polyakov(h, out))}
+        assert (seen["plaq"], seen["poly"]) == want, mode
+    assert host.lib.su2_destroy(h) == OK
+
+
+@pytest.mark.parametrize("dims,same", [((32, 32, 32, 32), True), ((20, 24, 24, 48), False)])
+def test_overrelaxation_tiles_in_mode_3(host, dims, same):
+    """Over-relaxation takes the heat bath's blocks on lattices they suit only
+    (20 x 24^2 x 48: 10.2 us a substep, 8.8 in lexicographic order)."""
+    h = host.create(dims)
+    assert host.lib.su2_set_launch(h, 256, 0, 3, 1) == OK
+    over = [t for n, _, t in launches(host, lambda: host.lib.su2_overrelax(h, 1)) if "overrelax" in n]
+    heat = [t for n, _, t in launches(host, lambda: host.lib.su2_heatbath(h, 2.3, 1, 1)) if "heatbath" in n]
+    assert len(over) == len(heat) == 8 and (over == heat) == same
+    assert host.lib.su2_destroy(h) == OK
