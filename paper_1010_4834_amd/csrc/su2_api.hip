@@ -73,6 +73,7 @@ struct su2_ensemble_s {
     long long total_links = 0;  // 4 * sum V
     long long total_sites = 0;
     long long max_sites = 0;    // of the largest lattice
+    double min_beta = 0.0;      // smallest coupling
 
     int block = 256, grid = 0, remap = 1, nl = 1;
     bool own_shape = true;  // the launch shape is the library's choice at creation
@@ -281,6 +282,11 @@ struct TmpEvents {
     }
 };
 
+// Links per tile of the heat bath where four lanes share a link, else 0.
+int split_links(const su2_ensemble_s *E) {
+    return E->nl == 1 && E->total_sites <= su2::split_sites(E->f32, E->sampler == SU2_CREUTZ, E->min_beta) ? E->block : 0;
+}
+
 KArgs kargs(su2_ensemble_s *E, int which = 0) {
     KArgs a;
     a.desc = E->ddesc;
@@ -298,7 +304,7 @@ KArgs kargs(su2_ensemble_s *E, int which = 0) {
     a.advance = 0;
     a.nslots = 0;
     a.every = 1;
-    a.tile_links = E->nl == 1 && E->total_sites <= su2::split_sites(E->f32, E->sampler == SU2_CREUTZ) ? E->block : 0;
+    a.tile_links = split_links(E);
     return a;
 }
 
@@ -616,6 +622,7 @@ su2_status create_common(int n, const int *dims, const double *betas, su2_start 
         off += 4 * V;
         sites += V;
         E->max_sites = std::max(E->max_sites, V);
+        E->min_beta = l ? std::min(E->min_beta, E->hdesc[l].beta) : E->hdesc[l].beta;
     }
     E->total_links = off;
     E->total_sites = sites;
@@ -1309,7 +1316,7 @@ su2_status su2_heatbath_noalloc(void *device_links, int Nx, int Ny, int Nz, int 
     a.advance = 1;
     a.nslots = 0;
     a.every = 1;
-    a.tile_links = 2LL * D.vh <= su2::split_sites(prec == SU2_F32, false) ? NOALLOC_BLOCK : 0;
+    a.tile_links = 2LL * D.vh <= su2::split_sites(prec == SU2_F32, false, beta) ? NOALLOC_BLOCK : 0;
     for (int k = 0; k < nsweeps; ++k)
         for (int mu = 0; mu < 4; ++mu)
             for (int par = 0; par < 2; ++par)
@@ -1538,8 +1545,10 @@ su2_status su2_set_sampler(su2_lattice E, su2_sampler s) { return su2_ensemble_s
 
 static su2_status set_beta(su2_ensemble_s *E, double beta) {
     if (E->hdesc[0].beta != beta) {
-        E->hdesc[0].beta = beta;
+        const int links = split_links(E);
+        E->hdesc[0].beta = E->min_beta = beta;
         E->hdesc[0].betaf = (float)beta;
+        if (split_links(E) != links) drop_graphs(E);  // captured with the other kernel
         CHK(upload_desc(E));
     }
     return SU2_OK;

@@ -26,13 +26,21 @@ struct KArgs {
 };
 
 // Largest number of sites, all lattices together, at which four lanes share a
-// link (k_heatbath_split; single-link launch shapes).  us per substep with one
-// and with four lanes: Kennedy-Pendleton binary64 7.9 and 6.1 at 8192 sites,
-// 8.1 and 6.7 at 32768, 8.0 and 8.3 at 57344; Creutz binary32 13.6 and 6.6 at
-// 8192, 14.3 and 9.5 at 110592, binary64 15.5 and 8.4, 17.4 and 17.2.  A
-// binary32 Kennedy-Pendleton try is too short to gain (4.1 and 4.2 at 8192).
-constexpr long long split_sites(bool f32, bool creutz) {
-    return creutz ? (f32 ? 1LL << 17 : 98304) : f32 ? 0 : 1LL << 15;
+// link (k_heatbath_split; single-link launch shapes); beta the smallest coupling.
+// us per substep with one and with four lanes: Kennedy-Pendleton binary64 7.9 and
+// 6.1 at 8192 sites, 8.1 and 6.7 at 32768, 8.0 and 8.3 at 57344; Creutz at beta 2.3
+// binary32 12.8 and 6.9 at 4096, 14.3 and 9.2 at 98304, binary64 15.1 and 8.7, 17.2
+// and 15.5.  A binary32 Kennedy-Pendleton try is too short to gain (4.1 and 4.2 at
+// 8192).  The smaller beta, the fewer tries there are to share: Creutz binary32
+// 5.7 and 6.1 at beta 0, 7.4 and 6.8 at beta 0.2 (98304 sites), 7.5 and 7.6 at beta
+// 0.3, 9.4 and 8.2 at beta 1 (131072); binary64 7.3 and 7.9 at beta 0, 9.2 and 8.7 at
+// beta 0.1 (65536), 9.9 and 12.0 at beta 0.5, 13.7 and 13.7 at beta 1.5 (98304);
+// Kennedy-Pendleton binary64, which has Creutz tries there, 6.4 and 6.6 at beta 0,
+// 8.5 and 7.3 at beta 0.3 (4096).
+constexpr long long split_sites(bool f32, bool creutz, double beta) {
+    if (!creutz) return f32 || beta < 0.1 ? 0 : 1LL << 15;
+    if (f32) return beta < 0.1 ? 1LL << 16 : beta < 0.5 ? 98304 : 1LL << 17;
+    return beta < 0.1 ? 1LL << 15 : beta < 1.5 ? 1LL << 16 : 98304;
 }
 
 // A call's sweeps of small lattices, one workgroup per lattice with its links

@@ -52,6 +52,7 @@ class Host:
         self.lib.su2_ensemble_run.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_uint64, C.c_void_p, C.c_void_p]
         self.lib.su2_ape_smear.argtypes = [C.c_void_p, C.c_double, C.c_int]
         self.lib.su2_heatbath.argtypes = [C.c_void_p, C.c_double, C.c_int, C.c_uint64]
+        self.lib.su2_heatbath_substep.argtypes = [C.c_void_p, C.c_double, C.c_uint64, C.c_int, C.c_int]
         self.lib.su2_autotune.argtypes = [C.c_void_p, C.c_double]
         self.lib.su2_wilson_loops.argtypes = [C.c_void_p, C.c_int, C.c_int, C.c_void_p]
         for f in ("su2_destroy", "su2_release_buffers"):

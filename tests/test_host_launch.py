@@ -5,7 +5,7 @@ import time
 
 import pytest
 
-from tests.host_lib import ENOMEM, F32, F64, OK, host_lib
+from tests.host_lib import CREUTZ, ENOMEM, F32, F64, HYBRID, OK, host_lib
 
 
 @pytest.fixture
@@ -189,4 +189,39 @@ def test_overrelaxation_tiles_in_mode_3(host, dims, same):
     over = [t for n, _, t in launches(host, lambda: host.lib.su2_overrelax(h, 1)) if "overrelax" in n]
     heat = [t for n, _, t in launches(host, lambda: host.lib.su2_heatbath(h, 2.3, 1, 1)) if "heatbath" in n]
     assert len(over) == len(heat) == 8 and (over == heat) == same
+    assert host.lib.su2_destroy(h) == OK
+
+
+@pytest.mark.parametrize("dims,prec,sampler,beta,four", [
+    ((16, 16, 16, 16), F32, CREUTZ, 0.0, True),
+    ((16, 16, 16, 20), F32, CREUTZ, 0.0, False),   # one try is most links' last
+    ((16, 16, 16, 24), F32, CREUTZ, 0.2, True),
+    ((16, 16, 16, 32), F32, CREUTZ, 0.2, False),
+    ((16, 16, 16, 32), F32, CREUTZ, 1.0, True),
+    ((16, 16, 16, 34), F32, CREUTZ, 6.0, False),
+    ((16, 16, 16, 8), F64, CREUTZ, 0.0, True),
+    ((16, 16, 16, 16), F64, CREUTZ, 0.0, False),
+    ((16, 16, 16, 16), F64, CREUTZ, 1.0, True),
+    ((16, 16, 16, 24), F64, CREUTZ, 1.0, False),
+    ((16, 16, 16, 24), F64, CREUTZ, 2.0, True),
+    ((16, 16, 16, 8), F64, HYBRID, 0.0, False),
+    ((16, 16, 16, 8), F64, HYBRID, 0.3, True),
+    ((16, 16, 16, 10), F64, HYBRID, 2.3, False),
+    ((8, 8, 8, 8), F32, HYBRID, 2.3, False),
+])
+def test_four_lanes_per_link(host, dims, prec, sampler, beta, four):
+    """By size, sampler, precision and coupling, also in a graph that was captured
+    at another coupling."""
+    h = host.create(dims, prec)
+    assert host.lib.su2_set_sampler(h, sampler) == OK
+    for b in (2.3, beta):
+        assert host.lib.su2_heatbath(h, b, 2, 1) == OK
+    host.lib.stub_clear()
+    assert host.lib.su2_heatbath_substep(h, beta, 1, 0, 0) == OK
+    names = host.names()
+    assert len(names) == 1 and ("k_heatbath_split" in names[0]) == four
+    host.lib.stub_clear()
+    assert host.lib.su2_heatbath(h, 2.3, 2, 1) == OK and host.lib.su2_heatbath(h, beta, 2, 1) == OK
+    now = [n for n in host.names() if "k_heatbath" in n]
+    assert not now or ("split" in now[-1]) == four     # captured anew where the kernel is another
     assert host.lib.su2_destroy(h) == OK
