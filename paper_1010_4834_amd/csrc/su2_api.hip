@@ -1112,9 +1112,15 @@ void tune_cache_put(const std::string &key, const Shape &v) {
 }
 
 su2_status autotune_common(su2_ensemble_s *E) {
+    // the shape depends on the lattices' extents and the sampler, and on whether
+    // four lanes share a link of a single-link shape
+    unsigned long long shape = 14695981039346656037ull;  // FNV-1a over the extents
+    for (const LatDesc &d : E->hdesc)
+        for (int k = 0; k < 4; ++k) shape = (shape ^ (unsigned long long)d.n[k]) * 1099511628211ull;
     char key[160];
-    std::snprintf(key, sizeof key, "%s:n%d:sites%lld:t%lld", E->f32 ? "f32" : "f64", E->n, E->total_sites,
-                  (long long)E->hdesc[0].n[3]);
+    std::snprintf(key, sizeof key, "%s:sampler%d:four%d:n%d:sites%lld:%llx", E->f32 ? "f32" : "f64", E->sampler,
+                  E->total_sites <= su2::split_sites(E->f32, E->sampler == SU2_CREUTZ, E->min_beta), E->n,
+                  E->total_sites, shape);
     Shape cached;
     if (tune_cache_get(key, cached)) return set_launch_common(E, cached.block, cached.grid, cached.remap, cached.nl);
 

@@ -225,3 +225,20 @@ def test_four_lanes_per_link(host, dims, prec, sampler, beta, four):
     now = [n for n in host.names() if "k_heatbath" in n]
     assert not now or ("split" in now[-1]) == four     # captured anew where the kernel is another
     assert host.lib.su2_destroy(h) == OK
+
+
+def test_tuned_shape_is_of_the_same_lattice_and_sampler(host):
+    """The shapes that the tuner keeps for later handles."""
+    def tuned(dims, prec=F64, sampler=HYBRID, beta=2.3):
+        h = host.create(dims, prec)
+        assert host.lib.su2_set_sampler(h, sampler) == OK
+        host.lib.stub_clear()
+        assert host.lib.su2_autotune(h, beta) == OK
+        trials = sum("k_heatbath" in n for n in host.names())
+        assert host.lib.su2_destroy(h) == OK
+        return trials > 0
+
+    assert tuned((10, 12, 14, 16)) and not tuned((10, 12, 14, 16)) and not tuned((10, 12, 14, 16), beta=2.4)
+    assert tuned((10, 12, 14, 16), sampler=CREUTZ) and not tuned((10, 12, 14, 16), sampler=CREUTZ)
+    assert tuned((14, 12, 10, 16)) and tuned((10, 14, 12, 16))   # as many sites, the same Nt
+    assert tuned((10, 12, 14, 16), prec=F32)
