@@ -77,13 +77,13 @@ struct su2_ensemble_s {
 
     int block = 256, grid = 0, remap = 1, nl = 1;
     bool own_shape = true;  // the launch shape is the library's choice at creation
-    std::vector<Tile> htiles, hstiles, hvtiles, hmtiles, hmtiles_z, hmtiles_b, hmtiles_b3;
-    Tile *tiles = nullptr, *stiles = nullptr, *vtiles = nullptr, *mtiles = nullptr;
+    std::vector<Tile> htiles, hstiles, hmtiles, hmtiles_z, hmtiles_b, hmtiles_b3;
+    Tile *tiles = nullptr, *stiles = nullptr, *mtiles = nullptr;
     Tile *mtiles_z = nullptr;  // the heat-bath tiles of each lattice in (z, t, y, x) order
     // tile mode 3: the heat-bath tiles in eight blocks per lattice, (z half,
     // t quarter) for mu < 3 and (z quarter, y half) for mu = 3
     Tile *mtiles_b = nullptr, *mtiles_b3 = nullptr;
-    int ntiles = 0, nstiles = 0, nvtiles = 0, nmtiles = 0;
+    int ntiles = 0, nstiles = 0, nmtiles = 0;
 
     void *links = nullptr;
     bool own_links = true;
@@ -287,12 +287,12 @@ int split_links(const su2_ensemble_s *E) {
     return E->nl == 1 && E->total_sites <= su2::split_sites(E->f32, E->sampler == SU2_CREUTZ, E->min_beta) ? E->block : 0;
 }
 
+// which: tiles of half-sites (0), of spatial sites (1), of heat-bath links (2).
 KArgs kargs(su2_ensemble_s *E, int which = 0) {
     KArgs a;
     a.desc = E->ddesc;
-    a.tiles = which == 0 ? E->tiles : which == 1 ? E->stiles : which == 2 ? E->vtiles
-            : which == 3 ? E->mtiles : which == 4 ? E->mtiles_z : which == 5 ? E->mtiles_b : E->mtiles_b3;
-    a.ntiles = which == 0 ? E->ntiles : which == 1 ? E->nstiles : which == 2 ? E->nvtiles : E->nmtiles;
+    a.tiles = which == 0 ? E->tiles : which == 1 ? E->stiles : E->mtiles;
+    a.ntiles = which == 0 ? E->ntiles : which == 1 ? E->nstiles : E->nmtiles;
     a.xcd_remap = E->remap != 0;
     a.links = E->links;
     a.st = E->st;
@@ -420,7 +420,6 @@ su2_status build_tiles(su2_ensemble_s *E) {
     CHK(fold_tries(E));
     E->htiles.clear();
     E->hstiles.clear();
-    E->hvtiles.clear();
     E->hmtiles.clear();
     E->hmtiles_z.clear();
     E->hmtiles_b.clear();
@@ -434,9 +433,6 @@ su2_status build_tiles(su2_ensemble_s *E) {
         d.stile0 = (int)E->hstiles.size();
         for (int s = 0; s < d.ns; s += B) E->hstiles.push_back(make_int2(l, s));
         d.nstile = (int)E->hstiles.size() - d.stile0;
-        d.vtile0 = (int)E->hvtiles.size();
-        for (int s = 0; s < 2 * d.vh; s += B) E->hvtiles.push_back(make_int2(l, s));
-        d.nvtile = (int)E->hvtiles.size() - d.vtile0;
         d.mtile0 = (int)E->hmtiles.size();
         for (int s = 0; s < d.vh; s += B * E->nl) E->hmtiles.push_back(make_int2(l, s));
         d.nmtile = (int)E->hmtiles.size() - d.mtile0;
@@ -473,11 +469,9 @@ su2_status build_tiles(su2_ensemble_s *E) {
     }
     E->ntiles = (int)E->htiles.size();
     E->nstiles = (int)E->hstiles.size();
-    E->nvtiles = (int)E->hvtiles.size();
     E->nmtiles = (int)E->hmtiles.size();
     CHK(dalloc(E, &E->tiles, sizeof(Tile) * E->ntiles));
     CHK(dalloc(E, &E->stiles, sizeof(Tile) * E->nstiles));
-    CHK(dalloc(E, &E->vtiles, sizeof(Tile) * E->nvtiles));
     CHK(dalloc(E, &E->mtiles, sizeof(Tile) * E->nmtiles));
     CHK(dalloc(E, &E->mtiles_z, sizeof(Tile) * E->nmtiles));
     CHK(dalloc(E, &E->mtiles_b, sizeof(Tile) * E->nmtiles));
@@ -510,8 +504,6 @@ su2_status build_tiles(su2_ensemble_s *E) {
     HIPCHK(hipMemcpyAsync(E->tiles, E->htiles.data(), sizeof(Tile) * E->ntiles, hipMemcpyHostToDevice,
                           E->stream()));
     HIPCHK(hipMemcpyAsync(E->stiles, E->hstiles.data(), sizeof(Tile) * E->nstiles, hipMemcpyHostToDevice,
-                          E->stream()));
-    HIPCHK(hipMemcpyAsync(E->vtiles, E->hvtiles.data(), sizeof(Tile) * E->nvtiles, hipMemcpyHostToDevice,
                           E->stream()));
     HIPCHK(hipMemcpyAsync(E->mtiles, E->hmtiles.data(), sizeof(Tile) * E->nmtiles, hipMemcpyHostToDevice,
                           E->stream()));
@@ -667,7 +659,7 @@ void destroy_common(su2_ensemble_s *E) {
         (void)hipEventDestroy(p.b);
     }
     for (auto e : E->evpool) (void)hipEventDestroy(e);
-    void *bufs[] = {E->ddesc, E->tiles, E->stiles, E->vtiles, E->mtiles, E->mtiles_z, E->mtiles_b, E->mtiles_b3, E->st, E->tries_part, E->part_plaq,
+    void *bufs[] = {E->ddesc, E->tiles, E->stiles, E->mtiles, E->mtiles_z, E->mtiles_b, E->mtiles_b3, E->st, E->tries_part, E->part_plaq,
                     E->part_poly, E->part_hb, E->fin_cnt, E->fin_chunk, E->ser_chunk,
                     E->sm[0], E->sm[1], E->wl_p, E->wpart, E->trace};
     for (void *b : bufs)
@@ -687,7 +679,7 @@ void destroy_common(su2_ensemble_s *E) {
 // per batch of measurements (series_batch), so a sweep holds no reduction
 // launch.
 su2_status enqueue_sweep(su2_ensemble_s *E, int meas, int every, hipStream_t s) {
-    KArgs a = kargs(E, 3);
+    KArgs a = kargs(E, 2);
     a.advance = 1;
     a.nslots = E->nslots;
     a.every = every;
@@ -1580,7 +1572,7 @@ su2_status su2_heatbath_substep(su2_lattice E, double beta, uint64_t seed, int m
     hipStream_t s = E->stream();
     {
         Timed t(E, SU2_K_HEATBATH, s, true);
-        KArgs a = kargs(E, 3);
+        KArgs a = kargs(E, 2);
         a.tiles = hb_tiles(E, mu);
         su2::launch_heatbath(a, E->f32, mu, parity, E->nl, E->block, E->grid, s,
                              E->trace != nullptr, false, t.ev());

@@ -33,7 +33,6 @@ struct LatDesc {
     float betaf;
     int tile0, ntile;    // range in the half-site tile table
     int stile0, nstile;  // range in the spatial-site tile table
-    int vtile0, nvtile;  // range in the full-site tile table
     int mtile0, nmtile;  // range in the heat-bath (links-per-lane) tile table
 };
 
@@ -53,7 +52,7 @@ struct DevState {
     unsigned int off_group; // Wilson loops: temporal lines too far off unit norm for their gauge
 };
 
-// A tile: lattice index and first index (half-site, spatial site or site).
+// A tile: lattice index and first index (half-site or spatial site).
 typedef int2 Tile;
 
 // Random-number purposes (third Philox counter word).
