@@ -133,14 +133,16 @@ void launch_ape(const KArgs &a, bool f32, const void *src, int src_raw, void *ds
 constexpr int ape_slice(bool f32) { return f32 ? 1024 : 512; }
 // and whether that is the shorter way.  us here and as one launch per step: 2^3 x 64,
 // 25 steps, 52 and 122 (binary32), 53 and 138; but 2^3 x 16384 288 and 154, 466 and
-// 208: in a slice of fewer than 48 sites lanes idle, which many slices pay for.
-// Binary32 slices above 256 sites take more steps to pay for being loaded by one
-// workgroup: 1024 sites x 64 times, 2, 5 and 25 steps 22 and 19, 30 and 30, 86 and
-// 128; a little so do slices whose last wavefront is partly filled (96 sites x 16384,
-// 2 and 5 steps 76 and 71, 149 and 185).
+// 208: in a slice of fewer than 48 sites lanes idle, which many slices pay for (4^2 x 2
+// x 4096, 2, 5 and 25 steps 22 and 21, 31 and 36, 88 and 155; 4 x 2^2 x 16384, 25 steps,
+// 270 and 214).  Binary32 slices above 256 sites take more
+// steps to pay for being loaded by one workgroup: 1024 sites x 64 times, 2, 5 and 25
+// steps 22 and 19, 30 and 30, 86 and 128; a little so do slices that leave a quarter
+// of their lanes idle (96 sites x 16384, 2 and 5 steps 76 and 71, 149 and 185).
 constexpr bool ape_in_slices(bool f32, int ns, int nt, int nsteps) {
-    if (ns > ape_slice(f32) || nsteps < 2 || (ns < 48 && nt > 512)) return false;
-    return !f32 || nsteps >= (ns > 256 ? 6 : ns % 64 ? 3 : 2);
+    if (ns > ape_slice(f32) || nsteps < 2) return false;
+    if (ns < 48 && nt > (ns >= 24 && nsteps >= 5 ? 4096 : 64 * ns)) return false;
+    return !f32 || nsteps >= (ns > 256 ? 5 : 4 * ns <= 3 * ((ns + 63) / 64 * 64) ? 3 : 2);
 }
 void launch_ape_slices(const KArgs &a, bool f32, int ns, int nt, const void *src, int src_raw, void *dst, double alpha,
                        int nsteps, hipStream_t s);

@@ -110,15 +110,20 @@ def test_wilson_bounds_in_turn(host, dims):
 @pytest.mark.parametrize("dims,steps,f64,f32", [
     ((2, 2, 2, 512), 25, True, True),
     ((2, 2, 2, 514), 25, False, False),    # idle lanes: one launch per step
+    ((4, 4, 2, 2048), 2, True, False),
+    ((4, 4, 2, 2050), 4, False, False),
+    ((4, 4, 2, 4096), 5, True, True),
+    ((4, 4, 2, 4098), 5, False, False),
     ((4, 2, 2, 65536), 5, False, False),
     ((6, 4, 2, 65536), 3, True, True),
     ((4, 4, 4, 4), 2, True, True),
     ((4, 4, 4, 4), 1, False, False),
-    ((6, 4, 4, 64), 2, True, False),       # a partly filled wavefront
+    ((6, 4, 4, 64), 2, True, False),       # a quarter of the lanes idle
+    ((6, 6, 6, 64), 2, True, True),
     ((8, 8, 4, 64), 2, True, True),
-    ((8, 8, 8, 64), 5, True, False),       # large slices
-    ((8, 8, 8, 64), 6, True, True),
-    ((16, 8, 8, 4), 6, False, True),
+    ((8, 8, 8, 64), 4, True, False),       # large slices
+    ((8, 8, 8, 64), 5, True, True),
+    ((16, 8, 8, 4), 5, False, True),
     ((16, 8, 10, 4), 25, False, False),
 ])
 def test_smearing_ways(host, dims, steps, f64, f32):
