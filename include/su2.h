@@ -36,8 +36,10 @@
  *    and the count is cleared once reported.
  *  - A handle is not thread-safe; separate handles are independent.
  *  - Precision SU2_F32 keeps links in binary32 and does every global
- *    reduction and the reunitarisation norm in binary64 (compensated
- *    two-sum accumulation); SU2_F64 is binary64 throughout.
+ *    reduction and the reunitarisation norm in binary64; SU2_F64 is binary64
+ *    throughout.  Reductions are of compensated (two-sum) pairs, formed after
+ *    a lane's own terms and, for the plaquette series of lattices that take
+ *    launches and for Wilson loops, a wavefront's are added in plain binary64.
  *  - Random numbers: Philox4x32-10 (Salmon et al., SC'11), key = seed,
  *    counter = (site, sweep, lattice_id<<8 | purpose<<4 | mu<<1 | parity,
  *    try).  A link update uses one call per try of its a0 draw and the
@@ -169,16 +171,19 @@ su2_status su2_ape_smear(su2_lattice lat, double alpha, int nsteps);
  * three spatial directions.  Spatial lines use the smeared links when
  * su2_ape_smear produced them since the last update, else the raw links;
  * the temporal sides always use the raw links.  The handle keeps a device
- * buffer of the links in the temporal gauge, (1 + Tmax/Nt) V times 92 bytes
- * (SU2_F32) or 152 bytes (SU2_F64), grown on demand and kept, so that repeated
- * measurements allocate nothing; freed with the handle.
+ * buffer, grown on demand and kept, so that repeated measurements allocate
+ * nothing; freed with the handle: the links in the temporal gauge, (1 +
+ * Tmax/Nt) V times 92 bytes (SU2_F32) or 152 bytes (SU2_F64), or, for few (R, T)
+ * and for small time slices in great number, and where the other buffer cannot be
+ * had, the spatial lines, 3 Rmax V times 16 or 32 bytes.  Links may have any norm
+ * (a caller's own buffer): temporal links far from unit norm take a second pass.
  * Rmax <= min(Nx,Ny,Nz), Tmax <= min(Nt, 32), else EINVAL.
  * Synchronises. */
 su2_status su2_wilson_loops(su2_lattice lat, int Rmax, int Tmax, double *out);
 
 /* Free the measurement buffers the handle keeps between calls: the smeared
- * links (2 x 3V links), the gauge-rotated links of the Wilson loops (81 MB
- * for Tmax = 16 at 24^3 x 48 in binary32) and the Wilson-loop partials.  The
+ * links (2 x 3V links), the gauge-rotated links or lines of the Wilson loops
+ * (81 MB for Tmax = 16 at 24^3 x 48 in binary32) and the Wilson-loop partials.  The
  * next su2_ape_smear / su2_wilson_loops allocates them again; the smeared
  * links are gone (su2_get_smeared: ESTATE).  Synchronises. */
 su2_status su2_release_buffers(su2_lattice lat);
@@ -239,16 +244,29 @@ su2_status su2_load(const char *path, su2_lattice *out);
  * multiple of 8), the tile mode (0: tiles round-robin over the XCDs; 1: each
  * XCD takes a contiguous share of the tile list; 2: as 1, with the heat-bath
  * tiles of every direction in (z, t, y, x) order, which modes 0 and 1 use for
- * the temporal direction only and beyond 32 MiB of links; 3: as 1, with each lattice's heat-bath tiles
- * in eight blocks -- (z half, t quarter) for mu < 3, (z quarter, y half) for
- * mu = 3 -- so that an XCD's share reads fewer halo links), and heat-bath
- * links per lane (1, 2 or 4: a
- * lane draws its links in one rejection loop).  Link updates do not depend
- * on it; reductions only in rounding.  EINVAL for other values. */
+ * the temporal direction only and beyond 32 MiB of links; 3: as 1, with each
+ * lattice's heat-bath tiles in eight blocks -- (z half, t quarter) for mu < 3,
+ * (z quarter, y half) for mu = 3 -- so that an XCD's share reads fewer halo
+ * links; over-relaxation takes the blocks only on lattices that a new handle
+ * would start in mode 3), and heat-bath links per lane (1, 2 or 4: a lane draws
+ * its links in one rejection loop).  Link updates do not depend on it;
+ * reductions only in rounding.  EINVAL for other values.
+ * Some launches have a shape of their own: runs of small lattices (see
+ * su2_ensemble_run) and smearing of small time slices take none of it;
+ * heat-bath substeps of few sites, where four lanes share a link (one link per
+ * lane only: at most 2^17 sites in all with the Creutz sampler, 2^15 with the
+ * hybrid one in binary64), take the block and the tile order, XCD by XCD whatever
+ * the grid and mode; Wilson loops take the block at most.  A handle whose shape
+ * was never set measures and smears XCD by XCD where that is the faster walk,
+ * whatever mode it starts in. */
 su2_status su2_set_launch(su2_lattice lat, int block, int grid, int xcd_remap, int links_per_lane);
 su2_status su2_get_launch(su2_lattice lat, int *block, int *grid, int *xcd_remap, int *links_per_lane);
 /* Time the candidate launch shapes on this lattice and keep the fastest
- * (the links are saved and restored around the trial sweeps). */
+ * (the links are saved and restored around the trial sweeps).  The trials are
+ * launches of single substeps, also on lattices whose runs are one launch and
+ * take no shape.  Shapes found are kept by the process for later handles of the
+ * same extents, precision and sampler; a shape without memory for its tables is
+ * passed over. */
 su2_status su2_autotune(su2_lattice lat, double beta);
 
 /* Per-kernel timing with HIP events on the handle's stream (enable = 1
@@ -314,15 +332,16 @@ su2_status su2_ensemble_set_sampler(su2_ensemble ens, su2_sampler sampler);
  * poly[i*M + k]; the last nsweeps % measure_every sweeps measure nothing.
  * Either pointer may be NULL to skip that measurement.  The sweeps (eight
  * substep launches each; the plaquette is summed inside the odd substeps of
- * measured sweeps) are replayed from captured HIP graphs -- or, where no
- * lattice has more than 1024 sites and every lattice finds room on a compute
- * unit, run as one launch with one workgroup per lattice: a run of 2 to 256
+ * measured sweeps) are replayed from captured HIP graphs: a run of 2 to 256
  * sweeps is one graph (run state, sweeps, series reduction and error word),
  * captured on the first run of that length, measure_every and measurement
  * choice; longer runs replay graphs of up to 16 sweeps (environment
  * SU2_GRAPH_SWEEPS) and of the smaller powers of two.  Partial sums are
  * reduced once per batch of measurements and the series stay on the device
- * until the end.  Measuring does not change the Markov chain.
+ * until the end.  Where no lattice has more than 1024 sites (binary32), 512
+ * (binary64) or 256 (Creutz sampler), and all of them find room on the compute
+ * units at once, a run is one launch instead, one workgroup per lattice.
+ * Measuring does not change the Markov chain.
  * Synchronises once; ENUMERIC as for su2_heatbath.  measure_every >= 1,
  * nsweeps >= 0, else EINVAL.  Environment SU2_NO_GRAPH launches every
  * kernel directly. */

@@ -161,8 +161,8 @@ struct WPlan {
 };
 // Split of the times after toff, at most `step` (16, 8 or 4) of them; false if
 // none fits the LDS.  The sums of a pass take 8 Rmax step bytes per wavefront,
-// which at 16 times leaves no room for the lines from some Rmax on (binary64:
-// 62 sites, T > 16).
+// which at 16 times leaves no room for the lines from some Rmax on (cubes with Rmax
+// their side: 82 sites in binary64, 112 in binary32; at 8 times 138 in binary64).
 bool wloops_plan(bool f32, const int *n, int Rmax, int Tmax, int toff, int step, WPlan &out);
 void launch_wgauge(const KArgs &a, bool f32, int ns, int next, void *P, hipStream_t s);
 void launch_wlinks(const KArgs &a, bool f32, const int *n, const void *sp, int sp_raw, int next, const void *P, void *L,
