@@ -969,7 +969,7 @@ su2_status measure_plaquette(su2_ensemble_s *E, int l, double *avg, double *sp, 
 su2_status measure_polyakov(su2_ensemble_s *E, int l, double *out) {
     hipStream_t s = E->stream();
     const KArgs a = xcd_args(E, 1);  // 128^3 x 8 73 us, 79 in round robin; 64^3 x 8 28 and 30
-    const bool one = E->n == 1 && E->nstiles <= su2::ONE_TILES && !E->timing;
+    const bool one = E->n == 1 && su2::polyakov_in_one(E->f32, E->nstiles, E->hdesc[0].n[3]) && !E->timing;
     if (one) {
         su2::launch_polyakov_one(a, E->f32, E->block, E->dres, E->derr, s);
     } else {

@@ -97,6 +97,15 @@ void launch_polyakov(const KArgs &a, bool f32, double *part, int block, int grid
 // The same measurements of a single lattice of at most ONE_TILES tiles in one
 // launch: results and error word straight to mapped host memory.
 constexpr int ONE_TILES = 2;
+// The Polyakov loop so, and up to which Nt: two tiles' products of Nt links follow
+// one another there, and in binary64 wait longer for their loads.  us a call and in
+// two launches: 4^4 18 and 23 (both precisions); binary32 8 x 8 x 6 x 64 25.5 and 26.4,
+// 8^3 x 128 33 and 31, x 1024 230 and 98, one tile 4^3 x 4096 263 and 277; binary64 8^3
+// x 16 22.5 and 24.5, 8 x 8 x 6 x 64 36 and 29, 8^3 x 1024 582 and 135, one tile 2^3 x 64
+// 25 and 26, 4^3 x 4096 1376 and 462.
+constexpr bool polyakov_in_one(bool f32, int tiles, int Nt) {
+    return tiles == 1 ? f32 || Nt <= 64 : tiles <= ONE_TILES && Nt <= (f32 ? 64 : 24);
+}
 void launch_plaquette_one(const KArgs &a, bool f32, int block, double *out, unsigned *err, hipStream_t s);
 void launch_polyakov_one(const KArgs &a, bool f32, int block, double *out, unsigned *err, hipStream_t s);
 // Final reduction of the standalone measurements: `chunks` workgroups per

@@ -247,3 +247,23 @@ def test_tuned_shape_is_of_the_same_lattice_and_sampler(host):
     assert tuned((10, 12, 14, 16), sampler=CREUTZ) and not tuned((10, 12, 14, 16), sampler=CREUTZ)
     assert tuned((14, 12, 10, 16)) and tuned((10, 14, 12, 16))   # as many sites, the same Nt
     assert tuned((10, 12, 14, 16), prec=F32)
+
+
+@pytest.mark.parametrize("dims,f64,f32", [
+    ((4, 4, 4, 4), 1, 1),
+    ((2, 2, 2, 64), 1, 1),
+    ((2, 2, 2, 66), 2, 1),       # one tile
+    ((4, 4, 4, 4096), 2, 1),
+    ((8, 8, 8, 24), 1, 1),
+    ((8, 8, 8, 26), 2, 1),       # two tiles, one after the other in one launch
+    ((8, 8, 8, 64), 2, 1),
+    ((8, 8, 8, 66), 2, 2),
+    ((8, 8, 10, 4), 2, 2),       # three tiles
+])
+def test_polyakov_launches(host, dims, f64, f32):
+    for prec, n in ((F64, f64), (F32, f32)):
+        h = host.create(dims, prec)
+        host.lib.stub_clear()
+        assert host.lib.su2_polyakov(h, (C.c_double * 1)()) == OK
+        assert len(host.names()) == n
+        assert host.lib.su2_destroy(h) == OK
