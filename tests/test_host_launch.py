@@ -79,8 +79,10 @@ def test_long_lines_take_fewer_times(host, n, nt, T, prec, kernels):
 
 
 def test_wilson_first_call_allocates_no_host_memory(host):
+    before = host.lib.stub_host_mallocs()
     h = host.create((8, 8, 8, 12))
     n = host.lib.stub_host_mallocs()
+    assert n == before + 1     # results and state words of a handle together
     assert host.wilson(h, 4, 6) == OK and host.wilson(h, 8, 12) == OK and host.lib.stub_host_mallocs() == n
     assert host.lib.su2_destroy(h) == OK
 
