@@ -260,6 +260,11 @@ __device__ __forceinline__ DD dd_add(DD a, DD b) {
     double h = s + e;
     return DD{h, e - (h - s)};
 }
+// v + x for a lane's running sum, the low part a plain sum of the errors
+__device__ __forceinline__ DD dd_acc(DD v, double x) {
+    const double s = v.hi + x, b = s - v.hi;
+    return DD{s, v.lo + ((v.hi - (s - b)) + (x - b))};
+}
 
 // Wavefront sums that need no lane-index registers: XOR butterflies within
 // each 32-lane half by ds_swizzle in bit-mask mode (lane j reads lane j ^ X),

@@ -664,11 +664,12 @@ __device__ __forceinline__ void small_copy(const LatDesc &d, char *links, float4
 // over-relaxation) of lattice blockIdx.x.  Measured sweeps write the mean
 // plaquette, of the links' terms as in k_heatbath, and the Polyakov loop to
 // outp / outl[l * nm + measurement], both summed in (hi, lo) pairs from the
-// lane on.
+// lane on; runs without measurements take the kernel without them (4^4, one sweep
+// in binary32: 19.6 us, 21.1 with the sums' code in it).
 // FOUR: four lanes per link (heat bath; the workgroup holds them all).  Figures
 // at small_sites().  The time is the instructions of one wavefront's update,
 // issued alone on its SIMD.
-template <class T, bool FOUR>
+template <class T, bool FOUR, bool MEAS>
 __global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, double *outp, double *outl,
                                                            unsigned *errp) {
     extern __shared__ double4 small_lds[];
@@ -683,7 +684,7 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, 
     unsigned long long tries = 0;
     int next = r.every - 1, m = 0;  // sweep of the next measurement
     for (int sw = 0; sw < r.nsweeps; ++sw) {
-        const bool measured = sw == next && m < r.nm;
+        const bool measured = MEAS && sw == next && m < r.nm;
         DD sum[2] = {{0.0, 0.0}, {0.0, 0.0}};  // plaquette, Polyakov loop
         for (int sub = 0; sub < 8; ++sub) {
             const int mu = sub >> 1, par = sub & 1;
@@ -695,22 +696,22 @@ __global__ __launch_bounds__(SMALL_BLOCK) void k_small_run(KArgs a, SmallRun r, 
                     const Site S = site_of(d, valid ? cb : 0, par);
                     uint32_t wt = 0;
                     double pw = 0.0;
-                    heatbath_link4<T, true>(
+                    heatbath_link4<T, MEAS>(
                         S, valid, mu, beta, a.sampler, sweep, c2, k0, k1, a.err, wt, pw,
                         [&](Q<T>(&L)[18]) { gather_lds(d, B, S, par, mu, L); },
                         [&](const Q<T> &U) { B.st(mu, par, cb, U); });
                     tries += wt;
-                    if (par && measured) sum[0] = dd_add(sum[0], DD{pw, 0.0});
+                    if (MEAS && par) sum[0] = dd_acc(sum[0], pw);
                 }
                 for (int first = tid; !FOUR && first - lane < d.vh; first += nb) {
                     uint32_t wt = 0;
                     double pw = 0.0;
-                    heatbath_links<T, 1, true>(
+                    heatbath_links<T, 1, MEAS>(
                         d, par, first, beta, a.sampler, sweep, c2, k0, k1, a.err, wt, pw,
                         [&](const Site &S, Q<T> *Vlow) { return staple_lds<T>(d, B, S, par, mu, Vlow); },
                         [&](int cb, int, const Q<T> &U, uint32_t) { B.st(mu, par, cb, U); });
                     tries += wt;
-                    if (par && measured) sum[0] = dd_add(sum[0], DD{pw, 0.0});
+                    if (MEAS && par) sum[0] = dd_acc(sum[0], pw);
                 }
             } else {
                 for (int cb = tid; cb < d.vh; cb += nb) {
@@ -2063,8 +2064,11 @@ bool launch_small_run(const KArgs &a, bool f32, int nlat, int sites, const Small
     const size_t lds = small_lds_bytes(f32, sites);
     const bool four = small_four(a.sampler == 1, r.over != 0);
     const int block = std::min(SMALL_BLOCK, ((four ? 4 : 1) * sites / 2 + 63) / 64 * 64);
-    const auto k = f32 ? (four ? k_small_run<float, true> : k_small_run<float, false>)
-                       : (four ? k_small_run<double, true> : k_small_run<double, false>);
+    const bool meas = r.nm > 0;
+    const auto k = f32 ? (four ? (meas ? k_small_run<float, true, true> : k_small_run<float, true, false>)
+                               : (meas ? k_small_run<float, false, true> : k_small_run<float, false, false>))
+                       : (four ? (meas ? k_small_run<double, true, true> : k_small_run<double, true, false>)
+                               : (meas ? k_small_run<double, false, true> : k_small_run<double, false, false>));
     // the same limit from every call: it belongs to the kernel, and another
     // thread's launch may come between this one and its own
     if (lds > (48 << 10) &&
