@@ -45,15 +45,15 @@ INFINITY_CACHE_BYTES = 256 << 20
 # per lane; a grid of 0 counts as its effective size, one workgroup per
 # tile).  Valid only for the sources whose code (comments and layout aside)
 # has this hash: the kernels and the host code that orders their tiles.
-HB_TRAFFIC = {"sources_sha256": "cc30362cdd12b4caef656dcdffa1bd1b5696d32a3258342ba1568fcb2bcd7a63",
-              "by_launch": {(128, 4096, 3, 1): 74334342, (64, 8192, 3, 1): 74306786,
-                            (256, 2048, 3, 1): 74138146, (64, 8192, 1, 1): 79569634,
-                            (64, 7168, 3, 1): 77089487, (128, 3584, 3, 1): 78368733,
-                            (256, 1792, 3, 1): 76802855, (64, 4096, 3, 1): 74336629,
-                            (128, 2048, 3, 1): 74482522, (256, 1024, 3, 1): 74204298,
-                            (64, 4096, 3, 2): 76584681, (128, 2048, 3, 2): 76107927},
+HB_TRAFFIC = {"sources_sha256": "36b93c946688edd76c74b8967f2d44af318c34832bfb23291780d0ee0ecacfbe",
+              "by_launch": {(128, 4096, 3, 1): 74337175, (64, 8192, 3, 1): 74298614,
+                            (256, 2048, 3, 1): 74126085, (64, 8192, 1, 1): 79484975,
+                            (64, 7168, 3, 1): 77144531, (128, 3584, 3, 1): 78445691,
+                            (256, 1792, 3, 1): 76873983, (64, 4096, 3, 1): 74314150,
+                            (128, 2048, 3, 1): 74460950, (256, 1024, 3, 1): 74175592,
+                            (64, 4096, 3, 2): 76566218, (128, 2048, 3, 2): 76178128},
               # the 64^4 control: 1 GiB algorithmic per launch
-              "control64": {(256, 32768, 0, 1): 1306138254}}
+              "control64": {(256, 32768, 0, 1): 1306443843}}
 KERNEL_SOURCES = ("su2_kernels.hip", "su2_device.hpp", "su2_internal.hpp", "su2_api.hip")
 
 
