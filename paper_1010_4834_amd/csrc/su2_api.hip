@@ -826,8 +826,8 @@ su2_status capture_run(su2_ensemble_s *E, int meas, int every, int nsweeps, hipG
 // within its LDS.  At those eight, us per substep here and as replayed launches:
 // 1024 lattices of 4^4 2.9 and 5.5 (binary32), 6.7 and 11.5; 256 of 1024 sites 2.9
 // and 5.4; 256 of 4^4 with Creutz 4.2 and 13.7, 6.3 and 16.1.  Where lattices would
-// queue for CUs the batched substeps keep the whole chip busy instead.  Not while tries are recorded per link or
-// kernels timed one by one, nor under SU2_NO_GRAPH.
+// queue for CUs the batched substeps keep the whole chip busy instead.  Not while
+// tries are recorded per link or kernels timed one by one, nor under SU2_NO_GRAPH.
 bool small_run_ok(const su2_ensemble_s *E, bool over) {
     if (E->trace || E->timing || E->n > 8 * 256 || std::getenv("SU2_NO_GRAPH")) return false;
     const bool creutz = E->sampler == SU2_CREUTZ;

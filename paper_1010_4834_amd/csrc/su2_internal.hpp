@@ -156,8 +156,9 @@ constexpr bool ape_in_slices(bool f32, int ns, int nt, int nsteps) {
 void launch_ape_slices(const KArgs &a, bool f32, int ns, int nt, const void *src, int src_raw, void *dst, double alpha,
                        int nsteps, hipStream_t s);
 // Wilson loops: prefix products of the temporal links (times 0 .. next - 1),
-// the spatial links and weights in that gauge, line by line, the loop traces of one pass of times (several passes beyond T = 16) and
-// their final sums, written to mapped host memory with the error word.
+// the spatial links and weights in that gauge, line by line, the loop traces of
+// one pass of times (several passes beyond T = 16) and their final sums, written
+// to mapped host memory with the error word.
 constexpr int wl_ke(bool f32) { return f32 ? 8 : 6; }  // line elements per lane at most
 struct WDir {             // split of one direction, see k_wloops
     int N, lines, XC, XE, G, TC, NB, ngrp, nxc, ntc, unit0;
